@@ -1,7 +1,6 @@
 // C ABI of libh3flash: argument validation and kernel dispatch.
 // Every check runs on the host before anything is enqueued.
 #include <stdint.h>
-#include <algorithm>
 #include <stdlib.h>
 #include <string.h>
 
@@ -269,13 +268,9 @@ size_t h3_workspace_size(int op, int B, int H, int L, int m, int chunk, int dtyp
             if (chunk == 1) return layer_ws(B, H, L).total;
             if (chunk != 2 && chunk != 4 && chunk != 8) return 0;
             return heads_ws(B, H, L, chunk).total;
-        case H3_OP_FFTCONV_BWD: {
-            // the spectrum of the du pass, then (same bytes, later in stream
-            // order) the kernel-gradient partial sums
-            size_t n = align_up(fftconv_workspace(B, H, L));
-            if (fftconv_wave_supported(L, dtype)) n = std::max(n, align_up(wgrad_wave_workspace(B, H)));
-            return n;
-        }
+        case H3_OP_FFTCONV_BWD:
+            // the spectrum of the du pass
+            return align_up(fftconv_workspace(B, H, L));
     }
     return 0;
 }
@@ -386,8 +381,8 @@ int h3_fftconv_bwd(const void *u, const float *k, const float *D, const void *dy
     if (dk || dD) {
         const char *sel = getenv("H3FLASH_WGRAD");   // "valu": the float32 VALU kernel at every length
         const bool valu = sel && strcmp(sel, "valu") == 0;
-        if (!valu && fftconv_wave_supported(L, dtype))
-            return launched(launch_wgrad_wave(u, dy, B, H, dtype, dk, dD, workspace, s));
+        if (!valu && wgrad_direct_supported(L, dtype))
+            return launched(launch_wgrad_direct(u, dy, B, H, L, dtype, dk, dD, s));
         return launched(launch_conv_wgrad(u, dy, B, H, L, dtype, dk, dD, s));
     }
     return launched(hipSuccess);

@@ -1,5 +1,6 @@
 // Kernel and skip gradients of the fused FFT convolution (the appendix on
-// the backward pass of FlashConv).  For y = k * u + D u and output gradient
+// the backward pass of FlashConv) for float32 rows, and for 16-bit rows
+// shorter than 256.  For y = k * u + D u and output gradient
 // dy, per channel h:
 //     dk = Re IFFT( sum_b conj(F u_b) . F dy_b )[:L],      dD = sum_{b,t} u dy,
 // with F the length-N = 2L DFT of the zero-padded rows.  Correlating through

@@ -94,13 +94,11 @@ size_t fftconv_workspace(int B, int H, int L);
 // null).  u, dy (B, H, L) of dtype.
 hipError_t launch_conv_wgrad(const void *u, const void *dy, int B, int H, int L, int dtype, float *dk, float *dD,
                              hipStream_t s);
-// The same on the matrix cores at L = 2048, 16-bit I/O (fftconv_wave_supported):
-// one workgroup per channel and group of four row pairs; with more than one
-// group per channel the partial sums go to ws (wgrad_wave_workspace bytes)
-// and a reduction kernel writes dk, dD.
-hipError_t launch_wgrad_wave(const void *u, const void *dy, int B, int H, int dtype, float *dk, float *dD,
-                             void *ws, hipStream_t s);
-size_t wgrad_wave_workspace(int B, int H);
+// The same as a direct correlation on the matrix cores: 16-bit I/O, L a power
+// of two in 256 .. 8192.
+bool wgrad_direct_supported(int L, int dtype);
+hipError_t launch_wgrad_direct(const void *u, const void *dy, int B, int H, int L, int dtype, float *dk, float *dD,
+                               hipStream_t s);
 
 // State passing pieces.
 // Optional tail of the matrix-core chunk-state kernel (chunk 8192 or 16384):
