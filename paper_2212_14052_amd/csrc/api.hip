@@ -268,9 +268,19 @@ size_t h3_workspace_size(int op, int B, int H, int L, int m, int chunk, int dtyp
             if (chunk == 1) return layer_ws(B, H, L).total;
             if (chunk != 2 && chunk != 4 && chunk != 8) return 0;
             return heads_ws(B, H, L, chunk).total;
-        case H3_OP_FFTCONV_BWD:
-            // the spectrum of the du pass
-            return align_up(fftconv_workspace(B, H, L));
+        case H3_OP_FFTCONV_BWD: {
+            // the spectrum of the du pass; at L = 2048 (16-bit) also room for
+            // kernel-gradient partial sums per eight rows, which no kernel
+            // uses: the size this entry has always answered, for callers that
+            // keep buffers of it
+            size_t n = align_up(fftconv_workspace(B, H, L));
+            const size_t ng = ((size_t)B + 7) / 8;
+            if (fftconv_wave_supported(L, dtype) && ng > 1) {
+                const size_t part = align_up(ng * H * ((size_t)L + 1) * sizeof(float));
+                if (part > n) n = part;
+            }
+            return n;
+        }
     }
     return 0;
 }
