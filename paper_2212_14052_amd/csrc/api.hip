@@ -40,42 +40,43 @@ bool fused_len_ok(int L, int dtype) {
 
 // Workspace layouts (each region 256-byte aligned).
 //
-// State passing, by path (a region a path does not use has size 0):
+// State passing on the VALU convolution (float32, and 16-bit chunks other than
+// 2048, 8192 and 16384):
 //   k       (H, chunk) float32            the chunk kernel f
-//   kspec   (H, chunk + 1) complex        its spectrum (VALU conv only)
+//   kspec   (H, chunk + 1) complex        its spectrum
 //   states  (B, H, nchunk, m) complex     chunk end-states s_c = M_ux u^(c)
-//   fused initial-state term (16-bit, chunk 8192 or 16384): per-channel power
-//   tables ctab, normalised weights w16 (B, H, nchunk, 64) fp16 complex and
-//   their exponents wexp (B, H, nchunk);
-//   otherwise: weights corr_w (B, H, nchunk, m) complex and the term itself,
-//   corr (B, H, L), in the I/O dtype on the matrix-core paths, else float32.
+//   corr_w  (B, H, nchunk, m) complex     the initial-state term's weights
+//   corr    (B, H, L) float32             the term itself
+// The one-pass kernel takes what it can use of its workspace for segment
+// states, which bounds the segments per row.  The size is the one that this
+// entry has always answered for these chunks: end-states, per-channel tables
+// of 25.6 KB and 260 bytes per chunk at chunks 8192 and 16384; kernel,
+// end-states, weights and a 16-bit term at chunk 2048.
 struct StatepassWs {
-    size_t k, kspec, states, corr_w, corr, ctab, w16, wexp, total;
-    bool fused, mfma, corr16;
+    size_t k, kspec, states, corr_w, corr, total;
+    bool scan;
 };
 StatepassWs statepass_ws(int B, int H, int L, int m, int chunk, int dtype) {
     StatepassWs w{};
     const size_t nchunk = (size_t)(L / chunk);
-    w.fused = fftconv_wave16k_supported(chunk, dtype) || fftconv_wave32k_supported(chunk, dtype);
-    w.mfma = fftconv_mfma_supported(chunk, dtype);
-    w.corr16 = w.mfma && state_correction_mfma_ok(chunk, dtype);
+    w.scan = ssm_scan_supported(chunk, dtype);
     size_t off = 0;
     auto take = [&](size_t bytes) {
         const size_t at = off;
         off += align_up(bytes);
         return at;
     };
-    // the chunk kernel f: the fused-term convs form it themselves
-    if (!w.fused) w.k = take((size_t)H * chunk * sizeof(float));
-    if (!w.mfma) w.kspec = take((size_t)H * (chunk + 1) * sizeof(float2));
-    w.states = take((size_t)B * H * nchunk * m * sizeof(float2));
-    if (w.fused) {
-        w.ctab = take((size_t)H * CORR_TAB_U4 * sizeof(uint4));
-        w.w16 = take((size_t)B * H * nchunk * 64 * sizeof(uint32_t));
-        w.wexp = take((size_t)B * H * nchunk * sizeof(int));
+    if (w.scan && chunk != 2048) {
+        take((size_t)B * H * nchunk * m * sizeof(float2));
+        take((size_t)H * 25600);
+        take((size_t)B * H * nchunk * 64 * 4);
+        take((size_t)B * H * nchunk * 4);
     } else {
+        w.k = take((size_t)H * chunk * sizeof(float));
+        if (!w.scan) w.kspec = take((size_t)H * (chunk + 1) * sizeof(float2));
+        w.states = take((size_t)B * H * nchunk * m * sizeof(float2));
         w.corr_w = take((size_t)B * H * nchunk * m * sizeof(float2));
-        w.corr = take((size_t)B * H * L * (w.corr16 ? 2 : sizeof(float)));
+        w.corr = take((size_t)B * H * L * (w.scan ? 2 : sizeof(float)));
     }
     w.total = off;
     return w;
@@ -177,69 +178,33 @@ int statepass_run(const void *u, const float *Abar, const float *Bbar, const flo
                   char *ws, hipStream_t s) {
     const int nchunk = L / chunk;
     const StatepassWs w = statepass_ws(B, H, L, m, chunk, dtype);
+    // the result does not depend on the chunk: 16-bit rows at the chunks of the
+    // matrix-core convolutions go through the sequence in one pass (B = 2, H =
+    // 1024, L = 131072, chunk 8192, fp16: 305 us, against 705 us for chunk
+    // end-states and a convolution of chunks)
+    if (w.scan) return launched(launch_ssm_scan(u, Abar, Bbar, C, D, x0, B, H, L, m, dtype, y, x_final, ws, w.total, s));
     float *kbuf = (float *)(ws + w.k);
-    float2 *Kspec = w.mfma ? nullptr : (float2 *)(ws + w.kspec);
+    float2 *Kspec = (float2 *)(ws + w.kspec);
     float2 *states = (float2 *)(ws + w.states);
+    float2 *corr_W = (float2 *)(ws + w.corr_w);
+    float *corr = (float *)(ws + w.corr);
     hipError_t e;
-    // f = [C Bbar, C Abar Bbar, ...] of length chunk, and its spectrum (the
-    // L = 8192 and 16384 convs with the fused state term form f themselves)
-    const bool gen_f = w.fused;
-    if (!gen_f && (e = launch_kernel_gen(1, Abar, Bbar, C, nullptr, H, m, chunk, kbuf, s)) != hipSuccess)
+    // f = [C Bbar, C Abar Bbar, ...] of length chunk, and its spectrum
+    if ((e = launch_kernel_gen(1, Abar, Bbar, C, nullptr, H, m, chunk, kbuf, s)) != hipSuccess) return H3_EDEVICE;
+    if ((e = launch_spectrum(kbuf, H, chunk, Kspec, s)) != hipSuccess) return H3_EDEVICE;
+    // s_c = M_ux u^(c) for every chunk, the scan over chunks, M_xy x^(c)
+    if ((e = launch_chunk_states(u, Abar, Bbar, B, H, L, m, chunk, dtype, states, s)) != hipSuccess) return H3_EDEVICE;
+    if ((e = launch_state_scan(Abar, C, x0, states, B, H, m, chunk, nchunk, corr_W, x_final, s)) != hipSuccess)
         return H3_EDEVICE;
-    if (!w.mfma && (e = launch_spectrum(kbuf, H, chunk, Kspec, s)) != hipSuccess) return H3_EDEVICE;
-    // s_c = M_ux u^(c) for every chunk, then the scan over chunks (for the
-    // fused term, inside the chunk-state kernel when it covers each channel
-    // with one workgroup)
-    StateTail tail{C, x0, (uint32_t *)(ws + w.w16), (int *)(ws + w.wexp), x_final, (uint4 *)(ws + w.ctab), 0};
-    bool fused_tail = false;
-    if ((e = launch_chunk_states(u, Abar, Bbar, B, H, L, m, chunk, dtype, states, s, w.fused ? &tail : nullptr,
-                                 &fused_tail)) != hipSuccess)
-        return H3_EDEVICE;
+    if ((e = launch_state_correction(Abar, corr_W, B, H, m, chunk, nchunk, corr, s)) != hipSuccess) return H3_EDEVICE;
     ConvArgs a{};
     a.u = u; a.y = y; a.Kspec = Kspec; a.D = D;
     a.B = B; a.H = H; a.L = chunk; a.nchunk = nchunk; a.pair_mode = 1; a.dtype = dtype;
-    if (w.fused) {
-        // chunk 8192 or 16384: the conv computes M_xy x^(c) itself from normalised
-        // weights (scan output) and per-channel power tables
-        uint4 *ctab = (uint4 *)(ws + w.ctab);
-        uint32_t *w16 = (uint32_t *)(ws + w.w16);
-        int *wexp = (int *)(ws + w.wexp);
-        if (!fused_tail) {
-            if ((e = launch_state_scan_w16(Abar, C, x0, states, B, H, m, chunk, nchunk, w16, wexp, x_final, s)) !=
-                hipSuccess)
-                return H3_EDEVICE;
-            if ((e = launch_corr_tables(Abar, H, m, ctab, s)) != hipSuccess) return H3_EDEVICE;
-        }
-        a.corr = w16;
-        a.corr_tab = ctab;
-        a.corr_e = wexp;
-        if (gen_f) {
-            a.gen_C = C;
-            a.gen_Bbar = Bbar;
-            a.m_gen = m;
-        }
-        return launched(launch_fftconv_mfma(a, gen_f ? nullptr : kbuf, s));
-    }
-    float2 *corr_W = (float2 *)(ws + w.corr_w);
-    void *corr = ws + w.corr;
-    if ((e = launch_state_scan(Abar, C, x0, states, B, H, m, chunk, nchunk, corr_W, x_final, s)) != hipSuccess)
-        return H3_EDEVICE;
-    // M_xy x^(c) for every chunk (in the I/O dtype when the matrix-core paths apply)
-    if (w.corr16)
-        e = launch_state_correction_mfma(Abar, corr_W, B, H, m, chunk, nchunk, dtype, corr, s);
-    else
-        e = launch_state_correction(Abar, corr_W, B, H, m, chunk, nchunk, (float *)corr, s);
-    if (e != hipSuccess) return H3_EDEVICE;
     a.corr = corr;
-    a.corr16 = w.corr16 ? 1 : 0;
-    if (w.mfma) return launched(launch_fftconv_mfma(a, kbuf, s));
     return launched(launch_fftconv(a, s));
 }
 
 }  // namespace h3
-
-namespace {
-}  // namespace
 
 extern "C" {
 
@@ -330,8 +295,6 @@ int h3_fftconv(const void *u, const float *k, const float *D, void *y, int B, in
     ConvArgs a{};
     a.u = u; a.y = y; a.D = D;
     a.B = B; a.H = H; a.L = L; a.nchunk = 1; a.pair_mode = 0; a.dtype = dtype;
-    a.corr = nullptr;
-    a.corr16 = 0;
     if (fftconv_mfma_supported(L, dtype)) return launched(launch_fftconv_mfma(a, k, s));
     if (fftconv_kgen_supported(L)) return launched(launch_fftconv_kgen(a, k, s));
     float2 *Kspec = (float2 *)workspace;
@@ -416,8 +379,6 @@ int h3_fftconv_spectral(const void *u, const float *Kspec, const float *D, void 
     ConvArgs a{};
     a.u = u; a.y = y; a.Kspec = (const float2 *)Kspec; a.D = D;
     a.B = B; a.H = H; a.L = L; a.nchunk = 1; a.pair_mode = 0; a.dtype = dtype;
-    a.corr = nullptr;
-    a.corr16 = 0;
     return launched(launch_fftconv(a, (hipStream_t)stream));
 }
 

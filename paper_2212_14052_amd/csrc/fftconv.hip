@@ -184,7 +184,7 @@ __global__ __launch_bounds__(N / 16 >= 64 ? N / 16 : 64) void fftconv_kernel(Con
             float oa = fmaf(w.x, ya_s, d * ua[q * HALF + r]);
             float ob = fmaf(-w.y, yb_s, d * ub[q * HALF + r]);
             if (a.corr) {
-                const float *cr = (const float *)a.corr;
+                const float *cr = a.corr;
                 oa += cr[pm.oa + n];
                 if (hb) ob += cr[pm.ob + n];
             }

@@ -130,13 +130,12 @@ __device__ __forceinline__ void forward_front(uint32_t (&d)[64], const uint4 *Lc
 // one MFMA per tile suffices: its matrix Fc stacks the real rows 0..7 (rows
 // 0..7 of the product: row a) over the imaginary rows 0..7 (rows 8..15: row
 // b).  Lane (g, c) then holds, for tile tau, the outputs p2 = 4 (g & 1) + i,
-// p1 = c, p0 = tau of row a (g < 2) or row b (g >= 2), times rem (REM), plus
-// the correction term of that row (CORR), times the gate (GATE: the same
-// points of the row at grow), packed two tiles at a time into d[8 s + i]
-// (points p0 = 2 s, 2 s + 1).
-template <int DT, int CORR, bool REM, bool GATE>
-__device__ __forceinline__ void out_layer(uint32_t (&d)[64], const h8_t &Fc, float rem, const void *corr,
-                                          long orow, int lane, const uint16_t *grow) {
+// p1 = c, p0 = tau of row a (g < 2) or row b (g >= 2), times rem (REM), times
+// the gate (GATE: the same points of the row at grow), packed two tiles at a
+// time into d[8 s + i] (points p0 = 2 s, 2 s + 1).
+template <int DT, bool REM, bool GATE>
+__device__ __forceinline__ void out_layer(uint32_t (&d)[64], const h8_t &Fc, float rem, int lane,
+                                          const uint16_t *grow) {
     const int g = lane >> 4, c = lane & 15;
     const int pbase = 256 * (4 * (g & 1)) + 16 * c;
     // gate: gq[2 i + h] holds the gate at points p0 = 8 h .. 8 h + 7 of output
@@ -163,16 +162,6 @@ __device__ __forceinline__ void out_layer(uint32_t (&d)[64], const h8_t &Fc, flo
         float yv[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) yv[i] = REM ? v[i] * rem : v[i];
-        if (CORR != 0) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int p = pbase + 256 * i + tau;
-                if (CORR == 2)
-                    yv[i] += lo_f<DT>(((const uint16_t *)corr)[orow + p]);
-                else
-                    yv[i] += ((const float *)corr)[orow + p];
-            }
-        }
         if constexpr (GATE) {
             // gate values of this lane's points: gq[2 i + tau / 8], half tau % 8
 #pragma unroll
@@ -197,14 +186,13 @@ __device__ __forceinline__ void out_layer(uint32_t (&d)[64], const h8_t &Fc, flo
 }  // namespace wv
 
 // ============================================================================
-// CORR: 0 none, 1 float32 correction term, 2 correction term in the I/O dtype.
 // CPW: channels per workgroup.  1: the four waves share one channel's row
 // pairs.  2 (at most two row pairs per channel, e.g. batch 4): channels
 // 2 hb and 2 hb + 1, both spectra computed by all four waves, then waves 0, 1
 // take the first channel's pairs and waves 2, 3 the second's, so no wave
 // idles while its workgroup holds the CU's LDS.
 // GATE: the output is multiplied by a.gate (same layout as y) before rounding.
-template <int DT, int CORR, int CPW, bool CT = false, bool GATE = false>
+template <int DT, int CPW, bool CT = false, bool GATE = false>
 __global__ __launch_bounds__(wv::NT) __attribute__((amdgpu_waves_per_eu(CPW == 1 || CT ? 3 : 2))) void
 fftconv_wave4096_kernel(ConvArgs a, const float *k, int wg_per_ch, int pairs_per_ch) {
     using namespace wv;
@@ -230,15 +218,8 @@ fftconv_wave4096_kernel(ConvArgs a, const float *k, int wg_per_ch, int pairs_per
     uint16_t *y = (uint16_t *)a.y;
 
     auto rows = [&](int qq, long &oa, long &ob) {
-        if (a.pair_mode == 0) {
-            oa = ((long)(2 * qq) * a.H + h) * L;
-            ob = (2 * qq + 1 < a.B) ? ((long)(2 * qq + 1) * a.H + h) * L : -1;
-        } else {
-            const int ncp = (a.nchunk + 1) / 2;
-            const int bb = qq / ncp, cp = qq % ncp;
-            oa = (((long)bb * a.H + h) * a.nchunk + 2 * cp) * L;
-            ob = (2 * cp + 1 < a.nchunk) ? oa + L : -1;
-        }
+        oa = ((long)(2 * qq) * a.H + h) * L;
+        ob = (2 * qq + 1 < a.B) ? ((long)(2 * qq + 1) * a.H + h) * L : -1;
     };
     // raw loads of a pair: lanes g < 2 hold points p2 = 4 g + j (j = 0..3),
     // p1 = c, p0 = 0..15 of both rows (8 consecutive 16-bit values per uint4)
@@ -539,14 +520,13 @@ fftconv_wave4096_kernel(ConvArgs a, const float *k, int wg_per_ch, int pairs_per
         // branch-free epilogue (a branch inside it lets the compiler hoist
         // all of the layer's MFMAs above it); the rare remainder scale picks
         // a second instance of the layer instead
-        const long obc = ob >= 0 ? ob : oa;   // row b's correction read from row a if absent
-        const long orow = lane_b ? obc : oa;
+        const long orow = lane_b && ob >= 0 ? ob : oa;
         // gate of the lane's 64 outputs (row a or b; a missing row b reads row a's)
         const uint16_t *grow = GATE ? (const uint16_t *)a.gate + orow : nullptr;
         if ((srema | sremb) == 0)
-            out_layer<DT, CORR, false, GATE>(d, Fc, 1.0f, a.corr, orow, lane, grow);
+            out_layer<DT, false, GATE>(d, Fc, 1.0f, lane, grow);
         else
-            out_layer<DT, CORR, true, GATE>(d, Fc, ldexpf(1.0f, lane_b ? sremb : srema), a.corr, orow, lane, grow);
+            out_layer<DT, true, GATE>(d, Fc, ldexpf(1.0f, lane_b ? sremb : srema), lane, grow);
         if (!lane_b || ob >= 0) {
             uint16_t *yrow = y + orow;
             const int gl = g & 1;
@@ -568,18 +548,14 @@ bool fftconv_wave_supported(int L, int dtype) { return L == wv::L && (dtype == F
 
 hipError_t launch_fftconv_wave(const ConvArgs &a, const float *k, hipStream_t s) {
     if (!fftconv_wave_supported(a.L, a.dtype)) return hipErrorInvalidValue;
-    int pairs_per_ch;
-    if (a.pair_mode == 0)
-        pairs_per_ch = (a.B + 1) / 2;
-    else
-        pairs_per_ch = a.B * ((a.nchunk + 1) / 2);
+    if (a.pair_mode != 0 || a.corr) return hipErrorInvalidValue;
+    const int pairs_per_ch = (a.B + 1) / 2;
     // split a channel over several workgroups only while the chip would hold
     // fewer than ~2 waves per SIMD and each wave still gets a pair
     int wg_per_ch = 1;
     while ((long)a.H * wg_per_ch * wv::NW < 2048 && pairs_per_ch >= 2 * wv::NW * wg_per_ch) wg_per_ch *= 2;
     dim3 grid(a.H * wg_per_ch), block(wv::NT);
-    const int corr = a.corr == nullptr ? 0 : (a.corr16 ? 2 : 1);
-    if (corr == 0 && a.pair_mode == 0 && pairs_per_ch <= 2 && wg_per_ch == 1 && a.H >= 2) {
+    if (pairs_per_ch <= 2 && wg_per_ch == 1 && a.H >= 2) {
         // two channels per workgroup: every wave has a row pair.  From two
         // workgroups per CU on (512 and more) the instance with the compact
         // table runs three per CU (B = 4: 51 -> 48 us at H = 2560, 337 -> 300
@@ -588,7 +564,7 @@ hipError_t launch_fftconv_wave(const ConvArgs &a, const float *k, hipStream_t s)
         const dim3 grid2((a.H + 1) / 2);
         const bool ct = grid2.x >= 512;
 #define H3_WAVE2_LAUNCH(DTV, CTV, GV) \
-    hipLaunchKernelGGL((fftconv_wave4096_kernel<DTV, 0, 2, CTV, GV>), grid2, block, 0, s, a, k, 1, pairs_per_ch)
+    hipLaunchKernelGGL((fftconv_wave4096_kernel<DTV, 2, CTV, GV>), grid2, block, 0, s, a, k, 1, pairs_per_ch)
 #define H3_WAVE2_CT(DTV, GV) \
     do {                                   \
         if (ct) H3_WAVE2_LAUNCH(DTV, true, GV); \
@@ -605,26 +581,14 @@ hipError_t launch_fftconv_wave(const ConvArgs &a, const float *k, hipStream_t s)
 #undef H3_WAVE2_LAUNCH
         return hipGetLastError();
     }
-#define H3_WAVE_LAUNCH(DTV, CV) \
-    hipLaunchKernelGGL((fftconv_wave4096_kernel<DTV, CV, 1>), grid, block, 0, s, a, k, wg_per_ch, pairs_per_ch)
-    if (a.gate) {
-        if (corr != 0 || a.pair_mode != 0) return hipErrorInvalidValue;
-        if (a.dtype == F16)
-            hipLaunchKernelGGL((fftconv_wave4096_kernel<F16, 0, 1, false, true>), grid, block, 0, s, a, k, wg_per_ch,
-                               pairs_per_ch);
-        else
-            hipLaunchKernelGGL((fftconv_wave4096_kernel<BF16, 0, 1, false, true>), grid, block, 0, s, a, k, wg_per_ch,
-                               pairs_per_ch);
-        return hipGetLastError();
-    }
+#define H3_WAVE_LAUNCH(DTV, GV) \
+    hipLaunchKernelGGL((fftconv_wave4096_kernel<DTV, 1, false, GV>), grid, block, 0, s, a, k, wg_per_ch, pairs_per_ch)
     if (a.dtype == F16) {
-        if (corr == 0) H3_WAVE_LAUNCH(F16, 0);
-        else if (corr == 1) H3_WAVE_LAUNCH(F16, 1);
-        else H3_WAVE_LAUNCH(F16, 2);
+        if (a.gate) H3_WAVE_LAUNCH(F16, true);
+        else H3_WAVE_LAUNCH(F16, false);
     } else {
-        if (corr == 0) H3_WAVE_LAUNCH(BF16, 0);
-        else if (corr == 1) H3_WAVE_LAUNCH(BF16, 1);
-        else H3_WAVE_LAUNCH(BF16, 2);
+        if (a.gate) H3_WAVE_LAUNCH(BF16, true);
+        else H3_WAVE_LAUNCH(BF16, false);
     }
 #undef H3_WAVE_LAUNCH
     return hipGetLastError();

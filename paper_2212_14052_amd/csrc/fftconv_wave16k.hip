@@ -88,7 +88,6 @@ __device__ const Half16 kHalf16 = make_half16();
 //   [8..11] w_16384^{k3 (4g+i)}        third layer, contraction point i
 //   [12]    w_16384^{-k3 c}            inverse third layer, output row c
 //   [13]    w_1024^{-k3 c}             inverse second layer's lane twiddles
-//   [14,15] w_64^{-c}, w_64^{-2c}      last layer's rows, when not tabulated
 struct Fac16 {
     uint32_t v[4 * 64 * 16];
 };
@@ -109,9 +108,6 @@ constexpr Fac16 make_fac16() {
             const Cd r3 = cwd(-k3 * c, N), rx = cwd(-k3 * c, 1024);
             p[12] = h2_bits(r3.re, r3.im);
             p[13] = h2_bits(rx.re, rx.im);
-            const Cd g1 = cwd(-c, 64), g2 = cwd(-2 * c, 64);
-            p[14] = h2_bits(g1.re, g1.im);
-            p[15] = h2_bits(g2.re, g2.im);
         }
     return t;
 }
@@ -188,38 +184,20 @@ __device__ __forceinline__ void last_acc(uint4 gr4, uint4 gi4, uint4 b4, f4_t (&
 // buffer: slot ((source * 4 + destination) * 2 + tt % 2); every quarter,
 // the wave's own included, passes through LDS, so no register index depends
 // on the wave.  Source blocks are visited in order with their operands
-// loaded one block ahead.  G_k3' comes from the LDS table G1, or (CORR 3,
-// whose LDS holds the state-term tables instead) from the conjugate DFT rows
-// times the lane's w_64^{-k3' c} (gf[k3' - 1]).
-template <int DT, int CORR>
-__device__ __forceinline__ void last_layer(uint32_t (&d)[64], uint4 *U, const uint4 *G1, const uint4 *Lc,
-                                           const uint32_t (&gf)[3], int w, int lane, float sca, float scb, uint16_t *ya,
-                                           uint16_t *yb, bool has_b, const void *cra, const void *crb, int ewa,
-                                           int ewb) {
+// loaded one block ahead.  G_k3' comes from the LDS table G1.
+template <int DT>
+__device__ __forceinline__ void last_layer(uint32_t (&d)[64], uint4 *U, const uint4 *G1, int w, int lane, float sca,
+                                           float scb, uint16_t *ya, uint16_t *yb, bool has_b) {
     const int g = lane >> 4, c = lane & 15;
     uint32_t pa0[8], pb0[8], pa1[8], pb1[8];   // packed outputs: [2 jj + half]
     const f4_t z = {0.f, 0.f, 0.f, 0.f};
     // this wave's share of the read-out below: row w >> 1, 16-byte pieces
     // i8 = (w & 1) 512 + 64 r + lane
     uint16_t *yrow = w < 2 ? ya : yb;
-    const void *crow = w < 2 ? cra : crb;
     const bool active = w < 2 || has_b;
-    uint4 c16[8];   // 16-bit correction term, loaded while the last layer runs
-    uint4 wq[4];    // fused state term: the row's weights W for the lane's 16 modes
     auto kinds = [&](int k3p, uint4 &gr, uint4 &gi) {
-        if constexpr (CORR != 3) {
-            gr = G1[(2 * k3p) * 64 + lane];
-            gi = G1[(2 * k3p + 1) * 64 + lane];
-        } else if (k3p == 0) {
-            gr = Lc[2 * 64 + lane];
-            gi = Lc[3 * 64 + lane];
-        } else {
-            uint32_t R[4], I[4];
-            const uint32_t ff[4] = {gf[k3p - 1], gf[k3p - 1], gf[k3p - 1], gf[k3p - 1]};
-            kinds_scaled(Lc[3 * 64 + lane], ff, R, I);
-            gr = make_uint4(R[0], R[1], R[2], R[3]);
-            gi = make_uint4(I[0], I[1], I[2], I[3]);
-        }
+        gr = G1[(2 * k3p) * 64 + lane];
+        gi = G1[(2 * k3p + 1) * 64 + lane];
     };
 #pragma unroll
     for (int half = 0; half < 2; ++half) {
@@ -231,11 +209,6 @@ __device__ __forceinline__ void last_layer(uint32_t (&d)[64], uint4 *U, const ui
                 const int T = 4 * q + 2 * half + t2;
                 U[((w * 4 + q) * 2 + t2) * 64 + lane] = make_uint4(d[4 * T], d[4 * T + 1], d[4 * T + 2], d[4 * T + 3]);
             }
-        if (CORR == 2 && half == 1) {
-#pragma unroll
-            for (int r = 0; r < 8; ++r)
-                c16[r] = active ? ((const uint4 *)crow)[(w & 1) * 512 + r * 64 + lane] : make_uint4(0, 0, 0, 0);
-        }
         __syncthreads();
         f4_t D[2][4] = {{z, z, z, z}, {z, z, z, z}};
         uint4 gr, gi;
@@ -268,11 +241,6 @@ __device__ __forceinline__ void last_layer(uint32_t (&d)[64], uint4 *U, const ui
             b0 = nb0;
             b1 = nb1;
         }
-        if (CORR == 3 && half == 1) {
-            // the row's weights for modes 16 kb + 4 g + (0..3): one uint4 per kb
-#pragma unroll
-            for (int kb = 0; kb < 4; ++kb) wq[kb] = active ? ((const uint4 *)crow)[4 * kb + g] : make_uint4(0, 0, 0, 0);
-        }
         // tiles 2 half (D[0]) and 2 half + 1 (D[1]) are consecutive points
 #pragma unroll
         for (int jj = 0; jj < 4; ++jj) {
@@ -297,38 +265,11 @@ __device__ __forceinline__ void last_layer(uint32_t (&d)[64], uint4 *U, const ui
         Uo[3072 + m4] = make_uint2(pb1[2 * jj], pb1[2 * jj + 1]);
     }
     __syncthreads();
-    if constexpr (CORR == 3) {
-        if (active) fused_state_term<DT, 2048>(U, G1, wq, w < 2 ? ewa : ewb, w >> 1, w & 1, lane, yrow);
-        return;
-    }
     if (active) {
 #pragma unroll
         for (int r = 0; r < 8; ++r) {
             const int i8 = (w & 1) * 512 + r * 64 + lane;   // uint4 index within the row
-            uint4 v = U[(w >> 1) * 1024 + i8];
-            if constexpr (CORR != 0) {
-                // state-passing initial-state term, added to the 16-bit outputs
-                float cv[8];
-                if constexpr (CORR == 1) {
-                    const float4 c0 = ((const float4 *)crow)[2 * i8], c1 = ((const float4 *)crow)[2 * i8 + 1];
-                    cv[0] = c0.x; cv[1] = c0.y; cv[2] = c0.z; cv[3] = c0.w;
-                    cv[4] = c1.x; cv[5] = c1.y; cv[6] = c1.z; cv[7] = c1.w;
-                } else {
-                    const uint4 cr = c16[r];
-                    const uint32_t cw[4] = {cr.x, cr.y, cr.z, cr.w};
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        cv[2 * e] = lo_f<DT>(cw[e]);
-                        cv[2 * e + 1] = hi_f<DT>(cw[e]);
-                    }
-                }
-                uint32_t vw[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    vw[e] = pack_out<DT>(lo_f<DT>(vw[e]) + cv[2 * e], hi_f<DT>(vw[e]) + cv[2 * e + 1]);
-                v = make_uint4(vw[0], vw[1], vw[2], vw[3]);
-            }
-            *(uint4 *)(yrow + 8 * i8) = v;
+            *(uint4 *)(yrow + 8 * i8) = U[(w >> 1) * 1024 + i8];
         }
     }
 }
@@ -336,16 +277,11 @@ __device__ __forceinline__ void last_layer(uint32_t (&d)[64], uint4 *U, const ui
 }  // namespace w16
 
 // ============================================================================
-// CORR: 0 none, 1 float32 correction term, 2 correction term in the I/O dtype,
-// 3 the term computed here from the chunk's weights W
-template <int DT, int CORR>
+template <int DT>
 __global__ __launch_bounds__(w16::NT) __attribute__((amdgpu_waves_per_eu(2))) void fftconv_wave16k_kernel(
     ConvArgs a, const float *k, int wg_per_ch, int pairs_per_ch) {
     using namespace w16;
-    // Ytab + Lc, then the last layer's matrices, or (CORR 3) the channel's
-    // state-term tables
-    constexpr int kTabAll = CORR == 3 ? kTab + CORR_TAB_U4 : kTab16;
-    __shared__ uint4 Tab[kTabAll];
+    __shared__ uint4 Tab[kTab16];   // Ytab + Lc, then the last layer's matrices
     __shared__ uint4 U[kU];         // pair staging, then the last-layer exchange
     __shared__ float red[3 * NW];   // row a max | kernel spectrum max | row b max
     const uint4 *Ytab = Tab, *Lc = Tab + kTabY, *G1 = Tab + kTab;
@@ -360,15 +296,8 @@ __global__ __launch_bounds__(w16::NT) __attribute__((amdgpu_waves_per_eu(2))) vo
     uint16_t *y = (uint16_t *)a.y;
 
     auto rows = [&](int qq, long &oa, long &ob) {
-        if (a.pair_mode == 0) {
-            oa = ((long)(2 * qq) * a.H + h) * L;
-            ob = (2 * qq + 1 < a.B) ? ((long)(2 * qq + 1) * a.H + h) * L : -1;
-        } else {
-            const int ncp = (a.nchunk + 1) / 2;
-            const int bb = qq / ncp, cp = qq % ncp;
-            oa = (((long)bb * a.H + h) * a.nchunk + 2 * cp) * L;
-            ob = (2 * cp + 1 < a.nchunk) ? oa + L : -1;
-        }
+        oa = ((long)(2 * qq) * a.H + h) * L;
+        ob = (2 * qq + 1 < a.B) ? ((long)(2 * qq + 1) * a.H + h) * L : -1;
     };
     // This wave's quarter of a pair: half x = w >> 1, lane rows g = 2 (w & 1)
     // + gi; lane l holds c = l & 15, j = l >> 4, points m = 4096 x + 256 (4 g
@@ -399,16 +328,15 @@ __global__ __launch_bounds__(w16::NT) __attribute__((amdgpu_waves_per_eu(2))) vo
 
     // ---- start-up loads: tables into LDS, factors, kernel row, first pair ----
 #pragma unroll
-    for (int r = 0; r < (kTabAll + NT - 1) / NT; ++r) {
-        const int base = r * NT + 64 * w;   // kTab and CORR_TAB_U4 are multiples of 64
-        if (base < kTabAll) {
-            const uint4 *src = (CORR != 3 || base < kTab) ? (const uint4 *)kHalf16.v + base
-                                                         : a.corr_tab + (long)h * CORR_TAB_U4 + (base - kTab);
+    for (int r = 0; r < (kTab16 + NT - 1) / NT; ++r) {
+        const int base = r * NT + 64 * w;   // kTab16 is a multiple of 64
+        if (base < kTab16) {
+            const uint4 *src = (const uint4 *)kHalf16.v + base;
             __builtin_amdgcn_global_load_lds((gvoid_t *)(src + lane), (lvoid_t *)(Tab + base), 16, 0, 0);
         }
     }
     __builtin_amdgcn_sched_barrier(0);
-    uint32_t f1[4], xf[4], f3[4], g3, xh, gf[3];
+    uint32_t f1[4], xf[4], f3[4], g3, xh;
     {
         const uint4 *fp = (const uint4 *)kFac16.v + (w * 64 + lane) * 4;
         const uint4 v0 = fp[0], v1 = fp[1], v2 = fp[2], v3 = fp[3];
@@ -417,65 +345,16 @@ __global__ __launch_bounds__(w16::NT) __attribute__((amdgpu_waves_per_eu(2))) vo
         f3[0] = v2.x; f3[1] = v2.y; f3[2] = v2.z; f3[3] = v2.w;
         g3 = v3.x;
         xh = v3.y;
-        gf[0] = v3.z;
-        gf[1] = v3.w;
-        gf[2] = cmul(v3.z, v3.w);   // w_64^{-3c}
     }
     float4 kq[8];   // [4 gi + s]: points m = ... + 16 c + 4 s .. + 3
-    // CORR 3 with gen_C: the kernel row is formed here (below); lane n = mode
-    // n loads C_n and Bbar_n instead
-    const bool gen = CORR == 3 && a.gen_C != nullptr;   // uniform
-    float2 gC = make_float2(0.f, 0.f), gB = make_float2(0.f, 0.f);
-    if (gen) {
-        if (lane < a.m_gen) {
-            gC = ((const float2 *)a.gen_C)[(long)h * a.m_gen + lane];
-            gB = ((const float2 *)a.gen_Bbar)[(long)h * a.m_gen + lane];
-        }
-    } else {
 #pragma unroll
-        for (int gi = 0; gi < 2; ++gi) {
-            const int off = 4096 * xq + 256 * (4 * (2 * (w & 1) + gi) + jq) + 16 * c;
+    for (int gi = 0; gi < 2; ++gi) {
+        const int off = 4096 * xq + 256 * (4 * (2 * (w & 1) + gi) + jq) + 16 * c;
 #pragma unroll
-            for (int s = 0; s < 4; ++s) kq[4 * gi + s] = *(const float4 *)(k + (long)h * L + off + 4 * s);
-        }
+        for (int s = 0; s < 4; ++s) kq[4 * gi + s] = *(const float4 *)(k + (long)h * L + off + 4 * s);
     }
     __builtin_amdgcn_sched_barrier(0);
     if (q0 < q1) issue_loads(q0);
-    if (CORR == 3 && gen) {
-        // k_t = 2 Re sum_n W_n Abar_n^t with W_n = C_n Bbar_n: the fused state
-        // term's sum (Algorithm 2's M_xy form) with the kernel's weights; waves
-        // 0 and 1 form t in [4096 w, 4096 w + 4096) in fp32 into U, then every
-        // wave reads its points as from k.  W is normalised to max |W| in
-        // [1/2, 1) (fp16), in the tables' unused tail.
-        if (q0 < q1)
-            __builtin_amdgcn_s_waitcnt(kWaitVm8);   // tables landed; the pair loads may be in flight
-        else
-            __builtin_amdgcn_s_waitcnt(kWaitVm0);
-        const float2 Wn = make_float2(gC.x * gB.x - gC.y * gB.y, gC.x * gB.y + gC.y * gB.x);
-        const int ew = __builtin_amdgcn_readfirstlane(exp_of(wave_max(fmaxf(fabsf(Wn.x), fabsf(Wn.y)))));
-        uint32_t *Wl = (uint32_t *)(Tab + kTab + 1568);   // 32 unused uint4 of the table
-        __syncthreads();   // every wave's table copies landed
-        if (w == 0) Wl[lane] = pk(ldexpf(Wn.x, -ew), ldexpf(Wn.y, -ew));
-        __syncthreads();
-        if (w < 2) {
-            uint4 wq[4];
-#pragma unroll
-            for (int kb = 0; kb < 4; ++kb) wq[kb] = ((const uint4 *)Wl)[4 * kb + g];
-            const float sc = ldexpf(2.0f, ew);
-            float *Uf = (float *)U;
-            state_term_core<false>(G1, wq, w, lane, [&](int t, f4_t D) {
-                *(float4 *)(Uf + t) = make_float4(D[0] * sc, D[1] * sc, D[2] * sc, D[3] * sc);
-            });
-        }
-        __syncthreads();
-#pragma unroll
-        for (int gi = 0; gi < 2; ++gi) {
-            const int off = 4096 * xq + 256 * (4 * (2 * (w & 1) + gi) + jq) + 16 * c;
-#pragma unroll
-            for (int s = 0; s < 4; ++s) kq[4 * gi + s] = *(const float4 *)((const float *)U + off + 4 * s);
-        }
-    }
-
     // ---- kernel spectrum block w of channel h (F(k + D delta) 2^-ek / 128) ----
     uint32_t K[64];
     int kexp;
@@ -626,13 +505,13 @@ __global__ __launch_bounds__(w16::NT) __attribute__((amdgpu_waves_per_eu(2))) vo
             }
         }
         __syncthreads();   // every wave is done reading the staged pair
-        forward_mid<CORR == 0>(d, Lc, Ytab, lane);
+        forward_mid<true>(d, Lc, Ytab, lane);
         {
             // third layer (contraction side times w_16384^{k3 p0} 2^-e2) and
             // the pointwise product with the kernel spectrum block
             uint32_t R[4], I[4];
             kinds_scaled(Lc[1 * 64 + lane], f3, R, I);
-            layer_sel<CORR == 0, false>(d, dft_of(R, I), NoPre{}, [&](int tau, f4_t re, f4_t im, uint4) {
+            layer_sel<true, false>(d, dft_of(R, I), NoPre{}, [&](int tau, f4_t re, f4_t im, uint4) {
 #pragma unroll
                 for (int jj = 0; jj < 4; ++jj) {
                     // opaque per use: otherwise the (-im, re) companion of every
@@ -648,7 +527,7 @@ __global__ __launch_bounds__(w16::NT) __attribute__((amdgpu_waves_per_eu(2))) vo
             uint32_t R[4], I[4];
             const uint32_t gg[4] = {g3, g3, g3, g3};
             kinds_scaled(Lc[3 * 64 + lane], gg, R, I);
-            layer_sel<CORR == 0, false>(d, dft_of(R, I), NoPre{}, [&](int tau, f4_t re, f4_t im, uint4) {
+            layer_sel<true, false>(d, dft_of(R, I), NoPre{}, [&](int tau, f4_t re, f4_t im, uint4) {
 #pragma unroll
                 for (int jj = 0; jj < 4; ++jj) d[4 * tau + jj] = pk(re[jj], im[jj]);
             });
@@ -670,7 +549,7 @@ __global__ __launch_bounds__(w16::NT) __attribute__((amdgpu_waves_per_eu(2))) vo
         {
             uint32_t xw[4], xs[4];
             twiddles_inv(Lc[4 * 64 + lane], xh, xw, xs);
-            layer_sel<CORR == 0, true>(d, lds_dft(Lc, lane, true), NoPre{}, [&](int tau, f4_t re, f4_t im, uint4) {
+            layer_sel<true, true>(d, lds_dft(Lc, lane, true), NoPre{}, [&](int tau, f4_t re, f4_t im, uint4) {
 #pragma unroll
                 for (int jj = 0; jj < 4; ++jj) d[4 * tau + jj] = cmul2(pk(re[jj], im[jj]), xw[jj], xs[jj]);
             });
@@ -683,23 +562,7 @@ __global__ __launch_bounds__(w16::NT) __attribute__((amdgpu_waves_per_eu(2))) vo
         rows(qq, oa, ob);
         const float sca = ldexpf(1.0f, kexp + eua), scb = ldexpf(1.0f, kexp + eub);
         uint16_t *ya = y + oa, *yb = y + (ob >= 0 ? ob : oa);
-        const long obc = ob >= 0 ? ob : oa;
-        const void *cra = nullptr, *crb = nullptr;
-        if (CORR == 1) {
-            cra = (const float *)a.corr + oa;
-            crb = (const float *)a.corr + obc;
-        } else if (CORR == 2) {
-            cra = (const uint16_t *)a.corr + oa;
-            crb = (const uint16_t *)a.corr + obc;
-        }
-        int ewa = 0, ewb = 0;
-        if (CORR == 3) {   // normalised weights W of chunk rows oa / L, obc / L
-            cra = (const uint32_t *)a.corr + (oa / L) * 64;
-            crb = (const uint32_t *)a.corr + (obc / L) * 64;
-            ewa = a.corr_e[oa / L];
-            ewb = a.corr_e[obc / L];
-        }
-        last_layer<DT, CORR>(d, U, G1, Lc, gf, w, lane, sca, scb, ya, yb, ob >= 0, cra, crb, ewa, ewb);
+        last_layer<DT>(d, U, G1, w, lane, sca, scb, ya, yb, ob >= 0);
     }
 }
 
@@ -707,32 +570,17 @@ bool fftconv_wave16k_supported(int L, int dtype) { return L == w16::L && (dtype 
 
 hipError_t launch_fftconv_wave16k(const ConvArgs &a, const float *k, hipStream_t s) {
     if (!fftconv_wave16k_supported(a.L, a.dtype)) return hipErrorInvalidValue;
-    int pairs_per_ch;
-    if (a.pair_mode == 0)
-        pairs_per_ch = (a.B + 1) / 2;
-    else
-        pairs_per_ch = a.B * ((a.nchunk + 1) / 2);
+    if (a.pair_mode != 0 || a.corr) return hipErrorInvalidValue;
+    const int pairs_per_ch = (a.B + 1) / 2;
     // two workgroups fit a CU: split a channel while fewer than ~2 per CU
     // and each still gets two pairs
     int wg_per_ch = 1;
     while ((long)a.H * wg_per_ch < 512 && pairs_per_ch >= 4 * wg_per_ch) wg_per_ch *= 2;
     dim3 grid(a.H * wg_per_ch), block(w16::NT);
-    const int corr = a.corr == nullptr ? 0 : a.corr_tab != nullptr ? 3 : (a.corr16 ? 2 : 1);
-    if (corr == 3 && (a.pair_mode != 1 || a.corr_e == nullptr)) return hipErrorInvalidValue;
-#define H3_W16_LAUNCH(DTV, CV) \
-    hipLaunchKernelGGL((fftconv_wave16k_kernel<DTV, CV>), grid, block, 0, s, a, k, wg_per_ch, pairs_per_ch)
-    if (a.dtype == F16) {
-        if (corr == 0) H3_W16_LAUNCH(F16, 0);
-        else if (corr == 1) H3_W16_LAUNCH(F16, 1);
-        else if (corr == 2) H3_W16_LAUNCH(F16, 2);
-        else H3_W16_LAUNCH(F16, 3);
-    } else {
-        if (corr == 0) H3_W16_LAUNCH(BF16, 0);
-        else if (corr == 1) H3_W16_LAUNCH(BF16, 1);
-        else if (corr == 2) H3_W16_LAUNCH(BF16, 2);
-        else H3_W16_LAUNCH(BF16, 3);
-    }
-#undef H3_W16_LAUNCH
+    if (a.dtype == F16)
+        hipLaunchKernelGGL(fftconv_wave16k_kernel<F16>, grid, block, 0, s, a, k, wg_per_ch, pairs_per_ch);
+    else
+        hipLaunchKernelGGL(fftconv_wave16k_kernel<BF16>, grid, block, 0, s, a, k, wg_per_ch, pairs_per_ch);
     return hipGetLastError();
 }
 

@@ -207,13 +207,9 @@ __device__ __forceinline__ void acc_rot(int n, h8_t Ar, h8_t Ai, h8_t b, h8_t nb
 // (k3' * 8 + w) of every source k3'.  The values of round 0 wait in fp32 and
 // are packed with those of round 1 (adjacent points), staged in LDS as rows
 // a and b, and stored by every wave as one contiguous eighth.
-// CORR: 0 none, 1 float32 term, 2 term in the I/O dtype, added at the store;
-// 3 the term computed here from the chunk rows' normalised weights (cra, crb:
-// 64 fp16 complex each; exponents ewa, ewb) and the channel's tables CT.
-template <int DT, int CORR>
-__device__ __forceinline__ void last_layer32(uint32_t (&d)[64], uint4 *U, const uint4 *G, const uint4 *CT, int w,
-                                             int lane, float sca, float scb, uint16_t *ya, uint16_t *yb, bool has_b,
-                                             const void *cra, const void *crb, int ewa, int ewb) {
+template <int DT>
+__device__ __forceinline__ void last_layer32(uint32_t (&d)[64], uint4 *U, const uint4 *G, int w, int lane, float sca,
+                                             float scb, uint16_t *ya, uint16_t *yb, bool has_b) {
     const int g = lane >> 4, c = lane & 15;
     float v0[4][2][4];        // round 0: [t3][row a, b][jj], scaled
     uint32_t po[4][2][4];     // packed rounds 0 and 1
@@ -268,8 +264,6 @@ __device__ __forceinline__ void last_layer32(uint32_t (&d)[64], uint4 *U, const 
     // outputs t = 4096 t3 + 256 (4 g + jj) + 16 c + 2 w (+ 1) of both rows go
     // through LDS (rows a, b as 16384 halves each), then out as 16-byte
     // chunks, each wave a contiguous eighth of the pair
-    uint4 cq[8];   // correction term (CORR 2), loaded while the outputs are staged
-    uint4 wq[4];   // fused state term (CORR 3): the row's weights W for the lane's 16 modes
     const bool active = w < 4 || has_b;
     __syncthreads();   // every exchange read is done
     uint32_t *Ud = (uint32_t *)U;
@@ -282,48 +276,12 @@ __device__ __forceinline__ void last_layer32(uint32_t (&d)[64], uint4 *U, const 
             Ud[8192 + dw] = po[t3][1][jj];
         }
     uint16_t *yrow = w < 4 ? ya : yb;
-    const void *crow = w < 4 ? cra : crb;
-    if (CORR == 2) {
-#pragma unroll
-        for (int r = 0; r < 8; ++r)
-            cq[r] = active ? ((const uint4 *)crow)[(w & 3) * 512 + r * 64 + lane] : make_uint4(0, 0, 0, 0);
-    }
-    if (CORR == 3) {   // modes 16 kb + 4 g + (0..3): one uint4 per kb
-#pragma unroll
-        for (int kb = 0; kb < 4; ++kb)
-            wq[kb] = active ? ((const uint4 *)crow)[4 * kb + (lane >> 4)] : make_uint4(0, 0, 0, 0);
-    }
     __syncthreads();
-    if constexpr (CORR == 3) {
-        if (active) fused_state_term<DT, 4096>(U, CT, wq, w < 4 ? ewa : ewb, w >> 2, w & 3, lane, yrow);
-        return;
-    }
     if (active) {
 #pragma unroll
         for (int r = 0; r < 8; ++r) {
             const int i8 = (w & 3) * 512 + r * 64 + lane;   // uint4 index within the row
-            uint4 v = U[(w >> 2) * 2048 + i8];
-            if constexpr (CORR != 0) {
-                float cv[8];
-                if constexpr (CORR == 1) {
-                    const float4 c0 = ((const float4 *)crow)[2 * i8], c1 = ((const float4 *)crow)[2 * i8 + 1];
-                    cv[0] = c0.x; cv[1] = c0.y; cv[2] = c0.z; cv[3] = c0.w;
-                    cv[4] = c1.x; cv[5] = c1.y; cv[6] = c1.z; cv[7] = c1.w;
-                } else {
-                    const uint32_t cw[4] = {cq[r].x, cq[r].y, cq[r].z, cq[r].w};
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        cv[2 * e] = lo_f<DT>(cw[e]);
-                        cv[2 * e + 1] = hi_f<DT>(cw[e]);
-                    }
-                }
-                uint32_t vw[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    vw[e] = pack_out<DT>(lo_f<DT>(vw[e]) + cv[2 * e], hi_f<DT>(vw[e]) + cv[2 * e + 1]);
-                v = make_uint4(vw[0], vw[1], vw[2], vw[3]);
-            }
-            *(uint4 *)(yrow + 8 * i8) = v;
+            *(uint4 *)(yrow + 8 * i8) = U[(w >> 2) * 2048 + i8];
         }
     }
 }
@@ -331,17 +289,14 @@ __device__ __forceinline__ void last_layer32(uint32_t (&d)[64], uint4 *U, const 
 }  // namespace w32
 
 // ============================================================================
-template <int DT, int CORR>
+template <int DT>
 __global__ __launch_bounds__(w32::NT) __attribute__((amdgpu_waves_per_eu(2))) void fftconv_wave32k_kernel(
     ConvArgs a, const float *k, int wg_per_ch, int pairs_per_ch) {
     using namespace w32;
-    // Ytab + Lc, then the last layer's rows, then (CORR 3) the channel's
-    // state-term tables
-    constexpr int kTabAll = CORR == 3 ? kTab32 + CORR_TAB_U4 : kTab32;
-    __shared__ uint4 Tab[kTabAll];
+    __shared__ uint4 Tab[kTab32];   // Ytab + Lc, then the last layer's rows
     __shared__ uint4 U[kU];         // pair staging, then the exchange and the output staging
     __shared__ float red[3 * NW];   // row a max | kernel spectrum max | row b max
-    const uint4 *Ytab = Tab, *Lc = Tab + kTabY, *G = Tab + kTab, *CT = Tab + kTab32;
+    const uint4 *Ytab = Tab, *Lc = Tab + kTabY, *G = Tab + kTab;
     uint32_t *Ud = (uint32_t *)U;
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);   // frequency block k3
@@ -353,15 +308,8 @@ __global__ __launch_bounds__(w32::NT) __attribute__((amdgpu_waves_per_eu(2))) vo
     uint16_t *y = (uint16_t *)a.y;
 
     auto rows = [&](int qq, long &oa, long &ob) {
-        if (a.pair_mode == 0) {
-            oa = ((long)(2 * qq) * a.H + h) * L;
-            ob = (2 * qq + 1 < a.B) ? ((long)(2 * qq + 1) * a.H + h) * L : -1;
-        } else {
-            const int ncp = (a.nchunk + 1) / 2;
-            const int bb = qq / ncp, cp = qq % ncp;
-            oa = (((long)bb * a.H + h) * a.nchunk + 2 * cp) * L;
-            ob = (2 * cp + 1 < a.nchunk) ? oa + L : -1;
-        }
+        oa = ((long)(2 * qq) * a.H + h) * L;
+        ob = (2 * qq + 1 < a.B) ? ((long)(2 * qq + 1) * a.H + h) * L : -1;
     };
     // This wave's eighth of a pair: quarter x = w >> 1, lane rows g = 2 (w & 1)
     // + gi; lane l holds c = l & 15, j = l >> 4, points m = 4096 x + 256 (4 g
@@ -392,11 +340,10 @@ __global__ __launch_bounds__(w32::NT) __attribute__((amdgpu_waves_per_eu(2))) vo
 
     // ---- start-up loads: tables into LDS, factors, kernel row, first pair ----
 #pragma unroll
-    for (int r = 0; r < (kTabAll + NT - 1) / NT; ++r) {
-        const int base = r * NT + 64 * w;   // kTab32 and CORR_TAB_U4 are multiples of 64
-        if (base < kTabAll) {
-            const uint4 *src = (CORR != 3 || base < kTab32) ? (const uint4 *)kHalf32.v + base
-                                                            : a.corr_tab + (long)h * CORR_TAB_U4 + (base - kTab32);
+    for (int r = 0; r < (kTab32 + NT - 1) / NT; ++r) {
+        const int base = r * NT + 64 * w;   // kTab32 is a multiple of 64
+        if (base < kTab32) {
+            const uint4 *src = (const uint4 *)kHalf32.v + base;
             __builtin_amdgcn_global_load_lds((gvoid_t *)(src + lane), (lvoid_t *)(Tab + base), 16, 0, 0);
         }
     }
@@ -414,59 +361,14 @@ __global__ __launch_bounds__(w32::NT) __attribute__((amdgpu_waves_per_eu(2))) vo
     };
     int e2 = 0;   // the spectrum's exponent: pairs' third layer carries 2^-e2
     float4 kq[8];   // [4 gi + s]: points m = ... + 16 c + 4 s .. + 3
-    // CORR 3 with gen_C: the kernel row is formed here (below); lane n = mode
-    // n loads C_n and Bbar_n instead
-    const bool gen = CORR == 3 && a.gen_C != nullptr;   // uniform
-    float2 gC = make_float2(0.f, 0.f), gB = make_float2(0.f, 0.f);
-    if (gen) {
-        if (lane < a.m_gen) {
-            gC = ((const float2 *)a.gen_C)[(long)h * a.m_gen + lane];
-            gB = ((const float2 *)a.gen_Bbar)[(long)h * a.m_gen + lane];
-        }
-    } else {
 #pragma unroll
-        for (int gi = 0; gi < 2; ++gi) {
-            const int off = 4096 * xq + 256 * (4 * (2 * (w & 1) + gi) + jq) + 16 * c;
+    for (int gi = 0; gi < 2; ++gi) {
+        const int off = 4096 * xq + 256 * (4 * (2 * (w & 1) + gi) + jq) + 16 * c;
 #pragma unroll
-            for (int s = 0; s < 4; ++s) kq[4 * gi + s] = *(const float4 *)(k + (long)h * L + off + 4 * s);
-        }
+        for (int s = 0; s < 4; ++s) kq[4 * gi + s] = *(const float4 *)(k + (long)h * L + off + 4 * s);
     }
     __builtin_amdgcn_sched_barrier(0);
     if (q0 < q1) issue_loads(q0);
-    if (CORR == 3 && gen) {
-        // k_t = 2 Re sum_n W_n Abar_n^t with W_n = C_n Bbar_n, as in the
-        // L = 8192 conv: waves 0 .. 3 form the quarters t in [4096 w, 4096 w
-        // + 4096) in fp32 into U, then every wave reads its points as from k
-        if (q0 < q1)
-            __builtin_amdgcn_s_waitcnt(kWaitVm8);   // tables landed; the pair loads may be in flight
-        else
-            __builtin_amdgcn_s_waitcnt(kWaitVm0);
-        const float2 Wn = make_float2(gC.x * gB.x - gC.y * gB.y, gC.x * gB.y + gC.y * gB.x);
-        const int ew = __builtin_amdgcn_readfirstlane(exp_of(wave_max(fmaxf(fabsf(Wn.x), fabsf(Wn.y)))));
-        uint32_t *Wl = (uint32_t *)(Tab + kTab32 + 1568);   // 32 unused uint4 of the table
-        __syncthreads();   // every wave's table copies landed
-        if (w == 0) Wl[lane] = pk(ldexpf(Wn.x, -ew), ldexpf(Wn.y, -ew));
-        __syncthreads();
-        if (w < 4) {
-            uint4 wq[4];
-            const int g = lane >> 4;
-#pragma unroll
-            for (int kb = 0; kb < 4; ++kb) wq[kb] = ((const uint4 *)Wl)[4 * kb + g];
-            const float sc = ldexpf(2.0f, ew);
-            float *Uf = (float *)U;
-            state_term_core<true>(CT, wq, w, lane, [&](int t, f4_t D) {
-                *(float4 *)(Uf + t) = make_float4(D[0] * sc, D[1] * sc, D[2] * sc, D[3] * sc);
-            });
-        }
-        __syncthreads();
-#pragma unroll
-        for (int gi = 0; gi < 2; ++gi) {
-            const int off = 4096 * xq + 256 * (4 * (2 * (w & 1) + gi) + jq) + 16 * c;
-#pragma unroll
-            for (int s = 0; s < 4; ++s) kq[4 * gi + s] = *(const float4 *)((const float *)U + off + 4 * s);
-        }
-    }
-
     // first-layer rows of this wave: the base (contraction side times
     // w_128^{k3 p2} / 4) and the same times w_8
     auto first_rows = [&](uint32_t (&Rq)[4][4], uint32_t (&Iq)[4][4]) {
@@ -707,23 +609,7 @@ __global__ __launch_bounds__(w32::NT) __attribute__((amdgpu_waves_per_eu(2))) vo
         rows(qq, oa, ob);
         const float sca = ldexpf(1.0f, kexp + eua), scb = ldexpf(1.0f, kexp + eub);
         uint16_t *ya = y + oa, *yb = y + (ob >= 0 ? ob : oa);
-        const long obc = ob >= 0 ? ob : oa;
-        const void *cra = nullptr, *crb = nullptr;
-        if (CORR == 1) {
-            cra = (const float *)a.corr + oa;
-            crb = (const float *)a.corr + obc;
-        } else if (CORR == 2) {
-            cra = (const uint16_t *)a.corr + oa;
-            crb = (const uint16_t *)a.corr + obc;
-        }
-        int ewa = 0, ewb = 0;
-        if (CORR == 3) {   // normalised weights W of chunk rows oa / L, obc / L
-            cra = (const uint32_t *)a.corr + (oa / L) * 64;
-            crb = (const uint32_t *)a.corr + (obc / L) * 64;
-            ewa = a.corr_e[oa / L];
-            ewb = a.corr_e[obc / L];
-        }
-        last_layer32<DT, CORR>(d, U, G, CT, w, lane, sca, scb, ya, yb, ob >= 0, cra, crb, ewa, ewb);
+        last_layer32<DT>(d, U, G, w, lane, sca, scb, ya, yb, ob >= 0);
     }
 }
 
@@ -731,32 +617,17 @@ bool fftconv_wave32k_supported(int L, int dtype) { return L == w32::L && (dtype 
 
 hipError_t launch_fftconv_wave32k(const ConvArgs &a, const float *k, hipStream_t s) {
     if (!fftconv_wave32k_supported(a.L, a.dtype)) return hipErrorInvalidValue;
-    int pairs_per_ch;
-    if (a.pair_mode == 0)
-        pairs_per_ch = (a.B + 1) / 2;
-    else
-        pairs_per_ch = a.B * ((a.nchunk + 1) / 2);
+    if (a.pair_mode != 0 || a.corr) return hipErrorInvalidValue;
+    const int pairs_per_ch = (a.B + 1) / 2;
     // one workgroup per CU (LDS): split a channel while fewer than ~one per
     // CU and each still gets two pairs
     int wg_per_ch = 1;
     while ((long)a.H * wg_per_ch < 256 && pairs_per_ch >= 4 * wg_per_ch) wg_per_ch *= 2;
     dim3 grid(a.H * wg_per_ch), block(w32::NT);
-    const int corr = a.corr == nullptr ? 0 : a.corr_tab != nullptr ? 3 : (a.corr16 ? 2 : 1);
-    if (corr == 3 && (a.pair_mode != 1 || a.corr_e == nullptr)) return hipErrorInvalidValue;
-#define H3_W32_LAUNCH(DTV, CV) \
-    hipLaunchKernelGGL((fftconv_wave32k_kernel<DTV, CV>), grid, block, 0, s, a, k, wg_per_ch, pairs_per_ch)
-    if (a.dtype == F16) {
-        if (corr == 0) H3_W32_LAUNCH(F16, 0);
-        else if (corr == 1) H3_W32_LAUNCH(F16, 1);
-        else if (corr == 2) H3_W32_LAUNCH(F16, 2);
-        else H3_W32_LAUNCH(F16, 3);
-    } else {
-        if (corr == 0) H3_W32_LAUNCH(BF16, 0);
-        else if (corr == 1) H3_W32_LAUNCH(BF16, 1);
-        else if (corr == 2) H3_W32_LAUNCH(BF16, 2);
-        else H3_W32_LAUNCH(BF16, 3);
-    }
-#undef H3_W32_LAUNCH
+    if (a.dtype == F16)
+        hipLaunchKernelGGL(fftconv_wave32k_kernel<F16>, grid, block, 0, s, a, k, wg_per_ch, pairs_per_ch);
+    else
+        hipLaunchKernelGGL(fftconv_wave32k_kernel<BF16>, grid, block, 0, s, a, k, wg_per_ch, pairs_per_ch);
     return hipGetLastError();
 }
 

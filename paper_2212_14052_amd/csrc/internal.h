@@ -36,17 +36,9 @@ struct ConvArgs {
     int nchunk;            // mode 1: chunks per row
     int pair_mode;
     int dtype;
-    // state-passing initial-state term (mode 1 only, may be null):
-    // (B, H, nchunk * L) added to the output; float32, or the I/O dtype if corr16
-    const void *corr;
-    int corr16;
-    // fused initial-state term (mode 1, L = 8192 and 16384 convs): when corr_tab is
-    // set, corr holds the normalised weights (B, H, nchunk, 64) fp16 complex
-    // and corr_e their exponents (B, H, nchunk), as written by
-    // launch_state_scan_w16, and corr_tab the per-channel tables written by
-    // launch_corr_tables
-    const uint4 *corr_tab;
-    const int *corr_e;
+    // state-passing initial-state term (VALU kernel, mode 1 only; may be
+    // null): (B, H, nchunk * L) float32, added to the output
+    const float *corr;
     // conj_k: convolve with the conjugated kernel spectrum, i.e. correlate:
     // y[t] = sum_{s>=t} k[s-t] u[s] (+ D u[t]), the input gradient of the
     // convolution.  Supported by the wave kernels and the VALU kernel.
@@ -55,12 +47,6 @@ struct ConvArgs {
     // convolution + D u), elementwise, gate in the I/O dtype and layout of y
     // (the output gating of the H3 layer, O = Q * S)
     const void *gate;
-    // gen_C, gen_Bbar (the L = 8192 and 16384 convs with the fused state term;
-    // may be null): the convolution kernel k_t = 2 Re sum_n C_n Bbar_n
-    // Abar_n^t (the state-passing f of length L) is formed in the kernel
-    // from them and the channel's power tables instead of read from k
-    const float *gen_C, *gen_Bbar;
-    int m_gen;   // their modes per channel (<= 64)
 };
 hipError_t launch_fftconv(const ConvArgs &a, hipStream_t s);
 // The VALU convolution of plain (B, H, L) rows (pair_mode 0, no correction
@@ -68,9 +54,7 @@ hipError_t launch_fftconv(const ConvArgs &a, hipStream_t s);
 // folded into k[0]); L a power of two in [16, 4096].
 bool fftconv_kgen_supported(int L);
 hipError_t launch_fftconv_kgen(const ConvArgs &a, const float *k, hipStream_t s);
-// The eight-wave register-resident convolution at L = 16384 (16-bit I/O):
-// plain rows or chunk pairs, with an optional correction term (float32, I/O
-// dtype, or the fused state term from corr_tab as at L = 8192).
+// The eight-wave register-resident convolution at L = 16384 (16-bit I/O).
 bool fftconv_wave32k_supported(int L, int dtype);
 hipError_t launch_fftconv_wave32k(const ConvArgs &a, const float *k, hipStream_t s);
 // Matrix-core block-FFT convolution (16-bit I/O, L = 2048, 8192 or 16384),
@@ -101,39 +85,21 @@ hipError_t launch_wgrad_direct(const void *u, const void *dy, int B, int H, int 
                                hipStream_t s);
 
 // State passing pieces.
-// Optional tail of the matrix-core chunk-state kernel (chunk 8192 or 16384):
-// when one workgroup covers a channel it also writes the channel's table of
-// the fused state term (ctab, as launch_corr_tables) and the scan of its rows
-// (w16, wexp, x_final, as launch_state_scan_w16); *fused tells whether it did.
-struct StateTail {
-    const float *C;
-    const float *x0;
-    uint32_t *w16;
-    int *wexp;
-    float *x_final;
-    uint4 *ctab;
-    int fuse;
-};
 hipError_t launch_chunk_states(const void *u, const float *Abar, const float *Bbar, int B, int H,
-                               int L, int m, int chunk, int dtype, float2 *states, hipStream_t s,
-                               const StateTail *tail = nullptr, bool *fused = nullptr);
+                               int L, int m, int chunk, int dtype, float2 *states, hipStream_t s);
 hipError_t launch_state_scan(const float *Abar, const float *C, const float *x0,
                              const float2 *states, int B, int H, int m, int chunk, int nchunk,
                              float2 *corr_W, float *x_final, hipStream_t s);
 // corr[row, c*chunk + t] = 2 Re sum_n corr_W[row, c, n] Abar_n^t  (row = b*H + h)
 hipError_t launch_state_correction(const float *Abar, const float2 *corr_W, int B, int H, int m,
                                    int chunk, int nchunk, float *corr, hipStream_t s);
-bool state_correction_mfma_ok(int chunk, int dtype);
-// Per-channel tables for the fused initial-state term of the L = 8192 and
-// L = 16384 convs (CORR_TAB_U4 uint4 per channel, the last 32 unused; m <= 64).
-constexpr int CORR_TAB_U4 = 1600;
-hipError_t launch_corr_tables(const float *Abar, int H, int m, uint4 *tab, hipStream_t s);
-// Scan variant for the fused term: normalised fp16 weights and exponents.
-hipError_t launch_state_scan_w16(const float *Abar, const float *C, const float *x0, const float2 *states,
-                                 int B, int H, int m, int chunk, int nchunk, uint32_t *w16, int *wexp,
-                                 float *x_final, hipStream_t s);
-hipError_t launch_state_correction_mfma(const float *Abar, const float2 *corr_W, int B, int H, int m,
-                                        int chunk, int nchunk, int dtype, void *corr, hipStream_t s);
+// State passing in one pass on the matrix cores (16-bit I/O, chunk 2048, 8192
+// or 16384; L a multiple of 1024, m <= 64).  ws: scratch for segment states;
+// what it holds bounds the segments per row.
+bool ssm_scan_supported(int chunk, int dtype);
+hipError_t launch_ssm_scan(const void *u, const float *Abar, const float *Bbar, const float *C, const float *D,
+                           const float *x0, int B, int H, int L, int m, int dtype, void *y, float *x_final, void *ws,
+                           size_t ws_bytes, hipStream_t s);
 
 // State passing (the C ABI entry points validate, then run it).
 size_t statepass_workspace(int B, int H, int L, int m, int chunk, int dtype);

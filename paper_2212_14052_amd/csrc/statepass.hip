@@ -7,7 +7,9 @@
 //   output                     y^(c)_t = (f * u^(c))_t + D u^(c)_t
 //                                        + 2 Re sum_n C_n Abar_n^{t+1} x^(c)_n
 // The chunk-local sums s_c of all chunks are independent (one workgroup per
-// chunk row); only the short scan over chunks is sequential.
+// chunk row); only the short scan over chunks is sequential.  16-bit I/O at
+// chunks 2048, 8192 and 16384 takes the one-pass kernel of ssm_scan.hip
+// instead; this file serves float32 I/O and the other chunks.
 #include "common.h"
 #include "internal.h"
 
@@ -86,8 +88,8 @@ __global__ __launch_bounds__(CS_THREADS) void chunk_states_kernel(const void *u_
 }
 
 // ------------------------------------------------- chunk sums, MFMA form ---
-// Same sums for 16-bit input and chunk % 1024 == 0.  Per channel, with blocks
-// of BW = 128 inputs (64 when chunk % 2048 != 0),
+// Same sums for 16-bit input and chunk 1024 or 4096.  Per channel, with blocks
+// of BW = 128 inputs (64 at chunk 1024),
 //   R[n][a] = sum_{b<BW} Abar_n^{BW-1-b} u_{BW a + b}
 // is a real matrix product (rows: Re / Im of 64 modes; reduction b; columns
 // a = 0 .. N'/BW - 1) on 16x16x32 MFMAs with the powers in 16-bit and the
@@ -102,9 +104,7 @@ __global__ __launch_bounds__(CS_THREADS) void chunk_states_kernel(const void *u_
 // Chunk rows reach LDS without passing through registers: the four waves copy
 // 1 KB slices of a row (64 lanes x 16 bytes, lane i to byte 16 i of the
 // slice) with global_load_lds_dwordx4 into two row buffers, one row ahead of
-// the row being reduced (a three-row ring measured slower at chunk 8192, 187
-// against 149 us: it leaves room for three workgroups per CU instead of
-// four).  A row is staged as N'/BW LDS rows of
+// the row being reduced.  A row is staged as N'/BW LDS rows of
 // BW inputs (2 BW bytes, 16-byte chunks), chunk c of LDS row a at slot
 // c ^ ((a / (256 / 2 BW)) % (2 BW / 16)), so the 16 lanes of an operand read
 // (16 consecutive rows a, one chunk) hit 16 distinct 16-byte bank groups.
@@ -151,7 +151,6 @@ __device__ __forceinline__ uint32_t sp_pack(float lo, float hi) {
     }
 }
 
-constexpr int SPM_CHUNK = 16384;   // largest chunk of the matrix-core form
 constexpr int CS_NS = 2;   // row buffers in the copy ring
 
 typedef __attribute__((address_space(3))) void cs_lds_t;
@@ -160,30 +159,23 @@ typedef __attribute__((address_space(3))) void cs_lds_t;
 // slot for the copies of waves with one slice less
 size_t chunk_states_lds(int chunk) { return (size_t)CS_NS * chunk * 2 + 2 * 64 * 8 + 1024; }
 
-__device__ void cs_state_tail(const StateTail &t, const float *Abar, const float2 *states, int B, int H, int m,
-                              int chunk, int nchunk, int h, uint4 *lds);
-
-// tail.fuse (one workgroup per channel, chunk 8192 or 16384): the workgroup
-// also writes the channel's fused-term table and scans its rows (cs_state_tail)
-// FULL: chunk == CMAX, so every column tile is present and the tiles' matrix
-// products are free to interleave (no per-tile branch)
-template <int DT, int BW, int CMAX, bool FULL>
+template <int DT, int BW, int CHUNK>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void chunk_states_mfma(
-    const uint16_t *u, const float *Abar, const float *Bbar, int B, int H, int L, int m, int chunk, int wg_per_ch,
-    float2 *states, StateTail tail) {
+    const uint16_t *u, const float *Abar, const float *Bbar, int B, int H, int L, int m, int wg_per_ch,
+    float2 *states) {
+    constexpr int chunk = CHUNK;
     constexpr int KS = BW / 32;          // 32-wide reduction steps per block
     constexpr int RB = 2 * BW;           // bytes per LDS row
     constexpr int SPR = RB / 16;         // 16-byte slots per LDS row
     constexpr int RPB = 256 / RB;        // LDS rows per 256-byte bank row
-    constexpr int NA_MAX = CMAX / BW;
     extern __shared__ __attribute__((aligned(1024))) char cs_lds[];
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);   // the wave index, in a scalar register
     const int r16 = lane & 15, kg = lane >> 4;
     const int h = blockIdx.x / wg_per_ch, part = blockIdx.x % wg_per_ch;
     const int nchunk = L / chunk;
-    const int NA = chunk / BW;          // columns a, multiple of 16
-    const int NCT = NA / 16;            // column tiles
+    constexpr int NCT = chunk / BW / 16;   // column tiles
+    static_assert(chunk / BW % 16 == 0, "whole column tiles");
     const int rows_per_ch = B * nchunk;
     const int per = (rows_per_ch + wg_per_ch - 1) / wg_per_ch;
     const int r0 = part * per, r1 = min(r0 + per, rows_per_ch);
@@ -283,32 +275,29 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void c
         __builtin_amdgcn_s_waitcnt(0x070);   // vmcnt(0) lgkmcnt(0)
         asm volatile("s_barrier" ::: "memory");
         if (w == 0 && rr > r0) store_row(rr - 1);
-        // the next row's copies (none past the last row: the tail below
-        // reuses the ring, so no copy may land there after the loop)
+        // the next row's copies
         if (rr + 1 < r1) issue(rr + 1);
         const char *us = cs_lds + ((rr - r0) % CS_NS) * row_b;
         sp_f4 sre = {0.f, 0.f, 0.f, 0.f}, sim = {0.f, 0.f, 0.f, 0.f};
         float2 E[4] = {E0[0], E0[1], E0[2], E0[3]};
 #pragma unroll
-        for (int ct = NA_MAX / 16 - 1; ct >= 0; --ct) {
-            if (FULL || ct < NCT) {
-                sp_f4 accr = {0.f, 0.f, 0.f, 0.f}, acci = {0.f, 0.f, 0.f, 0.f};
-                const int a = 16 * ct + r16;
+        for (int ct = NCT - 1; ct >= 0; --ct) {
+            sp_f4 accr = {0.f, 0.f, 0.f, 0.f}, acci = {0.f, 0.f, 0.f, 0.f};
+            const int a = 16 * ct + r16;
 #pragma unroll
-                for (int ks = 0; ks < KS; ++ks) {
-                    // B operand: column a, reduction b = 32 ks + 8 kg .. + 7 (16-byte chunk 4 ks + kg)
-                    const int c = 4 * ks + kg;
-                    const uint4 bv = *(const uint4 *)(us + a * RB + 16 * (c ^ ((a / RPB) % SPR)));
-                    accr = sp_mfma<DT>(Are[ks], bv, accr);
-                    acci = sp_mfma<DT>(Aim[ks], bv, acci);
-                }
-                // lane: rows (modes) 4 kg + j, column a = 16 ct + r16
+            for (int ks = 0; ks < KS; ++ks) {
+                // B operand: column a, reduction b = 32 ks + 8 kg .. + 7 (16-byte chunk 4 ks + kg)
+                const int c = 4 * ks + kg;
+                const uint4 bv = *(const uint4 *)(us + a * RB + 16 * (c ^ ((a / RPB) % SPR)));
+                accr = sp_mfma<DT>(Are[ks], bv, accr);
+                acci = sp_mfma<DT>(Aim[ks], bv, acci);
+            }
+            // lane: rows (modes) 4 kg + j, column a = 16 ct + r16
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    sre[j] = fmaf(E[j].x, accr[j], fmaf(-E[j].y, acci[j], sre[j]));
-                    sim[j] = fmaf(E[j].x, acci[j], fmaf(E[j].y, accr[j], sim[j]));
-                    E[j] = cmul(E[j], Zstep[j]);
-                }
+            for (int j = 0; j < 4; ++j) {
+                sre[j] = fmaf(E[j].x, accr[j], fmaf(-E[j].y, acci[j], sre[j]));
+                sim[j] = fmaf(E[j].x, acci[j], fmaf(E[j].y, accr[j], sim[j]));
+                E[j] = cmul(E[j], Zstep[j]);
             }
         }
         // reduce over the 16 columns held by lanes r16 = 0..15
@@ -327,28 +316,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void c
     }
     __syncthreads();   // the last row's sums are in LDS; every copy has landed
     if (w == 0) store_row(r1 - 1);
-    if (tail.fuse) {
-        // every chunk sum of the channel is written and visible to the
-        // workgroup (a workgroup-scope fence: the readers are this
-        // workgroup's waves, and a device-scope one would write back the
-        // L2); the row ring is free for the table
-        __threadfence_block();
-        __syncthreads();
-        cs_state_tail(tail, Abar, states, B, H, m, chunk, nchunk, h, (uint4 *)cs_lds);
-    }
 }
 
 bool chunk_states_mfma_ok(int chunk, int dtype) {
-    return (dtype == F16 || dtype == BF16) && chunk % 1024 == 0 && chunk <= SPM_CHUNK;
+    return (dtype == F16 || dtype == BF16) && (chunk == 1024 || chunk == 4096);
 }
 
 hipError_t launch_chunk_states_mfma(const void *u, const float *Abar, const float *Bbar, int B, int H,
-                                    int L, int m, int chunk, int dtype, float2 *states, hipStream_t s,
-                                    const StateTail *tail, bool *fused) {
+                                    int L, int m, int chunk, int dtype, float2 *states, hipStream_t s) {
     const int rows_per_ch = B * (L / chunk);
     const uint16_t *u16 = (const uint16_t *)u;
-    const bool wide = chunk % 2048 == 0;   // 128-wide blocks need 16 columns per tile: chunk / 128 % 16 == 0
-    const bool big = chunk > 8192;         // multiple of 2048 here, so wide
     const size_t lds = chunk_states_lds(chunk);
     // Workgroups per channel: a workgroup walks its rows one after another,
     // the grid runs in ceil(workgroups / resident) rounds.  Take the count in
@@ -375,244 +352,21 @@ hipError_t launch_chunk_states_mfma(const void *u, const float *Abar, const floa
         }
         return best;
     };
-#define H3_CS_LAUNCH(DTV, BWV, CMV)                                                                              \
+#define H3_CS_LAUNCH(DTV, BWV, CV)                                                                               \
     do {                                                                                                         \
-        auto fn = chunk == CMV ? chunk_states_mfma<DTV, BWV, CMV, true> : chunk_states_mfma<DTV, BWV, CMV, false>; \
+        auto fn = chunk_states_mfma<DTV, BWV, CV>;                                                               \
         (void)hipFuncSetAttribute((const void *)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);      \
         const int wg = pick_wg((const void *)fn);                                                                \
-        StateTail tl{};                                                                                          \
-        if (tail && wg == 1 && (size_t)CS_NS * chunk * 2 >= (size_t)CORR_TAB_U4 * 16) {                         \
-            tl = *tail;                                                                                          \
-            tl.fuse = 1;                                                                                         \
-            if (fused) *fused = true;                                                                            \
-        }                                                                                                        \
-        hipLaunchKernelGGL(fn, dim3(H * wg), dim3(256), lds, s, u16, Abar, Bbar, B, H, L, m, chunk, wg, states,  \
-                           tl);                                                                                  \
+        hipLaunchKernelGGL(fn, dim3(H * wg), dim3(256), lds, s, u16, Abar, Bbar, B, H, L, m, wg, states);        \
     } while (0)
     if (dtype == BF16) {
-        if (big) H3_CS_LAUNCH(BF16, 128, 16384);
-        else if (wide) H3_CS_LAUNCH(BF16, 128, 8192);
-        else H3_CS_LAUNCH(BF16, 64, 8192);
+        if (chunk == 4096) H3_CS_LAUNCH(BF16, 128, 4096);
+        else H3_CS_LAUNCH(BF16, 64, 1024);
     } else {
-        if (big) H3_CS_LAUNCH(F16, 128, 16384);
-        else if (wide) H3_CS_LAUNCH(F16, 128, 8192);
-        else H3_CS_LAUNCH(F16, 64, 8192);
+        if (chunk == 4096) H3_CS_LAUNCH(F16, 128, 4096);
+        else H3_CS_LAUNCH(F16, 64, 1024);
     }
 #undef H3_CS_LAUNCH
-    return hipGetLastError();
-}
-
-// -------------------------------------------- initial-state term, MFMA form ---
-// corr[c N' + t] = 2 Re sum_n W_n Abar_n^t,  W_n = C_n x^(c)_n Abar_n  (so the
-// term is 2 Re sum_n C_n Abar_n^{t+1} x^(c)_n, the M_xy x^(c) of Algorithm 2).
-// With t = 64 a + b:  corr = 2 sum_k Pm[a][k] Qm[k][b],
-//   Pm[a][k] = Re (W_k E[a][k]) (k < 64), -Im (W_{k-64} E[a][k-64]) (k >= 64),
-//   Qm[k][b] = Re Abar_k^b (k < 64), Im Abar_{k-64}^b (k >= 64),
-//   E[a][n] = Abar_n^{64 a}.
-// Per channel the tables E and Q (powers in float64, stored fp16) sit in LDS;
-// per chunk row W is scaled by a power of two to max |W| in [1/2, 1) before
-// rounding to fp16, and the scale is undone in fp32.  Output in the I/O dtype.
-// Workgroup (4 waves): one channel, a set of its chunk rows; wave w owns
-// tiles a = 16 (TPW w) .. 16 (TPW (w + 1)) - 1 of every chunk (TPW = NAM / 64
-// tiles per wave), all 64 columns b.  NAM = 128 serves chunks up to 8192, 256
-// chunks up to 16384 (the E table then takes 69.6 KB of LDS instead of 34.8).
-typedef _Float16 cr_h2 __attribute__((ext_vector_type(2)));
-constexpr int CR_NA = 256;   // largest a-range (chunk / 64) of the matrix-core form
-
-template <int DT, int NAM>
-__global__ __launch_bounds__(256) void state_correction_mfma(const float *Abar, const float2 *corr_W,
-                                                             int B, int H, int m, int chunk, int nchunk,
-                                                             int wg_per_ch, uint16_t *corr) {
-    constexpr int TPW = NAM / 64;
-    __shared__ __attribute__((aligned(16))) uint32_t Et[NAM][64 + 4];       // E[a][n], fp16 complex
-    __shared__ __attribute__((aligned(16))) uint16_t Qt[64][128 + 8];       // Qm[k][b] as [b][k]
-    __shared__ float2 Ws[64];
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    const int r16 = lane & 15, kg = lane >> 4;
-    const int h = blockIdx.x / wg_per_ch, part = blockIdx.x % wg_per_ch;
-    const int NA = chunk / 64;
-    const int rows_per_ch = B * nchunk;
-    const int per = (rows_per_ch + wg_per_ch - 1) / wg_per_ch;
-    const int r0 = part * per, r1 = min(r0 + per, rows_per_ch);
-    {
-        const int n = tid & 63, q = tid >> 6;
-        double2 z = make_double2(0.0, 0.0);
-        if (n < m) z = make_double2(Abar[2 * ((long)h * m + n)], Abar[2 * ((long)h * m + n) + 1]);
-        // Q: b = 16 q .. 16 q + 15
-        double2 p = sp_zpow(z, 16 * q);
-        for (int j = 0; j < 16; ++j) {
-            Qt[16 * q + j][n] = __builtin_bit_cast(uint16_t, (_Float16)p.x);
-            Qt[16 * q + j][64 + n] = __builtin_bit_cast(uint16_t, (_Float16)p.y);
-            p = sp_zmul(p, z);
-        }
-        // E: a = q, q + 4, ... (stride 4)
-        const double2 z64 = sp_zpow(z, 64), z256 = sp_zpow(z64, 4);
-        double2 e = sp_zpow(z64, q);
-        for (int a = q; a < NA; a += 4) {
-            cr_h2 v = {(_Float16)e.x, (_Float16)e.y};
-            Et[a][n] = __builtin_bit_cast(uint32_t, v);
-            e = sp_zmul(e, z256);
-        }
-    }
-    __syncthreads();
-    auto crow_of = [&](int rr) {
-        const int bb = rr / nchunk, cc = rr % nchunk;
-        return ((long)bb * H + h) * nchunk + cc;
-    };
-    // W of the next chunk row is loaded one row ahead
-    float2 wnext = (r0 < r1 && lane < m) ? corr_W[crow_of(r0) * m + lane] : make_float2(0.f, 0.f);
-    for (int rr = r0; rr < r1; ++rr) {
-        const long crow = crow_of(rr);
-        // W for this chunk row, scaled
-        float2 wv = wnext;
-        if (rr + 1 < r1 && lane < m) wnext = corr_W[crow_of(rr + 1) * m + lane];
-        float mx = fmaxf(fabsf(wv.x), fabsf(wv.y));
-#pragma unroll
-        for (int o = 32; o >= 1; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
-        int ew = 0;
-        if (mx > 0.f && mx < 3.0e38f) frexpf(mx, &ew);
-        wv = make_float2(ldexpf(wv.x, -ew), ldexpf(wv.y, -ew));
-        if (w == 0) Ws[lane] = wv;
-        __syncthreads();
-        // wave w: a-tiles TPW w .. TPW w + TPW - 1
-#pragma unroll
-        for (int at2 = 0; at2 < TPW; ++at2) {
-            const int at = TPW * w + at2;
-            if (16 * at >= NA) break;
-            const int a = 16 * at + r16;
-            // A fragments: k = 32 ks + 8 kg + i; n = k mod 64
-            uint4 Af[4];
-#pragma unroll
-            for (int ks = 0; ks < 2; ++ks) {
-                uint32_t re[4], im[4];
-#pragma unroll
-                for (int i2 = 0; i2 < 4; ++i2) {
-                    float pr[2], pim[2];
-#pragma unroll
-                    for (int ii = 0; ii < 2; ++ii) {
-                        const int n = 32 * ks + 8 * kg + 2 * i2 + ii;
-                        const cr_h2 e = __builtin_bit_cast(cr_h2, Et[a][n]);
-                        const float2 wn = Ws[n];
-                        const float er = (float)e.x, ei = (float)e.y;
-                        pr[ii] = wn.x * er - wn.y * ei;
-                        pim[ii] = -(wn.x * ei + wn.y * er);
-                    }
-                    re[i2] = sp_pack<F16>(pr[0], pr[1]);
-                    im[i2] = sp_pack<F16>(pim[0], pim[1]);
-                }
-                Af[ks] = make_uint4(re[0], re[1], re[2], re[3]);
-                Af[2 + ks] = make_uint4(im[0], im[1], im[2], im[3]);
-            }
-            // transposed product D[b][a] = sum_k Qm[k][b] Pm[a][k]: the Q tile
-            // is the A operand and the P fragment the B operand (same
-            // registers and addresses), so a lane ends up with four
-            // consecutive t and writes them as one 8-byte store
-            const float sc = ldexpf(2.0f, ew);
-#pragma unroll
-            for (int bt = 0; bt < 4; ++bt) {
-                sp_f4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int ks = 0; ks < 4; ++ks) {
-                    const uint4 qv = *(const uint4 *)&Qt[16 * bt + r16][32 * ks + 8 * kg];
-                    acc = sp_mfma<F16>(qv, Af[ks], acc);
-                }
-                // lane: rows b = 16 bt + 4 kg + j, column a = 16 at + r16
-                const int t = 64 * (16 * at + r16) + 16 * bt + 4 * kg;
-                uint2 o;
-                if (DT == BF16) {
-                    o.x = (uint32_t)f32_to_bf16(acc[0] * sc) | ((uint32_t)f32_to_bf16(acc[1] * sc) << 16);
-                    o.y = (uint32_t)f32_to_bf16(acc[2] * sc) | ((uint32_t)f32_to_bf16(acc[3] * sc) << 16);
-                } else {
-                    o.x = sp_pack<F16>(acc[0] * sc, acc[1] * sc);
-                    o.y = sp_pack<F16>(acc[2] * sc, acc[3] * sc);
-                }
-                *(uint2 *)(corr + crow * chunk + t) = o;
-            }
-        }
-        __syncthreads();   // Ws is rewritten by the next chunk row
-    }
-}
-
-bool state_correction_mfma_ok(int chunk, int dtype) {
-    return (dtype == F16 || dtype == BF16) && chunk % 1024 == 0 && chunk / 64 <= CR_NA;
-}
-
-hipError_t launch_state_correction_mfma(const float *Abar, const float2 *corr_W, int B, int H, int m,
-                                        int chunk, int nchunk, int dtype, void *corr, hipStream_t s) {
-    const int rows_per_ch = B * nchunk;
-    int wg = 1;
-    while (H * wg < 1024 && rows_per_ch / (2 * wg) >= 4) wg *= 2;
-    dim3 grid(H * wg), block(256);
-    const bool big = chunk / 64 > 128;
-    if (dtype == BF16) {
-        if (big)
-            hipLaunchKernelGGL((state_correction_mfma<BF16, 256>), grid, block, 0, s, Abar, corr_W, B, H, m, chunk, nchunk, wg, (uint16_t *)corr);
-        else
-            hipLaunchKernelGGL((state_correction_mfma<BF16, 128>), grid, block, 0, s, Abar, corr_W, B, H, m, chunk, nchunk, wg, (uint16_t *)corr);
-    } else {
-        if (big)
-            hipLaunchKernelGGL((state_correction_mfma<F16, 256>), grid, block, 0, s, Abar, corr_W, B, H, m, chunk, nchunk, wg, (uint16_t *)corr);
-        else
-            hipLaunchKernelGGL((state_correction_mfma<F16, 128>), grid, block, 0, s, Abar, corr_W, B, H, m, chunk, nchunk, wg, (uint16_t *)corr);
-    }
-    return hipGetLastError();
-}
-
-// ---------------------------- per-channel tables of the fused state term ---
-// For the L = 8192 and 16384 convs with the initial-state term fused in (their read-out
-// computes 2 Re sum_n Abar_n^b V_n(a), t = 64 a + b, V_n(a) = W_n Abar_n^{64 a},
-// on the matrix cores), per channel, in fp16 (re, im) pairs:
-//   [0, 1024)     Abar_n^b as the A operand: uint4 (ib * 4 + kb) * 64 + 16 g + c
-//                 holds b = 16 ib + c and modes n = 16 kb + 4 g + q in dword q
-//   [1024, 1536)  Abar_n^{64 a}, a = 64 h2 + c: uint4 (h2 * 4 + kb) * 64 + 16 g + c,
-//                 modes n = 16 kb + 4 g + q in dword q
-//   [1536, 1552)  Abar_n^1024: uint4 kb * 4 + g, modes n = 16 kb + 4 g + q
-//   [1552, 1568)  Abar_n^8192, the same layout (chunk 16384: a in [128, 256)
-//                 takes Abar_n^{64 (a - 128)} times Abar_n^8192)
-// Modes n >= m hold powers of 0 (their weights W_n are zero).  Powers in float64.
-__device__ __forceinline__ uint32_t ct_h2(double2 p) {
-    typedef _Float16 h2 __attribute__((ext_vector_type(2)));
-    h2 v = {(_Float16)p.x, (_Float16)p.y};
-    return __builtin_bit_cast(uint32_t, v);
-}
-// Channel h's table, assembled in ts (CORR_TAB_U4 uint4 of LDS) by a
-// 256-thread workgroup, then written to dst in 16-byte pieces.
-__device__ void corr_tables_body(const float *Abar, int h, int m, uint4 *ts, uint4 *dst) {
-    const int tid = threadIdx.x, n = tid & 63, q4 = tid >> 6;
-    uint32_t *t = (uint32_t *)ts;
-    for (int i = tid; i < CORR_TAB_U4; i += 256) ts[i] = make_uint4(0, 0, 0, 0);   // unused tail
-    __syncthreads();
-    double2 z = make_double2(0.0, 0.0);
-    if (n < m) z = make_double2(Abar[2 * ((long)h * m + n)], Abar[2 * ((long)h * m + n) + 1]);
-    const int kb = n >> 4, g = (n >> 2) & 3, q = n & 3;
-    // b = 16 q4 + i: ib = q4, c = i
-    double2 p = sp_zpow(z, 16 * q4);
-    for (int i = 0; i < 16; ++i) {
-        t[((q4 * 4 + kb) * 64 + 16 * g + i) * 4 + q] = ct_h2(p);
-        p = sp_zmul(p, z);
-    }
-    // a = 64 h2 + c with h2 = q4 >> 1, c = 8 (q4 & 1) + i
-    const int h2 = q4 >> 1;
-    const double2 z64 = sp_zpow(z, 64);
-    double2 e = sp_zpow(z64, 64 * h2 + 8 * (q4 & 1));
-    for (int i = 0; i < 8; ++i) {
-        const int c = 8 * (q4 & 1) + i;
-        t[(1024 + (h2 * 4 + kb) * 64 + 16 * g + c) * 4 + q] = ct_h2(e);
-        e = sp_zmul(e, z64);
-    }
-    if (q4 == 0) t[(1536 + kb * 4 + g) * 4 + q] = ct_h2(sp_zpow(z, 1024));
-    if (q4 == 1) t[(1552 + kb * 4 + g) * 4 + q] = ct_h2(sp_zpow(z, 8192));   // chunk 16384: a >= 128
-    __syncthreads();
-    for (int i = tid; i < CORR_TAB_U4; i += 256) dst[i] = ts[i];
-}
-__global__ __launch_bounds__(256) void corr_tables_kernel(const float *Abar, int H, int m, uint4 *tab) {
-    __shared__ uint4 ts[CORR_TAB_U4];
-    corr_tables_body(Abar, blockIdx.x, m, ts, tab + (long)blockIdx.x * CORR_TAB_U4);
-}
-
-hipError_t launch_corr_tables(const float *Abar, int H, int m, uint4 *tab, hipStream_t s) {
-    if (m > 64) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(corr_tables_kernel, dim3(H), dim3(256), 0, s, Abar, H, m, tab);
     return hipGetLastError();
 }
 
@@ -646,80 +400,10 @@ __global__ void state_scan_kernel(const float *Abar, const float *C, const float
     }
 }
 
-// The same scan for the fused state term: one wavefront per (batch, channel)
-// row, lane n = mode (modes n >= m idle).  For every chunk the weights
-// W_n = C_n Abar_n x^(c)_n are written normalised, W / 2^e with max |W| in
-// [1/2, 1), as fp16 (re, im) pairs, 64 per chunk row (zero beyond m), with
-// the exponent e per chunk row.
-// One wavefront: row = b H + h, lane n = mode.
-__device__ void scan_w16_row(const float *Abar, const float *C, const float *x0, const float2 *states, long row,
-                             int H, int m, int chunk, int nchunk, uint32_t *w16, int *wexp, float *x_final, int n) {
-    const int h = (int)(row % H);
-    const bool on = n < m;
-    const long i = (long)h * m + n;
-    float2 cab = make_float2(0.f, 0.f), AN = make_float2(0.f, 0.f), x = make_float2(0.f, 0.f);
-    if (on) {
-        const double ar = Abar[2 * i], ai = Abar[2 * i + 1];
-        cab = cmul(make_float2(C[2 * i], C[2 * i + 1]), make_float2((float)ar, (float)ai));
-        AN = cexp_scaled((double)chunk, 0.5 * log(ar * ar + ai * ai), atan2(ai, ar));
-        if (x0) x = make_float2(x0[2 * (row * m + n)], x0[2 * (row * m + n) + 1]);
-    }
-    for (int c = 0; c < nchunk; ++c) {
-        const float2 W = cmul(cab, x);
-        float mx = fmaxf(fabsf(W.x), fabsf(W.y));
-#pragma unroll
-        for (int o = 32; o >= 1; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
-        int e = 0;
-        if (mx > 0.f && mx < 3.0e38f) frexpf(mx, &e);
-        typedef _Float16 h2 __attribute__((ext_vector_type(2)));
-        const h2 v = {(_Float16)ldexpf(W.x, -e), (_Float16)ldexpf(W.y, -e)};
-        const long rc = row * nchunk + c;
-        w16[rc * 64 + n] = __builtin_bit_cast(uint32_t, v);
-        if (n == 0) wexp[rc] = e;
-        if (on) x = cadd(cmul(AN, x), states[rc * m + n]);
-    }
-    if (x_final && on) {
-        x_final[2 * (row * m + n)] = x.x;
-        x_final[2 * (row * m + n) + 1] = x.y;
-    }
-}
-__global__ __launch_bounds__(256) void state_scan_w16_kernel(const float *Abar, const float *C, const float *x0,
-                                                             const float2 *states, int B, int H, int m, int chunk,
-                                                             int nchunk, uint32_t *w16, int *wexp, float *x_final) {
-    const long row = (long)blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (row >= (long)B * H) return;   // whole wavefronts leave together
-    scan_w16_row(Abar, C, x0, states, row, H, m, chunk, nchunk, w16, wexp, x_final, threadIdx.x & 63);
-}
-
-// The tail of the chunk-state kernel when one workgroup holds all chunk rows
-// of channel h: its table of the fused state term (assembled in the kernel's
-// LDS row ring, free by then) and the scan of its B rows, one wavefront per
-// row.  The chunk sums were written by this workgroup and are read back.
-__device__ void cs_state_tail(const StateTail &t, const float *Abar, const float2 *states, int B, int H, int m,
-                              int chunk, int nchunk, int h, uint4 *lds) {
-    corr_tables_body(Abar, h, m, lds, t.ctab + (long)h * CORR_TAB_U4);
-    const int w = threadIdx.x >> 6;
-    for (int b = w; b < B; b += 4)
-        scan_w16_row(Abar, t.C, t.x0, states, (long)b * H + h, H, m, chunk, nchunk, t.w16, t.wexp, t.x_final,
-                     threadIdx.x & 63);
-}
-
-hipError_t launch_state_scan_w16(const float *Abar, const float *C, const float *x0, const float2 *states,
-                                 int B, int H, int m, int chunk, int nchunk, uint32_t *w16, int *wexp,
-                                 float *x_final, hipStream_t s) {
-    if (m > 64) return hipErrorInvalidValue;
-    const long rows = (long)B * H;
-    hipLaunchKernelGGL(state_scan_w16_kernel, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, s, Abar, C, x0,
-                       states, B, H, m, chunk, nchunk, w16, wexp, x_final);
-    return hipGetLastError();
-}
-
 hipError_t launch_chunk_states(const void *u, const float *Abar, const float *Bbar, int B, int H,
-                               int L, int m, int chunk, int dtype, float2 *states, hipStream_t s,
-                               const StateTail *tail, bool *fused) {
-    if (fused) *fused = false;
+                               int L, int m, int chunk, int dtype, float2 *states, hipStream_t s) {
     if (chunk_states_mfma_ok(chunk, dtype))
-        return launch_chunk_states_mfma(u, Abar, Bbar, B, H, L, m, chunk, dtype, states, s, tail, fused);
+        return launch_chunk_states_mfma(u, Abar, Bbar, B, H, L, m, chunk, dtype, states, s);
     const int nchunk = L / chunk;
     const long ncr = (long)B * H * nchunk;
     const size_t lds = (size_t)chunk * sizeof(float) +

@@ -1,0 +1,112 @@
+"""One-pass state passing (16-bit rows, chunks 2048, 8192, 16384) against the
+float64 recurrence and against the chunked float32 convolution path, at the
+edges of its dispatch: one and many segments per row, a short last segment,
+one to four waves per workgroup, few modes, and parameters that leave the
+usual range."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import workloads
+from tests._util import check, cplx64, cplx_to_f32pairs, f32dev, to_dev, to_np64
+
+pytestmark = pytest.mark.gpu
+
+# fp16 tables and states: 2^-11 each, sums of 128 and 64 products around the
+# largest term, then the output's rounding (bf16: 2^-8), against the tensor's
+# and the row's maximum
+TOL = {workloads.F16: 5e-3, workloads.BF16: 1e-2}
+TOL_X = {workloads.F16: 3e-3, workloads.BF16: 1e-4}
+
+
+@pytest.fixture(scope="module")
+def h3():
+    import paper_2212_14052_amd as h3
+    h3.lib()
+    return h3
+
+
+def _run(h3, w, Ab, Bb, C, D, x0, chunk):
+    y, xf = h3.statepass_conv(to_dev(w.u, w.dtype), f32dev(Ab), f32dev(Bb), f32dev(C),
+                              None if D is None else f32dev(D), chunk, x0=None if x0 is None else f32dev(x0))
+    torch.cuda.synchronize()
+    return to_np64(y), cplx64(to_np64(xf))
+
+
+def _ref(w, Ab, Bb, C, D, x0):
+    return oracle.recurrence(w.u64, cplx64(Ab), cplx64(Bb), cplx64(C),
+                             None if D is None else D.astype(np.float64), x0=None if x0 is None else cplx64(x0))
+
+
+def _params(w):
+    A, B, C, dt = w.ssm.complex64()
+    Ab, Bb = oracle.zoh(A, B, dt)
+    return cplx_to_f32pairs(Ab), cplx_to_f32pairs(Bb), w.ssm.C
+
+
+@pytest.mark.parametrize("dtype", [workloads.F16, workloads.BF16])
+@pytest.mark.parametrize("B,H,L,chunk,m,x0", [
+    (1, 1, 2048, 2048, 64, True),          # one step, one wave
+    (1, 2, 2 * 2048, 2048, 1, False),      # one mode, two segments
+    (3, 5, 7 * 2048, 2048, 33, True),      # one step per segment
+    (1, 700, 5 * 2048, 2048, 8, True),     # three segments, the last one short
+    (1, 1025, 2048, 2048, 4, True),        # rows past one per SIMD: one segment
+    (2, 515, 2 * 2048, 2048, 16, False),   # two waves per workgroup
+    (5, 210, 2048, 2048, 64, True),        # five items, the last workgroup not full
+    (2, 3, 16384, 8192, 64, True),
+    (1, 3, 32768, 16384, 64, False),
+])
+def test_scan_matches_recurrence(h3, dtype, B, H, L, chunk, m, x0):
+    w = workloads.statepass_workload("t", B, H, L, chunk, dtype, seed=H + L, m=m, dt_lo=1e-3, dt_hi=1e-1,
+                                     x0_scale=1.0 if x0 else 0.0)
+    Ab, Bb, C = _params(w)
+    y, xf = _run(h3, w, Ab, Bb, C, w.D, w.x0, chunk)
+    ry, rx = _ref(w, Ab, Bb, C, w.D, w.x0)
+    check(y, ry, TOL[dtype], "y")
+    check(xf, rx, TOL_X[dtype], "x_final", rows=False)
+
+
+@pytest.mark.parametrize("dtype", [workloads.F16, workloads.BF16])
+@pytest.mark.parametrize("case", ["no_skip", "zero_b", "zero_c", "growing", "decayed", "tiny_u", "large_u", "scaled_c"])
+def test_scan_unusual_parameters(h3, dtype, case):
+    B, H, L = 2, 6, 4 * 2048
+    w = workloads.statepass_workload("t", B, H, L, 2048, dtype, seed=17, m=48, dt_lo=1e-3, dt_hi=1e-1, x0_scale=1.0)
+    Ab, Bb, C = (np.array(v) for v in _params(w))
+    D, x0 = w.D, np.array(w.x0)
+    if case == "no_skip":
+        D = None
+    elif case == "zero_b":          # modes that the input does not reach
+        Bb[:, ::3] = 0
+    elif case == "zero_c":          # modes that the output does not see, with a large state
+        C[:, ::3] = 0
+        x0[:, :, ::3] *= 1e4
+    elif case == "growing":         # |Abar| > 1 by a factor of three over the sequence
+        a = cplx64(Ab)
+        Ab = cplx_to_f32pairs(a / np.abs(a) * 3.0 ** (1.0 / L))
+        Bb = Bb * 1e-2
+    elif case == "decayed":         # modes gone within a few inputs, and Abar = 0
+        a = cplx64(Ab)
+        Ab = cplx_to_f32pairs(a * np.linspace(0.0, 0.5, a.shape[1]))
+    elif case in ("tiny_u", "large_u"):
+        # |y| reaches some 30 here: 2^12 times that leaves fp16 (65504)
+        s = 2.0 ** -10 if case == "tiny_u" else 2.0 ** (12 if dtype == workloads.BF16 else 10)
+        w.u, w.u64 = workloads.round_to(w.u64 * s, dtype)
+        x0 = (x0 * s).astype(np.float32)
+    elif case == "scaled_c":        # output weights far apart between channels
+        f = (10.0 ** np.linspace(-12, 12, H)).astype(np.float32) if dtype == workloads.BF16 else \
+            (10.0 ** np.linspace(-2, 3, H)).astype(np.float32)
+        C = C * f[:, None, None]
+        D = D * f
+    y, xf = _run(h3, w, Ab, Bb, C, D, x0, 2048)
+    ry, rx = _ref(w, Ab, Bb, C, D, x0)
+    for h in range(H):
+        check(np.ascontiguousarray(y[:, h]), np.ascontiguousarray(ry[:, h]), TOL[dtype], f"y{h}")
+    check(xf, rx, TOL_X[dtype], "x_final", rows=False)
+    if case == "decayed":
+        return   # the general path takes Abar's logarithm, which Abar = 0 has not
+    # the general path (float32 convolution of chunks of 512) on the same inputs
+    y2, x2 = _run(h3, w, Ab, Bb, C, D, x0, 512)
+    for h in range(H):
+        check(np.ascontiguousarray(y[:, h]), np.ascontiguousarray(y2[:, h]), 2 * TOL[dtype], f"y{h} chunk 512")
+    check(xf, x2, 2 * TOL_X[dtype], "x_final chunk 512", rows=False)
