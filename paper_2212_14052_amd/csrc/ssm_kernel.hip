@@ -232,21 +232,32 @@ __global__ __launch_bounds__(256) void kernel_gen_mfma(int mode, const float *P0
     }
     // ---- Q rows b = 16 w .. 16 w + 15 and P rows 4 NR w .. 4 NR w + 4 NR - 1 of mode n
     {
-        double2 p = zpow(z, 16 * w);
+        // z^16, z^32, z^64 by squaring; the waves' starting powers from those
+        // (w is uniform): z^(16 w) and z^(64 (a0 + 4 NR w))
+        const double2 z2 = zmul(z, z), z4 = zmul(z2, z2), z8 = zmul(z4, z4), z16 = zmul(z8, z8), z32 = zmul(z16, z16);
+        const double2 z64 = zmul(z32, z32);
+        const double2 one = make_double2(1.0, 0.0);
+        double2 p = w == 0 ? one : w == 1 ? z16 : w == 2 ? z32 : zmul(z16, z32);
 #pragma unroll
         for (int j = 0; j < 16; ++j) {
             Qt[16 * w + j][n] = (float)p.x;
             Qt[16 * w + j][64 + n] = (float)p.y;
-            p = zmul(p, z);
+            if (j < 15) p = zmul(p, z);
         }
-        const double2 z64 = zpow(z, 64);
-        double2 q = zpow(z64, a0 + 4 * NR * w);
+        double2 s = zmul(z64, z64);
+        s = zmul(s, s);
+#pragma unroll
+        for (int i = 1; i < NR; i *= 2) s = zmul(s, s);   // z64^(4 NR)
+        double2 q = a0 > 0 ? zpow(z64, a0) : one;
+        if (w > 0) q = a0 > 0 ? zmul(q, s) : s;
+        if (w > 1) q = zmul(q, s);
+        if (w > 2) q = zmul(q, s);
 #pragma unroll
         for (int j = 0; j < 4 * NR; ++j) {
             const float qr = (float)q.x, qi = (float)q.y;
             Pm[4 * NR * w + j][n] = Wn.x * qr - Wn.y * qi;
             Pm[4 * NR * w + j][64 + n] = -(Wn.x * qi + Wn.y * qr);
-            q = zmul(q, z64);
+            if (j < 4 * NR - 1) q = zmul(q, z64);
         }
     }
     __syncthreads();
@@ -282,8 +293,10 @@ __global__ __launch_bounds__(256) void kernel_gen_mfma(int mode, const float *P0
 }
 
 // Rows of 64 outputs per workgroup: 64 once the output row holds that many
-// (half the workgroups, each sharing its setup among twice the outputs), else 32.
-static inline int kgen_rows(int L) { return L / 64 >= 64 ? 64 : 32; }
+// (half the workgroups, each sharing its setup among twice the outputs), else
+// 32, and 16 where the row has no more (L <= 1024: 32 rows would compute as
+// many again for nothing; H = 4096, L = 1024: 35 -> 24 us together with the shared squarings of the set-up).
+static inline int kgen_rows(int L) { return L / 64 >= 64 ? 64 : L / 64 > 16 ? 32 : 16; }
 
 static void launch_kgen_mfma(int mode, const float *P0, const float *P1, const float *C, const float *dt,
                              int H, int m, int L, float *k, int div, long nrows, hipStream_t s) {
@@ -292,8 +305,10 @@ static void launch_kgen_mfma(int mode, const float *P0, const float *P1, const f
     const dim3 grid((unsigned)(nrt * nrows)), block(256);
     if (R == 64)
         hipLaunchKernelGGL(kernel_gen_mfma<4>, grid, block, 0, s, mode, P0, P1, C, dt, H, m, L, k, div);
-    else
+    else if (R == 32)
         hipLaunchKernelGGL(kernel_gen_mfma<2>, grid, block, 0, s, mode, P0, P1, C, dt, H, m, L, k, div);
+    else
+        hipLaunchKernelGGL(kernel_gen_mfma<1>, grid, block, 0, s, mode, P0, P1, C, dt, H, m, L, k, div);
 }
 
 hipError_t launch_discretize(const float *A, const float *B, const float *dt, int H, int m,
