@@ -33,6 +33,7 @@ EXTRA = {
     # with the VALU, so AGPR destinations only add copies
     "fftconv_wave.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
     "fftconv_wave16k.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
+    "conv_direct.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
     "ssm_scan.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
     # its compile-time twiddle tables need more constexpr evaluation steps
     # than clang's default allows

@@ -1,0 +1,247 @@
+// Fused convolution of 16-bit rows by direct summation on the matrix cores
+// (L = 256, 512, 1024 and 4096; L = 2048 and 8192 up have their own
+// transforms, shorter rows and float32 the VALU transform):
+//     y[t] = sum_{s <= t} k[t-s] u[s] + D u[t],
+// or, for the input gradient, the correlation sum_{s >= t} k[s-t] u[s] + D u[t].
+//
+// u is 16-bit as it comes; the float32 kernel (skip term in its first tap) is
+// split into two 16-bit pieces, k = hi + lo, so that every product is exact in
+// the matrix core's float32 and the result is the float32 sum of a kernel
+// rounded to 22 bits (fp16) or 16 (bf16): its error is the output's own
+// rounding, as with the float32 transform that this replaces.
+//
+// One tile product, rows i < 16, columns n < 16, reduction kk < 32:
+//     D[i][n] += sum_kk A[i][kk] B[kk][n],   A[i][kk] = k[tau + 16 + i - kk],
+//                                            B[kk][n] = u[t0 + 16 n - tau - 16 + kk]
+// adds the lags tau + 16 + i - kk to y[t0 + 16 n + i].  With tau = 256 d + rho
+// the kernel tiles A_d and the input tiles B_a (at 256 a - rho) form a
+// product of polynomials over 256-blocks, D_b += sum_d A_d B_{b-d}, so NB
+// tiles of each feed NB (NB + 1) / 2 products (NB = L / 256) and the half
+// square above the diagonal is left out.
+//
+// Split of the work: one wave per R rows of a channel, all waves of a
+// workgroup on one channel, whose kernel pieces they share in LDS (read as
+// five dwords and shifted by half a dword where a lane's taps start at an odd
+// element).  R = 2 up to L = 1024 reads each kernel tile once for two rows
+// (B = 8, H = 768, L = 1024: R = 1 / 2 / 4: 29 / 27 / 30 us with the kernel
+// generation); at 4096 one row's 16 accumulator tiles and four kernel tiles
+// at a time (hi and lo) let three waves share a SIMD (134 us at B = 5, H =
+// 767; eight tiles and two waves: 144).  Bound by the matrix cores, L^2 (1 +
+// 256 / L) multiply-adds per row, and by the LDS reads up to 1024.
+//
+// Measured, with the kernel generation (us; the float32 transform before): B =
+// 16, H = 1024, L = 512, bf16: 66 -> 23; B = 8, H = 768, L = 1024, fp16: 42 ->
+// 24; B = 5, H = 767, L = 4096, bf16: 158 -> 134.
+#include "common.h"
+#include "internal.h"
+
+namespace h3 {
+namespace {
+
+typedef _Float16 cd_h8 __attribute__((ext_vector_type(8)));
+typedef __bf16 cd_b8 __attribute__((ext_vector_type(8)));
+typedef _Float16 cd_h2 __attribute__((ext_vector_type(2)));
+typedef __bf16 cd_b2 __attribute__((ext_vector_type(2)));
+typedef unsigned cd_u4 __attribute__((ext_vector_type(4)));
+typedef float cd_f2 __attribute__((ext_vector_type(2)));
+typedef float cd_f4 __attribute__((ext_vector_type(4)));
+
+template <int DT>
+__device__ __forceinline__ cd_f4 cd_mfma(uint4 a, uint4 b, cd_f4 c) {
+    if constexpr (DT == BF16)
+        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(cd_b8, a), __builtin_bit_cast(cd_b8, b), c, 0, 0, 0);
+    else
+        return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(cd_h8, a), __builtin_bit_cast(cd_h8, b), c, 0, 0, 0);
+}
+template <int DT>
+__device__ __forceinline__ uint32_t cd_pack(float lo, float hi) {
+    const cd_f2 v = {lo, hi};
+    if constexpr (DT == BF16) return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, cd_b2));
+    else return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, cd_h2));
+}
+template <int DT>
+__device__ __forceinline__ uint16_t cd_round(float v) { return DT == BF16 ? f32_to_bf16(v) : f32_to_f16(v); }
+template <int DT>
+__device__ __forceinline__ float cd_value(uint16_t v) { return DT == BF16 ? bf16_to_f32(v) : f16_to_f32(v); }
+
+constexpr int CD_MAXW = 8;
+
+
+// LDS elements (16-bit) of the two kernel pieces and of a row slot
+template <int NB>
+struct CdPlan {
+    static constexpr int L = 256 * NB;
+    static constexpr int KS = L + 24, US = L + 240;
+    static constexpr size_t lds(int waves, int R) { return 2 * (2 * (size_t)KS + (size_t)waves * R * US); }
+};
+
+// Workgroup: one channel, `blockDim.x / 64` waves of R rows each.  CONJ: the
+// correlation y[t] = sum_{s>=t} k[s-t] u[s] (+ D u[t]) instead.
+template <int DT, int NB, int R, bool CONJ>
+__global__ __launch_bounds__(64 * CD_MAXW, NB == 16 ? 3 : 4) void conv_direct_kernel(const uint16_t *u, const float *k, const float *D,
+                                                                     uint16_t *y, int B, int H, int wg_per_ch) {
+    using P = CdPlan<NB>;
+    constexpr int L = P::L;
+    extern __shared__ __attribute__((aligned(16))) uint16_t cd_sm[];
+    __shared__ float red[CD_MAXW];
+    const int tid = threadIdx.x, lane = tid & 63, nt = blockDim.x, nw = nt >> 6;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int h = blockIdx.x / wg_per_ch, part = blockIdx.x % wg_per_ch;
+    const int i16 = lane & 15, g = lane >> 4;
+    const int b0 = (part * nw + w) * R, nr = min(R, B - b0);   // may be <= 0
+    uint16_t *kh = cd_sm, *kl = cd_sm + P::KS;
+    uint16_t *us = cd_sm + 2 * P::KS + w * R * P::US;
+
+    // the wave's rows into LDS, zeros in front (behind, for the correlation)
+    constexpr int PIECES = L / 8, PT = (PIECES + 63) / 64;
+    cd_u4 raw[R][PT];
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int p = 0; p < PT; ++p)
+            // (rows and pieces past the end: the last one again, never used)
+            raw[r][p] = *(const cd_u4 *)(u + ((long)min(b0 + r, B - 1) * H + h) * L + 8 * min(64 * p + lane, PIECES - 1));
+
+    // the kernel as two 16-bit pieces hi + lo (fp16: times a power of two that
+    // puts its largest value in [2^14, 2^15), so that lo stays normal),
+    // reversed: element L - t holds k_t (the correlation: element 16 + t)
+    const float skip = D ? D[h] : 0.f;
+    const float *kr = k + (long)h * L;
+    int ek = 0;
+    if constexpr (DT == F16) {
+        float mx = 0.f;
+        for (int t = tid; t < L; t += nt) mx = fmaxf(mx, fabsf(t == 0 ? kr[0] + skip : kr[t]));
+#pragma unroll
+        for (int o = 32; o >= 1; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
+        if (lane == 0) red[w] = mx;
+        __syncthreads();
+        for (int v = 0; v < nw; ++v) mx = fmaxf(mx, red[v]);
+        ek = pow2_exp(mx) - 15;
+    }
+    for (int t = tid; t < L; t += nt) {
+        const float v = ldexpf(t == 0 ? kr[0] + skip : kr[t], -ek);
+        const uint16_t hi = cd_round<DT>(v);
+        const int x = CONJ ? 16 + t : L - t;
+        kh[x] = hi;
+        kl[x] = cd_round<DT>(v - cd_value<DT>(hi));
+    }
+    // zeros: lags below 0 and (reversed: element 0) from L on
+    for (int x = tid; x < 24; x += nt) {
+        const int z = CONJ ? (x < 16 ? x : L + x) : (x == 0 ? 0 : L + x);
+        kh[z] = 0;
+        kl[z] = 0;
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        uint16_t *ur = us + r * P::US;
+#pragma unroll
+        for (int p = 0; p < PT; ++p) *(cd_u4 *)(ur + (CONJ ? 0 : 240) + 8 * min(64 * p + lane, PIECES - 1)) = raw[r][p];
+        if (lane < 30) *(uint4 *)(ur + (CONJ ? L : 0) + 8 * lane) = make_uint4(0, 0, 0, 0);
+    }
+    __syncthreads();
+    if (nr <= 0) return;   // whole waves; no barrier follows
+
+    cd_f4 acc[R][NB];
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int b = 0; b < NB; ++b) acc[r][b] = cd_f4{0.f, 0.f, 0.f, 0.f};
+    // A: lags 256 d + rho + 16 + i - kk (correlation: 256 d + rho + kk - i),
+    // kk = 8 g + e; five dwords from the even element below, shifted
+    const int e0 = CONJ ? 16 - i16 + 8 * g : L - 16 - i16 + 8 * g;
+    const uint32_t sh = (uint32_t)(i16 & 1) * 16;
+    const uint32_t *kh32 = (const uint32_t *)kh + (e0 >> 1), *kl32 = (const uint32_t *)kl + (e0 >> 1);
+    // B: inputs 256 a - rho - 16 + 16 n + kk (correlation: 256 a + rho + 16 n + kk)
+    const uint16_t *ub = us + (CONJ ? 0 : 224) + 16 * i16 + 8 * g;
+    auto afrag = [&](const uint32_t *s) {
+        const uint32_t q0 = s[0], q1 = s[1], q2 = s[2], q3 = s[3], q4 = s[4];
+        return make_uint4(__builtin_amdgcn_alignbit(q1, q0, sh), __builtin_amdgcn_alignbit(q2, q1, sh),
+                          __builtin_amdgcn_alignbit(q3, q2, sh), __builtin_amdgcn_alignbit(q4, q3, sh));
+    };
+    constexpr int DB = NB < 4 ? NB : 4;   // kernel tiles held at once (hi and lo)
+#pragma unroll 1
+    for (int rho = 0; rho < 256; rho += 32) {
+#pragma unroll
+        for (int d0 = 0; d0 < NB; d0 += DB) {
+            uint4 Ah[DB], Al[DB];
+#pragma unroll
+            for (int d = 0; d < DB; ++d) {
+                const int o = (CONJ ? rho : -rho) / 2 + (CONJ ? 128 : -128) * (d0 + d);
+                Ah[d] = afrag(kh32 + o);
+                Al[d] = afrag(kl32 + o);
+            }
+#pragma unroll
+            for (int a = CONJ ? d0 : 0; a < (CONJ ? NB : NB - d0); ++a)
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    if (r > 0 && r >= nr) continue;
+                    const uint4 Bv = *(const uint4 *)(ub + r * P::US + 256 * a + (CONJ ? rho : -rho));
+#pragma unroll
+                    for (int d = 0; d < DB; ++d) {
+                        const int b = CONJ ? a - d0 - d : a + d0 + d;
+                        if (b >= 0 && b < NB) acc[r][b] = cd_mfma<DT>(Ah[d], Bv, acc[r][b]);
+                    }
+#pragma unroll
+                    for (int d = 0; d < DB; ++d) {
+                        const int b = CONJ ? a - d0 - d : a + d0 + d;
+                        if (b >= 0 && b < NB) acc[r][b] = cd_mfma<DT>(Al[d], Bv, acc[r][b]);
+                    }
+                }
+        }
+    }
+    const float s = ldexpf(1.f, ek);
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+        if (r < nr) {
+            uint16_t *yr = y + ((long)(b0 + r) * H + h) * L + 16 * i16 + 4 * g;
+#pragma unroll
+            for (int b = 0; b < NB; ++b)
+                *(uint2 *)(yr + 256 * b) = make_uint2(cd_pack<DT>(acc[r][b][0] * s, acc[r][b][1] * s),
+                                                      cd_pack<DT>(acc[r][b][2] * s, acc[r][b][3] * s));
+        }
+}
+
+template <int DT, int NB, int R, bool CONJ>
+hipError_t launch_direct(const ConvArgs &a, const float *k, hipStream_t s) {
+    using P = CdPlan<NB>;
+    const int groups = (a.B + R - 1) / R;
+    int wgc = (groups + CD_MAXW - 1) / CD_MAXW;
+    while ((long)a.H * wgc < 512 && wgc * 2 <= groups) wgc *= 2;
+    const int nw = (groups + wgc - 1) / wgc;
+    const size_t lds = P::lds(nw, R);
+    auto fn = conv_direct_kernel<DT, NB, R, CONJ>;
+    if (lds > 60000) (void)hipFuncSetAttribute((const void *)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    hipLaunchKernelGGL(fn, dim3((unsigned)(a.H * wgc)), dim3(64 * nw), lds, s, (const uint16_t *)a.u, k, a.D,
+                       (uint16_t *)a.y, a.B, a.H, wgc);
+    return hipGetLastError();
+}
+
+template <int DT, bool CONJ>
+hipError_t launch_direct_nb(const ConvArgs &a, const float *k, hipStream_t s) {
+    switch (a.L) {
+        case 256: return a.B >= 2 ? launch_direct<DT, 1, 2, CONJ>(a, k, s) : launch_direct<DT, 1, 1, CONJ>(a, k, s);
+        case 512: return a.B >= 2 ? launch_direct<DT, 2, 2, CONJ>(a, k, s) : launch_direct<DT, 2, 1, CONJ>(a, k, s);
+        case 1024: return a.B >= 2 ? launch_direct<DT, 4, 2, CONJ>(a, k, s) : launch_direct<DT, 4, 1, CONJ>(a, k, s);
+        case 4096: return launch_direct<DT, 16, 1, CONJ>(a, k, s);
+    }
+    return hipErrorInvalidValue;
+}
+
+}  // namespace
+
+// At L = 4096 a wave takes some 40 us for its row, and a launch that leaves the
+// chip part empty is no faster: from 1280 rows on (us, direct / transform, with
+// the kernel generation: B = 16, H = 64: 65 / 44; B = 1, H = 64: 47 / 24; B = 1,
+// H = 1482: 97 / 131; B = 2, H = 768: 68 / 83; B = 8, H = 250: 69 / 74).
+bool conv_direct_supported(int B, int H, int L, int dtype) {
+    if (dtype != F16 && dtype != BF16) return false;
+    return L == 256 || L == 512 || L == 1024 || (L == 4096 && (long)B * H >= 1280);
+}
+
+hipError_t launch_conv_direct(const ConvArgs &a, const float *k, hipStream_t s) {
+    if (!conv_direct_supported(a.B, a.H, a.L, a.dtype) || a.pair_mode != 0 || a.corr || a.gate) return hipErrorInvalidValue;
+    if (a.dtype == F16) return a.conj_k ? launch_direct_nb<F16, true>(a, k, s) : launch_direct_nb<F16, false>(a, k, s);
+    return a.conj_k ? launch_direct_nb<BF16, true>(a, k, s) : launch_direct_nb<BF16, false>(a, k, s);
+}
+
+}  // namespace h3
