@@ -48,6 +48,15 @@ template <> struct IO<BF16> {
     static __device__ __forceinline__ void st(uint16_t *p, long i, float v) { p[i] = f32_to_bf16(v); }
 };
 
+// 16-byte store of a result that nothing in this launch reads again, past the
+// caches' write-allocate path: whole lines of a streaming output go out at 5.2
+// TB/s beside their loads, against 4.0 with ordinary stores (a copy of 537 MB).
+// For partly written lines it is slower.
+__device__ __forceinline__ void store_stream(void *p, uint4 v) {
+    typedef unsigned u4 __attribute__((ext_vector_type(4)));
+    __builtin_nontemporal_store(__builtin_bit_cast(u4, v), (u4 *)p);
+}
+
 // Exponent e with m = f 2^e, f in [1/2, 1) (frexp); 0 for 0, NaN and inf, so
 // that such rows pass through unscaled.
 __device__ __forceinline__ int pow2_exp(float m) {

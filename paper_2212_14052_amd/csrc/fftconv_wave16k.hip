@@ -269,7 +269,7 @@ __device__ __forceinline__ void last_layer(uint32_t (&d)[64], uint4 *U, const ui
 #pragma unroll
         for (int r = 0; r < 8; ++r) {
             const int i8 = (w & 1) * 512 + r * 64 + lane;   // uint4 index within the row
-            *(uint4 *)(yrow + 8 * i8) = U[(w >> 1) * 1024 + i8];
+            store_stream(yrow + 8 * i8, U[(w >> 1) * 1024 + i8]);
         }
     }
 }

@@ -281,7 +281,7 @@ __device__ __forceinline__ void last_layer32(uint32_t (&d)[64], uint4 *U, const 
 #pragma unroll
         for (int r = 0; r < 8; ++r) {
             const int i8 = (w & 3) * 512 + r * 64 + lane;   // uint4 index within the row
-            *(uint4 *)(yrow + 8 * i8) = U[(w >> 2) * 2048 + i8];
+            store_stream(yrow + 8 * i8, U[(w >> 2) * 2048 + i8]);
         }
     }
 }

@@ -42,7 +42,6 @@ typedef _Float16 sc_h8 __attribute__((ext_vector_type(8)));
 typedef _Float16 sc_h2 __attribute__((ext_vector_type(2)));
 typedef __bf16 sc_b8 __attribute__((ext_vector_type(8)));
 typedef __bf16 sc_b2 __attribute__((ext_vector_type(2)));
-typedef unsigned sc_u4 __attribute__((ext_vector_type(4)));
 typedef float sc_f2 __attribute__((ext_vector_type(2)));
 typedef float sc_f16 __attribute__((ext_vector_type(16)));
 
@@ -417,7 +416,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void s
             settle();
 #pragma unroll
             for (int k = 0; k < 4; ++k)
-                __builtin_nontemporal_store(*(const sc_u4 *)(lines + 8 * SC_UP * k), (sc_u4 *)(yp + 512 * k));
+                store_stream(yp + 512 * k, *(const uint4 *)(lines + 8 * SC_UP * k));
             yp += SC_STEP;
             settle();
         }
