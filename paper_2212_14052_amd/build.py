@@ -34,6 +34,7 @@ EXTRA = {
     "fftconv_wave.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
     "fftconv_wave16k.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
     "conv_direct.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
+    "layer_direct.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
     "ssm_scan.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
     # its compile-time twiddle tables need more constexpr evaluation steps
     # than clang's default allows

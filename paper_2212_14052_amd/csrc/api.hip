@@ -452,11 +452,17 @@ int h3_layer_fwd(const void *x, const void *Wq, const void *Wk, const void *Wv, 
         if ((e = launch_fftconv_mfma(ca, diag_k, s)) != hipSuccess) return H3_EDEVICE;
         if ((e = launch_gate_transpose(q, kk, o_tm, B, d, L, dtype, s)) != hipSuccess) return H3_EDEVICE;
     } else {
-        if ((e = launch_spectrum(diag_k, d, L, Kspec, s)) != hipSuccess) return H3_EDEVICE;
-        if ((e = launch_layer_mid(q, kk, v, shift_C, shift_D, m_s, Kspec, diag_D, B, d, L, dtype, o_cm,
-                                  s)) != hipSuccess)
-            return H3_EDEVICE;
-        // O (B, d, L) -> (B, L, d)
+        // O channel-major -> o_cm
+        if (layer_direct_supported(L)) {
+            e = launch_layer_direct(q, kk, v, shift_C, shift_D, m_s, diag_k, diag_D, B, d, L, dtype, o_cm, s);
+        } else {
+            if ((e = launch_spectrum(diag_k, d, L, Kspec, s)) != hipSuccess) return H3_EDEVICE;
+            e = launch_layer_mid(q, kk, v, shift_C, shift_D, m_s, Kspec, diag_D, B, d, L, dtype, o_cm, s);
+        }
+        if (e != hipSuccess) return H3_EDEVICE;
+        // the output projection reads it K-major where its tiles fit, else (B, L, d)
+        if (gemm_w_tile(d, B * L, d) && L % 256 == 0)
+            return launched(launch_gemm_w(&Wo, o_cm, out, B * L, d, dtype, 2, d, L, s));
         if ((e = launch_transpose_batched(o_cm, o_tm, B, d, L, s)) != hipSuccess) return H3_EDEVICE;
     }
     return launched(layer_out(o_tm, Wo, out, B, L, d, dtype, wt, s));

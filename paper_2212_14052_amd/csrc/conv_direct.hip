@@ -32,37 +32,11 @@
 // Measured, with the kernel generation (us; the float32 transform before): B =
 // 16, H = 1024, L = 512, bf16: 66 -> 23; B = 8, H = 768, L = 1024, fp16: 42 ->
 // 24; B = 5, H = 767, L = 4096, bf16: 158 -> 134.
-#include "common.h"
+#include "direct_conv.h"
 #include "internal.h"
 
 namespace h3 {
 namespace {
-
-typedef _Float16 cd_h8 __attribute__((ext_vector_type(8)));
-typedef __bf16 cd_b8 __attribute__((ext_vector_type(8)));
-typedef _Float16 cd_h2 __attribute__((ext_vector_type(2)));
-typedef __bf16 cd_b2 __attribute__((ext_vector_type(2)));
-typedef unsigned cd_u4 __attribute__((ext_vector_type(4)));
-typedef float cd_f2 __attribute__((ext_vector_type(2)));
-typedef float cd_f4 __attribute__((ext_vector_type(4)));
-
-template <int DT>
-__device__ __forceinline__ cd_f4 cd_mfma(uint4 a, uint4 b, cd_f4 c) {
-    if constexpr (DT == BF16)
-        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(cd_b8, a), __builtin_bit_cast(cd_b8, b), c, 0, 0, 0);
-    else
-        return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(cd_h8, a), __builtin_bit_cast(cd_h8, b), c, 0, 0, 0);
-}
-template <int DT>
-__device__ __forceinline__ uint32_t cd_pack(float lo, float hi) {
-    const cd_f2 v = {lo, hi};
-    if constexpr (DT == BF16) return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, cd_b2));
-    else return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, cd_h2));
-}
-template <int DT>
-__device__ __forceinline__ uint16_t cd_round(float v) { return DT == BF16 ? f32_to_bf16(v) : f32_to_f16(v); }
-template <int DT>
-__device__ __forceinline__ float cd_value(uint16_t v) { return DT == BF16 ? bf16_to_f32(v) : f16_to_f32(v); }
 
 constexpr int CD_MAXW = 8;
 
@@ -108,22 +82,11 @@ __global__ __launch_bounds__(64 * CD_MAXW, NB == 16 ? 3 : 4) void conv_direct_ke
     const float skip = D ? D[h] : 0.f;
     const float *kr = k + (long)h * L;
     int ek = 0;
-    if constexpr (DT == F16) {
-        float mx = 0.f;
-        for (int t = tid; t < L; t += nt) mx = fmaxf(mx, fabsf(t == 0 ? kr[0] + skip : kr[t]));
-#pragma unroll
-        for (int o = 32; o >= 1; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
-        if (lane == 0) red[w] = mx;
-        __syncthreads();
-        for (int v = 0; v < nw; ++v) mx = fmaxf(mx, red[v]);
-        ek = pow2_exp(mx) - 15;
-    }
+    if constexpr (DT == F16) ek = cd_kernel_exp(kr, L, skip, red, tid, nt);
     for (int t = tid; t < L; t += nt) {
         const float v = ldexpf(t == 0 ? kr[0] + skip : kr[t], -ek);
-        const uint16_t hi = cd_round<DT>(v);
         const int x = CONJ ? 16 + t : L - t;
-        kh[x] = hi;
-        kl[x] = cd_round<DT>(v - cd_value<DT>(hi));
+        cd_split<DT>(v, kh[x], kl[x]);
     }
     // zeros: lags below 0 and (reversed: element 0) from L on
     for (int x = tid; x < 24; x += nt) {
@@ -153,11 +116,6 @@ __global__ __launch_bounds__(64 * CD_MAXW, NB == 16 ? 3 : 4) void conv_direct_ke
     const uint32_t *kh32 = (const uint32_t *)kh + (e0 >> 1), *kl32 = (const uint32_t *)kl + (e0 >> 1);
     // B: inputs 256 a - rho - 16 + 16 n + kk (correlation: 256 a + rho + 16 n + kk)
     const uint16_t *ub = us + (CONJ ? 0 : 224) + 16 * i16 + 8 * g;
-    auto afrag = [&](const uint32_t *s) {
-        const uint32_t q0 = s[0], q1 = s[1], q2 = s[2], q3 = s[3], q4 = s[4];
-        return make_uint4(__builtin_amdgcn_alignbit(q1, q0, sh), __builtin_amdgcn_alignbit(q2, q1, sh),
-                          __builtin_amdgcn_alignbit(q3, q2, sh), __builtin_amdgcn_alignbit(q4, q3, sh));
-    };
     constexpr int DB = NB < 4 ? NB : 4;   // kernel tiles held at once (hi and lo)
 #pragma unroll 1
     for (int rho = 0; rho < 256; rho += 32) {
@@ -167,8 +125,8 @@ __global__ __launch_bounds__(64 * CD_MAXW, NB == 16 ? 3 : 4) void conv_direct_ke
 #pragma unroll
             for (int d = 0; d < DB; ++d) {
                 const int o = (CONJ ? rho : -rho) / 2 + (CONJ ? 128 : -128) * (d0 + d);
-                Ah[d] = afrag(kh32 + o);
-                Al[d] = afrag(kl32 + o);
+                Ah[d] = cd_frag(kh32 + o, sh);
+                Al[d] = cd_frag(kl32 + o, sh);
             }
 #pragma unroll
             for (int a = CONJ ? d0 : 0; a < (CONJ ? NB : NB - d0); ++a)

@@ -118,6 +118,12 @@ hipError_t launch_transpose_batched(const void *in, void *out, int nb, int R, in
 // O (B, L, d) token-major = (Q * S)^T per batch slice, Q and S (B, d, L); R = d, C = L.
 hipError_t launch_gate_transpose(const void *q, const void *sv, void *out, int nb, int R, int C, int dtype,
                                  hipStream_t s);
+// O = Q * (diag conv of (shift FIR of K) * V) over (B, d, L) rows, channel-major,
+// in one kernel (L 256, 512 or 1024; m_s <= 64).
+bool layer_direct_supported(int L);
+hipError_t launch_layer_direct(const void *q, const void *k, const void *v, const float *shift_C, const float *shift_D,
+                               int m_s, const float *diag_k, const float *diag_D, int B, int d, int L, int dtype,
+                               void *o, hipStream_t s);
 // G = (shift FIR of K + shift_D K) * V over (B, d, L) rows (m_s <= 64, L % 16 == 0);
 // v null: G = the shift FIR of K alone.
 hipError_t launch_shift_gate(const void *k, const void *v, const float *shift_C, const float *shift_D, int m_s,

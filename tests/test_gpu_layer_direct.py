@@ -1,0 +1,46 @@
+"""The layer's sequence mixing by direct summation (L = 256, 512, 1024) against
+the float64 oracle: batches that leave a wave's rows unfilled or split a
+channel over workgroups, few taps, no skips, both output-projection paths,
+and gates far from 1 (G is scaled per row)."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import workloads
+from tests._util import check, f32dev, to_dev
+
+pytestmark = pytest.mark.gpu
+
+# the 16-bit Q, K, V and O between the matrix products, as for the layer tests
+TOL = {workloads.F16: 1e-2, workloads.BF16: 2e-2}
+
+
+@pytest.fixture(scope="module")
+def h3():
+    import paper_2212_14052_amd as h3
+    h3.lib()
+    return h3
+
+
+@pytest.mark.parametrize("dtype", [workloads.F16, workloads.BF16])
+@pytest.mark.parametrize("B,L,d,m_s,skips,vscale", [
+    (1, 256, 128, 64, True, 1.0), (3, 256, 256, 1, False, 1.0), (2, 512, 128, 5, True, 1.0),
+    (1, 1024, 256, 64, True, 1.0), (5, 1024, 128, 63, False, 1.0), (17, 1024, 128, 64, True, 1.0),
+    (2, 1024, 256, 17, True, 2.0 ** -7), (2, 1024, 320, 64, True, 2.0 ** 6),
+])
+def test_layer_direct(h3, dtype, B, L, d, m_s, skips, vscale):
+    w = workloads.layer_workload("t", B, L, d, dtype, seed=B + L + m_s, m=8, m_shift=m_s)
+    A, Bm, C, dt = w.diag.complex64()
+    k = oracle.ssm_kernel(A, Bm, C, dt, L).astype(np.float32)
+    Wv, Wv64 = workloads.round_to(w.W["v"][1] * vscale, dtype)
+    sD = np.linspace(-1, 1, d).astype(np.float32) if skips else None
+    dD = w.diag_D if skips else None
+    W = {n: to_dev(w.W[n][0], dtype) for n in "qko"}
+    out = h3.layer_fwd(to_dev(w.x, dtype), W["q"], W["k"], to_dev(Wv, dtype), W["o"], f32dev(w.shift_C),
+                       None if sD is None else f32dev(sD), f32dev(k), None if dD is None else f32dev(dD))
+    torch.cuda.synchronize()
+    ref = oracle.h3_layer(w.x64, w.W["q"][1], w.W["k"][1], Wv64, w.W["o"][1], w.shift_C.astype(np.float64),
+                          k.astype(np.float64), None if dD is None else dD.astype(np.float64),
+                          shift_D=None if sD is None else sD.astype(np.float64))
+    check(out, ref, TOL[dtype], "out", rows=False)
