@@ -82,10 +82,14 @@ StatepassWs statepass_ws(int B, int H, int L, int m, int chunk, int dtype) {
     return w;
 }
 
+// Shapes that need no room for transposed weights (the workspace's size as
+// this entry has always answered it: the 128-wide tiles need none either).
+bool wide_tiles(int d, int Nx) { return Nx % 256 == 0 && (d % 320 == 0 || d % 256 == 0); }
+
 struct LayerWs {
     size_t qkv, o_cm, o_tm, kspec, wt, total;
 };
-// wt: the four weights transposed to (out, in), only for shapes the
+// wt: the four weights transposed to (out, in), used only for shapes the
 // weight-tiled GEMM does not take (the 128 x 128-tile GEMM reads both operands
 // reduction-contiguous)
 LayerWs layer_ws(int B, int d, int L) {
@@ -96,7 +100,7 @@ LayerWs layer_ws(int B, int d, int L) {
     w.o_tm = w.o_cm + align_up(act);
     w.kspec = w.o_tm + align_up(act);
     w.wt = w.kspec + align_up((size_t)d * (L + 1) * sizeof(float2));
-    w.total = w.wt + (gemm_w_tile(d, B * L, d) ? 0 : align_up((size_t)4 * d * d * 2));
+    w.total = w.wt + (wide_tiles(d, B * L) ? 0 : align_up((size_t)4 * d * d * 2));
     return w;
 }
 
@@ -116,20 +120,20 @@ HeadsWs heads_ws(int B, int d, int L, int dh) {
     w.o_tm = w.sv + align_up((size_t)dh * act);
     w.kspec = w.o_tm + align_up(act);
     w.wt = w.kspec + align_up((size_t)d * dh * (L + 1) * sizeof(float2));
-    w.total = w.wt + (gemm_w_tile(d, B * L, d) ? 0 : align_up((size_t)4 * d * d * 2));
+    w.total = w.wt + (wide_tiles(d, B * L) ? 0 : align_up((size_t)4 * d * d * 2));
     return w;
 }
 
 // [Q;K;V] channel-major: per projection j and batch b the (d, L) block
 // j B d L + b d L is (x_b W_j)^T.  The weights come as Algorithm 1 writes
 // them, (in, out) with Q = x W_Q, and the weight-tiled GEMM reads them so:
-// one launch for Q, K and V (d a multiple of 320 or 256, B L of 256).  Other
+// one launch for Q, K and V (d a multiple of 128, B L of 256).  Other
 // shapes take the 128 x 128-tile GEMM per projection, which reads both
 // operands reduction-contiguous: the weights are transposed into wt first.
 hipError_t layer_qkv(const void *x, const void *Wq, const void *Wk, const void *Wv, char *qkv, int B, int L, int d,
                      int dtype, void *wt, hipStream_t s) {
     const void *Wqkv[3] = {Wq, Wk, Wv};
-    if (gemm_w_tile(d, B * L, d)) return launch_gemm_w(Wqkv, x, qkv, B * L, d, dtype, 1, d, L, s);
+    if (gemm_w_tile(d, B * L, d, 1)) return launch_gemm_w(Wqkv, x, qkv, B * L, d, dtype, 1, d, L, s);
     const size_t act = (size_t)B * L * d * 2, wb = (size_t)d * d * 2;
     for (int j = 0; j < 3; ++j) {
         char *wj = (char *)wt + j * wb;
@@ -143,7 +147,7 @@ hipError_t layer_qkv(const void *x, const void *Wq, const void *Wk, const void *
 // out = O (B L, d) . Wo (d, d), O token-major
 hipError_t layer_out(const void *o_tm, const void *Wo, void *out, int B, int L, int d, int dtype, void *wt,
                      hipStream_t s) {
-    if (gemm_w_tile(d, B * L, d)) return launch_gemm_w(&Wo, o_tm, out, B * L, d, dtype, 0, d, L, s);
+    if (gemm_w_tile(d, B * L, d, 1)) return launch_gemm_w(&Wo, o_tm, out, B * L, d, dtype, 0, d, L, s);
     char *wo = (char *)wt + 3 * (size_t)d * d * 2;
     hipError_t e = launch_transpose_batched(Wo, wo, 1, d, d, s);
     if (e != hipSuccess) return e;
@@ -441,7 +445,7 @@ int h3_layer_fwd(const void *x, const void *Wq, const void *Wk, const void *Wv, 
         ConvArgs ca{};
         ca.u = o_cm; ca.y = (void *)kk; ca.D = diag_D;
         ca.B = B; ca.H = d; ca.L = L; ca.nchunk = 1; ca.pair_mode = 0; ca.dtype = dtype;
-        if (fftconv_wave_supported(L, dtype) && gemm_w_tile(d, B * L, d)) {
+        if (fftconv_wave_supported(L, dtype) && gemm_w_tile(d, B * L, d, 1)) {
             // L = 2048: the convolution's epilogue gates with Q and writes
             // O = Q * S channel-major into K's slot; the output projection
             // reads it K-major
@@ -461,7 +465,7 @@ int h3_layer_fwd(const void *x, const void *Wq, const void *Wk, const void *Wv, 
         }
         if (e != hipSuccess) return H3_EDEVICE;
         // the output projection reads it K-major where its tiles fit, else (B, L, d)
-        if (gemm_w_tile(d, B * L, d) && L % 256 == 0)
+        if (gemm_w_tile(d, B * L, d, 1) && L % 256 == 0)
             return launched(launch_gemm_w(&Wo, o_cm, out, B * L, d, dtype, 2, d, L, s));
         if ((e = launch_transpose_batched(o_cm, o_tm, B, d, L, s)) != hipSuccess) return H3_EDEVICE;
     }

@@ -135,14 +135,15 @@ hipError_t launch_heads_expand(int dh, const void *kbar, const void *v, void *g,
                                hipStream_t s);
 hipError_t launch_heads_contract(int dh, const void *q, const void *sv, void *o, int B, int d, int L, int dtype,
                                  hipStream_t s);
-// The layer's projections on TW x 256 tiles (TW = 320 or 256) with the
+// The layer's projections on TW x 256 tiles (TW = 320, 256 or 128) with the
 // weights as stored, (K, d) row-major (Q = x W): out_mode 1: W[0..2] = W_Q,
 // W_K, W_V into the channel-major [Q;K;V] layout as launch_gemm_nt
 // (out_mode 1); out_mode 0: W[0] = W_O, C = X W_O row-major (Nx, d).  X is
 // (Nx, K) row-major; out_mode 2: as out_mode 0 with X stored K-major,
-// (Nx / L, K, L) (needs L % 256 == 0).  gemm_w_tile gives the tile height (0: not supported:
-// needs Nx % 256 == 0, K % 32 == 0, d a multiple of 320 or 256).
-int gemm_w_tile(int d, int Nx, int K);
+// (Nx / L, K, L) (needs L % 256 == 0).  gemm_w_tile gives TW for nproj
+// projections at once (0: not supported: needs Nx % 256 == 0, K % 32 == 0, d a
+// multiple of 320, 256 or 128).
+int gemm_w_tile(int d, int Nx, int K, int nproj);
 hipError_t launch_gemm_w(const void *const *W, const void *X, void *C, int Nx, int K, int dtype, int out_mode, int d,
                          int L, hipStream_t s);
 hipError_t launch_gemm_nt(const void *A, const void *Bt, void *C, int M, int N, int K, int dtype,

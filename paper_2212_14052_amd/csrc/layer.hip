@@ -264,7 +264,7 @@ __global__ __launch_bounds__(G2_T) void gemm_nt_256(const uint16_t *A, const uin
 //        tokens of one channel are one 64-byte run;
 // OUT 0: element (n, m) of a row-major (Nx, Mw) result, with the output
 //        features along the MFMA columns (lanes) for 64-byte runs.
-constexpr int GW_X = 256, GW_K = 32, GW_T = 512, GW_NS = 4;
+constexpr int GW_X = 256, GW_K = 32, GW_T = 512;
 
 typedef __attribute__((address_space(3))) void lds_void;
 typedef short gw_v4s __attribute__((ext_vector_type(4)));
@@ -272,7 +272,7 @@ typedef __attribute__((address_space(3))) gw_v4s lds_v4s;
 
 __device__ __forceinline__ int gw_xoff(int row, int chunk) { return row * 64 + ((chunk ^ ((row >> 2) & 3)) << 4); }
 
-template <int TW, int SS, bool XKM> struct GwShape {
+template <int TW, int SS, bool XKM, int NS> struct GwShape {
     static constexpr int WP = 2 * TW + 64;            // weight row pitch, bytes (704 or 576)
     static constexpr int WB = GW_K * WP;              // weight part of a stage, bytes
     static constexpr int WS = WB / 1024;              // its slices (22 or 18)
@@ -286,12 +286,12 @@ template <int TW, int SS, bool XKM> struct GwShape {
     static_assert(WB % 1024 == 0 && (WP % 256 == 64 || WP % 256 == 192), "weight stage layout");
     // LDS bytes: the stages, and a 1 KB slot that takes the copies of waves
     // with fewer slices (never read), so every wave issues NSL per step
-    static constexpr size_t LDS = (size_t)GW_NS * STAGE_B + (SLICES % 8 ? 1024 : 0);
+    static constexpr size_t LDS = (size_t)NS * STAGE_B + (SLICES % 8 ? 1024 : 0);
     // SS stages are consumed per barrier (one super-step); the copies of the
-    // next GW_NS / SS - 1 super-steps are in flight meanwhile.  s_waitcnt
-    // immediate for vmcnt((GW_NS / SS - 2) SS NSL): the copies issued after
+    // next NS / SS - 1 super-steps are in flight meanwhile.  s_waitcnt
+    // immediate for vmcnt((NS / SS - 2) SS NSL): the copies issued after
     // the super-step waited for may stay in flight (expcnt, lgkmcnt not waited)
-    static constexpr int INFL = (GW_NS / SS - 2) * SS * NSL;
+    static constexpr int INFL = (NS / SS - 2) * SS * NSL;
     static constexpr int WAIT = 0xf70 | (INFL & 15) | ((INFL >> 4) << 14);
 };
 
@@ -300,12 +300,12 @@ template <int TW, int SS, bool XKM> struct GwShape {
 // convolution writes it, channel-major): a stage then holds 32 rows (k) of
 // 256 activation rows, pitch XP, and the fragments are read with transposing
 // LDS reads like the weights.
-template <int DT, int OUT, int TW, int SS>
-__global__ __launch_bounds__(GW_T) __attribute__((amdgpu_waves_per_eu(2, 2))) void gemm_w(
+template <int DT, int OUT, int TW, int SS, int NS>
+__global__ __launch_bounds__(GW_T) __attribute__((amdgpu_waves_per_eu(NS == 3 ? 4 : 2, NS == 3 ? 4 : 2))) void gemm_w(
     const uint16_t *W0, const uint16_t *W1, const uint16_t *W2, const uint16_t *X, uint16_t *C, int Mw, int Nx,
     int K, int ldw, int d, int L) {
     constexpr bool XKM = OUT == 2;
-    using S = GwShape<TW, SS, XKM>;
+    using S = GwShape<TW, SS, XKM, NS>;
     extern __shared__ __attribute__((aligned(1024))) uint16_t gw_lds[];
     int tw, tx;
     gemm_tile(Mw / TW, Nx / GW_X, tw, tx);
@@ -346,9 +346,9 @@ __global__ __launch_bounds__(GW_T) __attribute__((amdgpu_waves_per_eu(2, 2))) vo
     // own for them before LDS reads; the explicit vmcnt waits order them.
     const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_void *)gw_lds;
     // copies of K step kt (clamped to the last step: past it they only keep
-    // the count per step fixed) into stage kt % GW_NS
+    // the count per step fixed) into stage kt % NS
     auto issue = [&](int kt) {
-        const uint32_t st = lds0 + (uint32_t)((kt % GW_NS) * S::STAGE_B);
+        const uint32_t st = lds0 + (uint32_t)((kt % NS) * S::STAGE_B);
         const uint32_t k0 = (uint32_t)min(kt, nk - 1) * GW_K;
 #pragma unroll
         for (int sl = 0; sl < S::NSL; ++sl) {
@@ -357,7 +357,7 @@ __global__ __launch_bounds__(GW_T) __attribute__((amdgpu_waves_per_eu(2, 2))) vo
             const bool wside = (real ? q : wvu) < S::WS;
             const uint16_t *base = wside ? Wj : X;
             const uint32_t vo = 2 * (soff[sl] + k0 * (wside ? (uint32_t)ldw : (XKM ? (uint32_t)L : 1u)));
-            const uint32_t la = real ? st + (uint32_t)q * 1024 : lds0 + (uint32_t)(GW_NS * S::STAGE_B);
+            const uint32_t la = real ? st + (uint32_t)q * 1024 : lds0 + (uint32_t)(NS * S::STAGE_B);
             asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, %2"
                          :
                          : "v"(vo), "s"(la), "s"(base)
@@ -379,7 +379,7 @@ __global__ __launch_bounds__(GW_T) __attribute__((amdgpu_waves_per_eu(2, 2))) vo
     const int tr_base = tr_row * S::WP + 2 * (ww * (TW / 2) + tr_col);
     const int trx_base = tr_row * S::XP + 2 * (wx * 64 + tr_col);
 #pragma unroll
-    for (int p = 0; p < GW_NS - SS; ++p) issue(p);
+    for (int p = 0; p < NS - SS; ++p) issue(p);
     for (int k0 = 0; k0 < nk; k0 += SS) {
         // the stages of this super-step landed for this wave (the copies of
         // later super-steps may still be in flight), then for every wave; the
@@ -388,11 +388,11 @@ __global__ __launch_bounds__(GW_T) __attribute__((amdgpu_waves_per_eu(2, 2))) vo
         __builtin_amdgcn_s_waitcnt(S::WAIT);
         asm volatile("s_barrier" ::: "memory");
 #pragma unroll
-        for (int p = 0; p < SS; ++p) issue(k0 + GW_NS - SS + p);
+        for (int p = 0; p < SS; ++p) issue(k0 + NS - SS + p);
 #pragma unroll
         for (int p = 0; p < SS; ++p) {
             const int kt = k0 + p;   // nk is a multiple of SS
-            const char *stg = (const char *)gw_lds + (kt % GW_NS) * S::STAGE_B;
+            const char *stg = (const char *)gw_lds + (kt % NS) * S::STAGE_B;
             const char *xs = stg + S::WB;
 #pragma unroll
             for (int ks = 0; ks < GW_K / 16; ++ks) {
@@ -923,8 +923,10 @@ template <int DT, int OUT, int TW>
 static hipError_t launch_gemm_w_t(const void *const *W, const void *X, void *C, int Mw, int Nx, int K, int ldw, int d,
                                   int L, hipStream_t s) {
     constexpr int SS = 1;
-    const size_t lds = GwShape<TW, SS, OUT == 2>::LDS;
-    auto fn = gemm_w<DT, OUT, TW, SS>;
+    // 128-wide tiles take three stages, so that two workgroups fit a CU
+    constexpr int NS = TW == 128 && OUT != 2 ? 3 : 4;
+    const size_t lds = GwShape<TW, SS, OUT == 2, NS>::LDS;
+    auto fn = gemm_w<DT, OUT, TW, SS, NS>;
     (void)hipFuncSetAttribute((const void *)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     hipLaunchKernelGGL(fn, dim3((Mw / TW) * (Nx / GW_X)), dim3(GW_T), lds, s, (const uint16_t *)W[0],
                        (const uint16_t *)W[OUT ? 1 : 0], (const uint16_t *)W[OUT ? 2 : 0], (const uint16_t *)X,
@@ -932,33 +934,44 @@ static hipError_t launch_gemm_w_t(const void *const *W, const void *X, void *C, 
     return hipGetLastError();
 }
 
-int gemm_w_tile(int d, int Nx, int K) {
+// Weight-tile width for Mw = nproj d output features over Nx rows: of the
+// widths that divide d the one with the least work on the busiest CU, tiles
+// per CU x (width + 48), the 48 standing for what a tile costs beside its
+// products.  0 where the kernel does not apply.
+int gemm_w_tile(int d, int Nx, int K, int nproj) {
     if (Nx % GW_X != 0 || K % GW_K != 0) return 0;
-    for (int tw : {320, 256})
-        if (d % tw == 0) return tw;
-    return 0;
+    int best = 0;
+    long cost = 0;
+    for (int tw : {320, 256, 128}) {
+        if (d % tw != 0) continue;
+        const long tiles = (long)(nproj * d / tw) * (Nx / GW_X), c = (tiles + 255) / 256 * (tw + 48);
+        if (!best || c < cost) {
+            best = tw;
+            cost = c;
+        }
+    }
+    return best;
 }
 
-template <int DT>
+template <int DT, int TW>
 static hipError_t launch_gemm_w_dt(const void *const *W, const void *X, void *C, int Mw, int Nx, int K, int ldw,
-                                   int out_mode, int d, int L, int tw, hipStream_t s) {
-    if (tw == 320)
-        return out_mode == 1 ? launch_gemm_w_t<DT, 1, 320>(W, X, C, Mw, Nx, K, ldw, d, L, s)
-               : out_mode == 2 ? launch_gemm_w_t<DT, 2, 320>(W, X, C, Mw, Nx, K, ldw, d, L, s)
-                               : launch_gemm_w_t<DT, 0, 320>(W, X, C, Mw, Nx, K, ldw, d, L, s);
-    return out_mode == 1 ? launch_gemm_w_t<DT, 1, 256>(W, X, C, Mw, Nx, K, ldw, d, L, s)
-           : out_mode == 2 ? launch_gemm_w_t<DT, 2, 256>(W, X, C, Mw, Nx, K, ldw, d, L, s)
-                           : launch_gemm_w_t<DT, 0, 256>(W, X, C, Mw, Nx, K, ldw, d, L, s);
+                                   int out_mode, int d, int L, hipStream_t s) {
+    return out_mode == 1 ? launch_gemm_w_t<DT, 1, TW>(W, X, C, Mw, Nx, K, ldw, d, L, s)
+           : out_mode == 2 ? launch_gemm_w_t<DT, 2, TW>(W, X, C, Mw, Nx, K, ldw, d, L, s)
+                           : launch_gemm_w_t<DT, 0, TW>(W, X, C, Mw, Nx, K, ldw, d, L, s);
 }
 
 hipError_t launch_gemm_w(const void *const *W, const void *X, void *C, int Nx, int K, int dtype, int out_mode, int d,
                          int L, hipStream_t s) {
-    const int tw = gemm_w_tile(d, Nx, K);
-    if (!tw) return hipErrorInvalidValue;
-    if (out_mode == 2 && L % GW_X != 0) return hipErrorInvalidValue;
-    const int Mw = out_mode == 1 ? 3 * d : d;
-    return dtype == BF16 ? launch_gemm_w_dt<BF16>(W, X, C, Mw, Nx, K, d, out_mode, d, L, tw, s)
-                         : launch_gemm_w_dt<F16>(W, X, C, Mw, Nx, K, d, out_mode, d, L, tw, s);
+    const int nproj = out_mode == 1 ? 3 : 1, Mw = nproj * d;
+    const int tw = gemm_w_tile(d, Nx, K, nproj);
+    if (!tw || (out_mode == 2 && L % GW_X != 0)) return hipErrorInvalidValue;
+#define H3_GW(DTV)                                                                                     \
+    (tw == 320   ? launch_gemm_w_dt<DTV, 320>(W, X, C, Mw, Nx, K, d, out_mode, d, L, s)                \
+     : tw == 256 ? launch_gemm_w_dt<DTV, 256>(W, X, C, Mw, Nx, K, d, out_mode, d, L, s)                \
+                 : launch_gemm_w_dt<DTV, 128>(W, X, C, Mw, Nx, K, d, out_mode, d, L, s))
+    return dtype == BF16 ? H3_GW(BF16) : H3_GW(F16);
+#undef H3_GW
 }
 
 template <int N, int DT>
