@@ -219,7 +219,8 @@ fftconv_wave4096_kernel(ConvArgs a, const float *k, int wg_per_ch, int pairs_per
 
     auto rows = [&](int qq, long &oa, long &ob) {
         oa = ((long)(2 * qq) * a.H + h) * L;
-        ob = (2 * qq + 1 < a.B) ? ((long)(2 * qq + 1) * a.H + h) * L : -1;
+        ob = -1;
+        if (2 * qq + 1 < a.B) ob = oa + (long)a.H * L;
     };
     // raw loads of a pair: lanes g < 2 hold points p2 = 4 g + j (j = 0..3),
     // p1 = c, p0 = 0..15 of both rows (8 consecutive 16-bit values per uint4)
@@ -520,7 +521,8 @@ fftconv_wave4096_kernel(ConvArgs a, const float *k, int wg_per_ch, int pairs_per
         // branch-free epilogue (a branch inside it lets the compiler hoist
         // all of the layer's MFMAs above it); the rare remainder scale picks
         // a second instance of the layer instead
-        const long orow = lane_b && ob >= 0 ? ob : oa;
+        const long obc = ob >= 0 ? ob : oa;   // wave-uniform
+        const long orow = lane_b ? obc : oa;
         // gate of the lane's 64 outputs (row a or b; a missing row b reads row a's)
         const uint16_t *grow = GATE ? (const uint16_t *)a.gate + orow : nullptr;
         if ((srema | sremb) == 0)

@@ -270,6 +270,18 @@ typedef __attribute__((address_space(3))) void lds_void;
 typedef short gw_v4s __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) gw_v4s lds_v4s;
 
+template <int DT>
+__device__ __forceinline__ uint32_t gw_pack(float lo, float hi) {
+    typedef float f2 __attribute__((ext_vector_type(2)));
+    const f2 v = {lo, hi};
+    if constexpr (DT == BF16) {
+        typedef __bf16 b2 __attribute__((ext_vector_type(2)));
+        return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, b2));
+    } else {
+        typedef _Float16 h2 __attribute__((ext_vector_type(2)));
+        return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, h2));
+    }
+}
 __device__ __forceinline__ int gw_xoff(int row, int chunk) { return row * 64 + ((chunk ^ ((row >> 2) & 3)) << 4); }
 
 template <int TW, int SS, bool XKM, int NS> struct GwShape {
@@ -426,41 +438,53 @@ __global__ __launch_bounds__(GW_T) __attribute__((amdgpu_waves_per_eu(NS == 3 ? 
                 for (int i = 0; i < S::TI; ++i)
 #pragma unroll
                     for (int j = 0; j < 2; ++j)
-                        acc[i][j] = OUT == 1 ? Mfma<DT>::run(fw[i], fx[j], acc[i][j])
-                                             : Mfma<DT>::run(fx[j], fw[i], acc[i][j]);
+                        acc[i][j] = OUT == 1 ? Mfma<DT>::run(fx[j], fw[i], acc[i][j])
+                                             : Mfma<DT>::run(fw[i], fx[j], acc[i][j]);
             }
         }
     }
     // no copy may land in LDS after the workgroup ends
     __builtin_amdgcn_s_waitcnt(0xf70);   // vmcnt(0)
-    // epilogue: the lane holds MFMA column (lane & 31) and rows 8 (e / 4) +
-    // 4 (lane / 32) + e % 4; element e of a tile lands at base + rstride x
-    // (8 (e / 4) + e % 4)
+    // epilogue: the tile goes out through LDS in two halves, as rows of the
+    // result in whole lines.  OUT 1: rows are output features (half: the
+    // waves' ww), 256 tokens each; else rows are tokens (half: wx / 2), TW
+    // features each.  The lane holds MFMA column (lane & 31) and rows 8 a + 4
+    // (lane / 32) .. + 3, which run along the row.
+    constexpr int ER = OUT == 1 ? TW / 2 : 128;              // rows per half
+    constexpr int EP = 2 * (OUT == 1 ? 256 : TW) + 16;       // row pitch, bytes
+    constexpr int EC = (OUT == 1 ? 256 : TW) / 8;            // 16-byte pieces per row
+    static_assert(ER * EP <= NS * S::STAGE_B && ER * EC % GW_T == 0, "epilogue layout");
+    char *eb = (char *)gw_lds;
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-        const int nx = x0 + wx * 64 + j * 32;
+    for (int half = 0; half < 2; ++half) {
+        __syncthreads();   // the stages' (or the first half's) reads are done
+        if ((OUT == 1 ? ww : wx >> 1) == half) {
 #pragma unroll
-        for (int i = 0; i < S::TI; ++i) {
-            const int mw = w0 + ww * (TW / 2) + i * 32;
-            long base, rstride;
+            for (int i = 0; i < S::TI; ++i)
+#pragma unroll
+                for (int j = 0; j < 2; ++j) {
+                    const int f = (OUT == 1 ? 0 : ww * (TW / 2)) + i * 32, x = (OUT == 1 ? wx : wx & 1) * 64 + j * 32;
+                    char *p = OUT == 1 ? eb + (f + (lane & 31)) * EP + 2 * (x + 4 * (lane >> 5))
+                                       : eb + (x + (lane & 31)) * EP + 2 * (f + 4 * (lane >> 5));
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        *(uint2 *)(p + 16 * e) = make_uint2(gw_pack<DT>(acc[i][j][4 * e], acc[i][j][4 * e + 1]),
+                                                            gw_pack<DT>(acc[i][j][4 * e + 2], acc[i][j][4 * e + 3]));
+                }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < ER * EC / GW_T; ++q) {
+            const int r = (q * GW_T + t) / EC, cc = (q * GW_T + t) % EC;
+            const uint4 v = *(const uint4 *)(eb + r * EP + 16 * cc);
+            long dst;
             if constexpr (OUT == 1) {
-                const int n = nx + (lane & 31), m = mw + 4 * (lane >> 5);
-                base = (long)jq * ((long)Nx * d) + (long)(n / L) * ((long)d * L) + (n % L) + (long)(m - jq * d) * L;
-                rstride = L;
+                const int n = x0 + 8 * cc, m = wc + half * ER + r;
+                dst = (long)jq * ((long)Nx * d) + (long)(n / L) * ((long)d * L) + (long)m * L + n % L;
             } else {
-                base = (long)(nx + 4 * (lane >> 5)) * Mw + mw + (lane & 31);
-                rstride = Mw;
+                dst = (long)(x0 + half * ER + r) * Mw + w0 + 8 * cc;
             }
-#pragma unroll
-            for (int e = 0; e < 16; ++e) {
-                const float v = acc[i][j][e];
-                uint16_t o;
-                if constexpr (DT == BF16)
-                    o = __builtin_bit_cast(uint16_t, (__bf16)v);
-                else
-                    o = __builtin_bit_cast(uint16_t, (_Float16)v);
-                C[base + rstride * (8 * (e >> 2) + (e & 3))] = o;
-            }
+            *(uint4 *)(C + dst) = v;
         }
     }
 }
