@@ -500,7 +500,7 @@ int h3_layer_fwd_heads(const void *x, const void *Wq, const void *Wk, const void
     const HeadsWs w = heads_ws(B, d, L, d_head);
     char *ws = (char *)workspace;
     char *qkv = ws + w.qkv;
-    void *kbar = ws + w.kbar, *g = ws + w.g, *sv = ws + w.sv, *o_tm = ws + w.o_tm, *wt = ws + w.wt;
+    void *kbar = ws + w.kbar, *g = ws + w.g, *o_tm = ws + w.o_tm, *wt = ws + w.wt;
     float2 *Kspec = (float2 *)(ws + w.kspec);
     const char *q = qkv, *kk = qkv + act, *v = qkv + 2 * act;
     hipError_t e;
@@ -509,19 +509,24 @@ int h3_layer_fwd_heads(const void *x, const void *Wq, const void *Wk, const void
     if ((e = launch_shift_gate(kk, nullptr, shift_C, shift_D, m_s, B, d, L, dtype, kbar, s)) != hipSuccess)
         return H3_EDEVICE;
     if ((e = launch_heads_expand(d_head, kbar, v, g, B, d, L, dtype, s)) != hipSuccess) return H3_EDEVICE;
-    // S = diagonal SSM of every (h, i, j) row: the fused convolution over d d_h channels
+    // S = diagonal SSM of every (h, i, j) row: the fused convolution over d d_h
+    // channels, in place (a wave or workgroup holds its rows whole before it
+    // writes them; a second buffer cost 20 us of 840 at d = 2560, d_h = 8)
     ConvArgs ca{};
-    ca.u = g; ca.y = sv; ca.D = diag_D;
+    ca.u = g; ca.y = g; ca.D = diag_D;
     ca.B = B; ca.H = d * d_head; ca.L = L; ca.nchunk = 1; ca.pair_mode = 0; ca.dtype = dtype;
     if (fftconv_mfma_supported(L, dtype)) {
-        if ((e = launch_fftconv_mfma(ca, diag_k, s)) != hipSuccess) return H3_EDEVICE;
+        e = launch_fftconv_mfma(ca, diag_k, s);
+    } else if (conv_direct_supported(B, d * d_head, L, dtype)) {
+        e = launch_conv_direct(ca, diag_k, s);
     } else {
         if ((e = launch_spectrum(diag_k, d * d_head, L, Kspec, s)) != hipSuccess) return H3_EDEVICE;
         ca.Kspec = Kspec;
-        if ((e = launch_fftconv(ca, s)) != hipSuccess) return H3_EDEVICE;
+        e = launch_fftconv(ca, s);
     }
-    // O_t[j] = sum_i Q_t[i] S_t[i][j], token-major; out = O Wo^T
-    if ((e = launch_heads_contract(d_head, q, sv, o_tm, B, d, L, dtype, s)) != hipSuccess) return H3_EDEVICE;
+    if (e != hipSuccess) return H3_EDEVICE;
+    // O_t[j] = sum_i Q_t[i] S_t[i][j], token-major; out = O Wo
+    if ((e = launch_heads_contract(d_head, q, g, o_tm, B, d, L, dtype, s)) != hipSuccess) return H3_EDEVICE;
     return launched(layer_out(o_tm, Wo, out, B, L, d, dtype, wt, s));
 }
 

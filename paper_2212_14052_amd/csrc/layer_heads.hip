@@ -12,7 +12,23 @@ namespace h3 {
 namespace {
 
 __device__ __forceinline__ float ld16(uint16_t v, int dt) { return dt == BF16 ? bf16_to_f32(v) : f16_to_f32(v); }
-__device__ __forceinline__ uint16_t st16(float v, int dt) { return dt == BF16 ? f32_to_bf16(v) : f32_to_f16(v); }
+template <int DT>
+__device__ __forceinline__ uint16_t st16(float v) {
+    if constexpr (DT == BF16) return __builtin_bit_cast(uint16_t, (__bf16)v);
+    else return f32_to_f16(v);
+}
+template <int DT>
+__device__ __forceinline__ uint32_t st16x2(float lo, float hi) {
+    typedef float f2 __attribute__((ext_vector_type(2)));
+    const f2 v = {lo, hi};
+    if constexpr (DT == BF16) {
+        typedef __bf16 b2 __attribute__((ext_vector_type(2)));
+        return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, b2));
+    } else {
+        typedef _Float16 h2 __attribute__((ext_vector_type(2)));
+        return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, h2));
+    }
+}
 
 // G[b, (h d_h + i) d_h + j, t] = Kbar[b, h d_h + i, t] V[b, h d_h + j, t], one
 // rounding; Kbar, V (B, d, L) channel-major, G (B, d d_h, L).  One thread per
@@ -45,9 +61,8 @@ __global__ __launch_bounds__(256) void heads_expand_kernel(const uint16_t *kbar,
             uint32_t o4[4];
 #pragma unroll
             for (int e = 0; e < 4; ++e)
-                o4[e] = (uint32_t)st16(kf[i][2 * e] * vf[j][2 * e], DT) |
-                        ((uint32_t)st16(kf[i][2 * e + 1] * vf[j][2 * e + 1], DT) << 16);
-            const long row = ((long)b * d * DH + (long)(h * DH + i) * DH + j) * L + t;
+                o4[e] = st16x2<DT>(kf[i][2 * e] * vf[j][2 * e], kf[i][2 * e + 1] * vf[j][2 * e + 1]);
+            const long row = (((long)b * nh + h) * DH * DH + i * DH + j) * L + t;
             *(uint4 *)(g + row) = make_uint4(o4[0], o4[1], o4[2], o4[3]);
         }
 }
@@ -61,7 +76,7 @@ template <int DT, int DH>
 __global__ __launch_bounds__(256) void heads_contract_kernel(const uint16_t *q, const uint16_t *s, int B, int d, int L,
                                                              uint16_t *o) {
     __shared__ __attribute__((aligned(16))) uint16_t tile[64][64 + 8];   // [token][channel]
-    const int ntt = L / 64, nct = d / 64;
+    const int ntt = L / 64, nct = d / 64, nh = d / DH;
     const int blk = blockIdx.x;
     const int tt = blk % ntt, ct = (blk / ntt) % nct, b = blk / (ntt * nct);
     const int cl = threadIdx.x >> 2, tq = (threadIdx.x & 3) * 16;
@@ -73,7 +88,7 @@ __global__ __launch_bounds__(256) void heads_contract_kernel(const uint16_t *q, 
 #pragma unroll
     for (int i = 0; i < DH; ++i) {
         const uint16_t *qr = q + ((long)b * d + h * DH + i) * L + t0;
-        const uint16_t *sr = s + ((long)b * d * DH + (long)(h * DH + i) * DH + j) * L + t0;
+        const uint16_t *sr = s + (((long)b * nh + h) * DH * DH + i * DH + j) * L + t0;
 #pragma unroll
         for (int hh = 0; hh < 2; ++hh) {
             const uint4 qv = *(const uint4 *)(qr + 8 * hh), sv = *(const uint4 *)(sr + 8 * hh);
@@ -86,7 +101,7 @@ __global__ __launch_bounds__(256) void heads_contract_kernel(const uint16_t *q, 
         }
     }
 #pragma unroll
-    for (int r = 0; r < 16; ++r) tile[tq + r][cl] = st16(acc[r], DT);
+    for (int r = 0; r < 16; ++r) tile[tq + r][cl] = st16<DT>(acc[r]);
     __syncthreads();
     // 64 tokens x 64 channels: thread -> token tk, channels 16 (tid & 3) .. + 15
     const int tk = threadIdx.x >> 2, cq = (threadIdx.x & 3) * 16;
@@ -95,47 +110,48 @@ __global__ __launch_bounds__(256) void heads_contract_kernel(const uint16_t *q, 
     *(uint4 *)(orow + 8) = *(const uint4 *)&tile[tk][cq + 8];
 }
 
-template <int DT>
-hipError_t launch_heads_dt(int dh, const void *kbar, const void *v, const void *q, void *g, const void *sv, void *o,
-                           int B, int d, int L, bool expand, hipStream_t st) {
+template <int DT, int DH>
+hipError_t launch_heads(const uint16_t *kbar, const uint16_t *v, const uint16_t *q, uint16_t *g, const uint16_t *sv,
+                        uint16_t *o, int B, int d, int L, hipStream_t st) {
+    if (kbar) {
+        const long n = (long)B * (d / DH) * (L / 8);
+        hipLaunchKernelGGL((heads_expand_kernel<DT, DH>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, kbar, v, B,
+                           d, L, g);
+    } else {
+        hipLaunchKernelGGL((heads_contract_kernel<DT, DH>), dim3((unsigned)((long)B * (d / 64) * (L / 64))), dim3(256), 0,
+                           st, q, sv, B, d, L, o);
+    }
+    return hipGetLastError();
+}
+
+hipError_t launch_heads_any(int dh, const void *kbar, const void *v, const void *q, void *g, const void *sv, void *o,
+                            int B, int d, int L, int dtype, hipStream_t s) {
+    if (d % 64 || L % 64) return hipErrorInvalidValue;
     const uint16_t *k16 = (const uint16_t *)kbar, *v16 = (const uint16_t *)v, *q16 = (const uint16_t *)q;
     const uint16_t *s16 = (const uint16_t *)sv;
     uint16_t *g16 = (uint16_t *)g, *o16 = (uint16_t *)o;
-    if (expand) {
-        const long n = (long)B * (d / dh) * (L / 8);
-        const dim3 grid((unsigned)((n + 255) / 256)), block(256);
-        switch (dh) {
-            case 2: hipLaunchKernelGGL((heads_expand_kernel<DT, 2>), grid, block, 0, st, k16, v16, B, d, L, g16); break;
-            case 4: hipLaunchKernelGGL((heads_expand_kernel<DT, 4>), grid, block, 0, st, k16, v16, B, d, L, g16); break;
-            case 8: hipLaunchKernelGGL((heads_expand_kernel<DT, 8>), grid, block, 0, st, k16, v16, B, d, L, g16); break;
-            default: return hipErrorInvalidValue;
-        }
-    } else {
-        const dim3 grid((unsigned)((long)B * (d / 64) * (L / 64))), block(256);
-        switch (dh) {
-            case 2: hipLaunchKernelGGL((heads_contract_kernel<DT, 2>), grid, block, 0, st, q16, s16, B, d, L, o16); break;
-            case 4: hipLaunchKernelGGL((heads_contract_kernel<DT, 4>), grid, block, 0, st, q16, s16, B, d, L, o16); break;
-            case 8: hipLaunchKernelGGL((heads_contract_kernel<DT, 8>), grid, block, 0, st, q16, s16, B, d, L, o16); break;
-            default: return hipErrorInvalidValue;
-        }
+#define H3_HEADS(DH)                                                                         \
+    (dtype == BF16 ? launch_heads<BF16, DH>(k16, v16, q16, g16, s16, o16, B, d, L, s)        \
+                   : launch_heads<F16, DH>(k16, v16, q16, g16, s16, o16, B, d, L, s))
+    switch (dh) {
+        case 2: return H3_HEADS(2);
+        case 4: return H3_HEADS(4);
+        case 8: return H3_HEADS(8);
     }
-    return hipGetLastError();
+#undef H3_HEADS
+    return hipErrorInvalidValue;
 }
 
 }  // namespace
 
 hipError_t launch_heads_expand(int dh, const void *kbar, const void *v, void *g, int B, int d, int L, int dtype,
                                hipStream_t s) {
-    if (d % 64 || L % 64) return hipErrorInvalidValue;
-    return dtype == BF16 ? launch_heads_dt<BF16>(dh, kbar, v, nullptr, g, nullptr, nullptr, B, d, L, true, s)
-                         : launch_heads_dt<F16>(dh, kbar, v, nullptr, g, nullptr, nullptr, B, d, L, true, s);
+    return launch_heads_any(dh, kbar, v, nullptr, g, nullptr, nullptr, B, d, L, dtype, s);
 }
 
 hipError_t launch_heads_contract(int dh, const void *q, const void *sv, void *o, int B, int d, int L, int dtype,
                                  hipStream_t s) {
-    if (d % 64 || L % 64) return hipErrorInvalidValue;
-    return dtype == BF16 ? launch_heads_dt<BF16>(dh, nullptr, nullptr, q, nullptr, sv, o, B, d, L, false, s)
-                         : launch_heads_dt<F16>(dh, nullptr, nullptr, q, nullptr, sv, o, B, d, L, false, s);
+    return launch_heads_any(dh, nullptr, nullptr, q, nullptr, sv, o, B, d, L, dtype, s);
 }
 
 }  // namespace h3
