@@ -36,8 +36,11 @@ EXTRA = {
     "conv_direct.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
     "layer_direct.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
     "ssm_scan.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
-    # its compile-time twiddle tables need more constexpr evaluation steps
+    # these files' compile-time twiddle tables need more constexpr evaluation steps
     # than clang's default allows
+    "fftconv.hip": ["-fconstexpr-steps=100000000"],
+    "fftconv_bwd.hip": ["-fconstexpr-steps=100000000"],
+    "layer.hip": ["-fconstexpr-steps=100000000"],
     "fftconv_wave32k.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1", "-fconstexpr-steps=100000000"],
 }
 

@@ -104,41 +104,161 @@ template <int N> struct FFTPlan {
     static_assert(N >= 32 && N <= 16384, "FFT length out of range");
 };
 
-// Twiddles exp(-2 pi i jm r / M) for r = 1..R-1 (M = Ns R, a power of two).
-// w1, w2, w4, w8 come from sincospi with exactly representable arguments;
-// the others are products of at most two of them.
+// Pass twiddles exp(-2 pi i jm r / M), jm < Ns = M / R, as constant tables
+// evaluated at compile time.  Entry jm holds w1, w2, w3, w4, w8, w12 for
+// radix 16 (the other nine are one product of two of them), w1..w4 for radix
+// 8, w1 and w2 for radix 4, w1 for radix 2: one to three 16-byte loads per
+// butterfly, whole lines across the wave, from a table that stays in the
+// vector caches (6 KB for the widest pass at N = 2048).  The transforms are
+// bound by VALU issue: w1, w2, w4, w8 from sincospif and up to three products
+// each took 3402 VALU instructions for a spectrum and a row pair at N = 2048.
+// Entries are the doubles rounded once.
+constexpr int kUnit = 16384;   // points on the unit circle
+struct UnitOctant {
+    double c[kUnit / 8 + 1], s[kUnit / 8 + 1];
+};
+constexpr UnitOctant make_unit_octant() {   // Taylor series on [0, pi/4]
+    UnitOctant t{};
+    for (int n = 0; n <= kUnit / 8; ++n) {
+        const double x = 6.283185307179586476925286766559 / kUnit * n, x2 = x * x;
+        double c = 1.0, s = x, tc = 1.0, ts = x;
+        for (int k = 1; k < 10; ++k) {
+            tc *= -x2 / ((2.0 * k - 1.0) * (2.0 * k));
+            ts *= -x2 / ((2.0 * k) * (2.0 * k + 1.0));
+            c += tc;
+            s += ts;
+        }
+        t.c[n] = c;
+        t.s[n] = s;
+    }
+    return t;
+}
+constexpr UnitOctant kUnitOctant = make_unit_octant();
+
+template <int M, int R> struct PassTab {
+    static constexpr int E = R == 16 ? 6 : R == 8 ? 4 : R / 2;   // factors per entry
+    alignas(16) float v[M / R * E * 2];
+};
+template <int M, int R> constexpr PassTab<M, R> make_pass_tab() {
+    static_assert(kUnit % M == 0, "pass length out of range");
+    PassTab<M, R> t{};
+    constexpr int E = PassTab<M, R>::E;
+    for (int jm = 0; jm < M / R; ++jm)
+        for (int e = 0; e < E; ++e) {
+            const int r = R == 16 && e >= 4 ? 4 * (e - 2) : e + 1;   // 1, 2, 3, 4, 8, 12
+            const int n = jm * r % M * (kUnit / M), quad = n / (kUnit / 4), m = n % (kUnit / 4);
+            const bool sw = m > kUnit / 8;         // past the octant: cos <-> sin
+            const int i = sw ? kUnit / 4 - m : m;
+            const double c = sw ? kUnitOctant.s[i] : kUnitOctant.c[i];
+            const double s = sw ? kUnitOctant.c[i] : kUnitOctant.s[i];
+            // exp(-i x) = c - i s, times (-i)^quad
+            const double re = quad == 0 ? c : quad == 1 ? -s : quad == 2 ? -c : s;
+            const double im = quad == 0 ? -s : quad == 1 ? -c : quad == 2 ? s : c;
+            t.v[(jm * E + e) * 2] = (float)re;
+            t.v[(jm * E + e) * 2 + 1] = (float)im;
+        }
+    return t;
+}
+template <int M, int R> __device__ const PassTab<M, R> kPassTab = make_pass_tab<M, R>();
+
+// The factors of Q butterflies of one pass, loaded ahead of their use.
+template <int R> struct PassTw {
+    static constexpr int Q = 16 / R, E = PassTab<16 * R, R>::E;
+    float2 w[Q * E];
+};
+template <int N, int R, int Ns>
+__device__ __forceinline__ PassTw<R> pass_tw_load(int tid) {
+    constexpr int T = N / 16;
+    // an opaque index per pass: equal passes of two transforms load their
+    // factors again instead of keeping them in registers in between
+    asm volatile("" : "+v"(tid));
+    PassTw<R> t;
+#pragma unroll
+    for (int q = 0; q < PassTw<R>::Q; ++q) {
+        const int jm = (tid + q * T) & (Ns - 1);
+        constexpr int E = PassTw<R>::E;
+        if constexpr (E == 1) {
+            t.w[q] = ((const float2 *)kPassTab<Ns * R, R>.v)[jm];
+        } else {
+            const float4 *p = (const float4 *)kPassTab<Ns * R, R>.v + jm * (E / 2);
+#pragma unroll
+            for (int e = 0; e < E / 2; ++e) {
+                const float4 f = p[e];
+                t.w[q * E + 2 * e] = make_float2(f.x, f.y);
+                t.w[q * E + 2 * e + 1] = make_float2(f.z, f.w);
+            }
+        }
+    }
+    return t;
+}
+
+// v[r] *= w_r, r = 1..R-1, for one butterfly; e holds its table entry.
 template <int R>
-__device__ __forceinline__ void pass_twiddles(float2 *v, int jm, int M) {
+__device__ __forceinline__ void pass_twiddles(float2 *v, const float2 *e) {
     float2 w[16];
-    const float base = -2.0f * (float)jm / (float)M;
-    {
-        float s, c;
-        sincospif(base, &s, &c);
-        w[1] = make_float2(c, s);
-    }
-    if (R > 2) {
-        float s, c;
-        sincospif(2.0f * base, &s, &c);
-        w[2] = make_float2(c, s);
-        w[3] = cmul(w[1], w[2]);
-    }
+    w[1] = e[0];
+    if (R > 2) w[2] = e[1];
+    if (R == 4) w[3] = cmul(w[1], w[2]);
     if (R > 4) {
-        float s, c;
-        sincospif(4.0f * base, &s, &c);
-        w[4] = make_float2(c, s);
-        w[5] = cmul(w[1], w[4]);
-        w[6] = cmul(w[2], w[4]);
-        w[7] = cmul(w[3], w[4]);
+        w[3] = e[2];
+        w[4] = e[3];
     }
     if (R > 8) {
-        float s, c;
-        sincospif(8.0f * base, &s, &c);
-        w[8] = make_float2(c, s);
-#pragma unroll
-        for (int r = 9; r < 16; ++r) w[r] = cmul(w[r - 8], w[8]);
+        w[8] = e[4];
+        w[12] = e[5];
     }
 #pragma unroll
+    for (int r = 5; r < R; ++r)
+        if (r % 4) w[r] = cmul(w[r % 4], w[r - r % 4]);
+#pragma unroll
     for (int r = 1; r < R; ++r) v[r] = cmul(v[r], w[r]);
+}
+
+// max of x over each group of W consecutive lanes, in every lane of the group
+// (W a power of two <= 64): lane exchanges on the VALU, no LDS.
+template <int CTRL> __device__ __forceinline__ uint32_t max_dpp(uint32_t x) {
+    const uint32_t y = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, 0xf, 0xf, false);
+    return x > y ? x : y;
+}
+template <int W> __device__ __forceinline__ uint32_t group_max(uint32_t x) {
+    if constexpr (W >= 2) x = max_dpp<0xB1>(x);     // quad_perm [1,0,3,2]
+    if constexpr (W >= 4) x = max_dpp<0x4E>(x);     // quad_perm [2,3,0,1]
+    if constexpr (W >= 8) x = max_dpp<0x141>(x);    // row_half_mirror
+    if constexpr (W >= 16) x = max_dpp<0x140>(x);   // row_mirror
+    if constexpr (W >= 32) {
+        const auto r = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+        x = r[0] > r[1] ? r[0] : r[1];
+    }
+    if constexpr (W >= 64) {
+        const auto r = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+        x = r[0] > r[1] ? r[0] : r[1];
+    }
+    return x;
+}
+
+// The largest |row a| and |row b| of a signal of T threads (float bits), from
+// each thread's own.  Signals of one wave or less need no LDS; wider ones pass
+// one value per wave through red (2 T / 64 words) and one barrier, which also
+// ends the reads of LDS before it.
+template <int T>
+__device__ __forceinline__ void signal_max(uint32_t *red, int tid, uint32_t &a, uint32_t &b) {
+    a = group_max<(T < 64 ? T : 64)>(a);
+    b = group_max<(T < 64 ? T : 64)>(b);
+    if constexpr (T > 64) {
+        constexpr int NW = T / 64;
+        if ((tid & 63) == 0) {
+            red[tid >> 6] = a;
+            red[NW + (tid >> 6)] = b;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < NW; ++i) {
+            a = red[i] > a ? red[i] : a;
+            b = red[NW + i] > b ? red[NW + i] : b;
+        }
+    } else {
+        __syncthreads();
+    }
 }
 
 // Stockham pass pieces for one signal in LDS buffer X (padded indexing).
@@ -153,15 +273,10 @@ __device__ __forceinline__ void pass_load(const float2 *X, int tid, float2 *v) {
     }
 }
 
-template <int N, int R, int Ns>
-__device__ __forceinline__ void pass_twiddle(int tid, float2 *v) {
-    if (Ns == 1) return;
-    constexpr int Q = 16 / R, T = N / 16;
+template <int R>
+__device__ __forceinline__ void pass_twiddle(const PassTw<R> &t, float2 *v) {
 #pragma unroll
-    for (int q = 0; q < Q; ++q) {
-        const int j = tid + q * T;
-        pass_twiddles<R>(v + q * R, j & (Ns - 1), Ns * R);
-    }
+    for (int q = 0; q < 16 / R; ++q) pass_twiddles<R>(v + q * R, t.w + q * PassTw<R>::E);
 }
 
 template <int R>
@@ -189,8 +304,9 @@ template <int N, int Ns, int NSEND>
 struct MidPasses {
     static __device__ __forceinline__ void run(float2 *X, int tid, float2 *v) {
         if constexpr (Ns < NSEND) {
+            const PassTw<16> tw = pass_tw_load<N, 16, Ns>(tid);
             pass_load<N, 16>(X, tid, v);
-            pass_twiddle<N, 16, Ns>(tid, v);
+            pass_twiddle<16>(tw, v);
             pass_dft<16>(v);
             __syncthreads();
             pass_store<N, 16, Ns>(X, tid, v);
@@ -214,8 +330,9 @@ __device__ __forceinline__ void fft_forward_from_regs(float2 *X, int tid, float2
         __syncthreads();
         MidPasses<N, R1, N / 16>::run(X, tid, v);
         // last forward pass: radix 16 at Ns = N/16, result stays in registers
+        const PassTw<16> tw = pass_tw_load<N, 16, N / 16>(tid);
         pass_load<N, 16>(X, tid, v);
-        pass_twiddle<N, 16, N / 16>(tid, v);
+        pass_twiddle<16>(tw, v);
         pass_dft<16>(v);
     }
 }
@@ -234,8 +351,9 @@ __device__ __forceinline__ void fft_second_from_regs(float2 *X, int tid, float2 
     pass_store<N, 16, 1>(X, tid, v);
     __syncthreads();
     MidPasses<N, 16, N / R1>::run(X, tid, v);
+    const PassTw<R1> tw = pass_tw_load<N, R1, N / R1>(tid);
     pass_load<N, R1>(X, tid, v);
-    pass_twiddle<N, R1, N / R1>(tid, v);
+    pass_twiddle<R1>(tw, v);
     pass_dft<R1>(v);
 }
 

@@ -101,7 +101,7 @@ __global__ __launch_bounds__(N / 16 >= 64 ? N / 16 : 64) void fftconv_kernel(Con
     constexpr int S = (T >= 64) ? 1 : 64 / T;
     constexpr int L = N / 2;
     extern __shared__ float2 lds[];
-    __shared__ uint32_t rmx[2 * S];   // per signal: max |row a|, max |row b| (float bits)
+    __shared__ uint32_t red[T > 64 ? T / 32 : 1];
     const int sig = threadIdx.x / T, tid = threadIdx.x % T;
     float2 *X = lds + sig * P::LDS;
     const int blk = xcd_logical_block(blockIdx.x, gridDim.x);
@@ -135,6 +135,7 @@ __global__ __launch_bounds__(N / 16 >= 64 ? N / 16 : 64) void fftconv_kernel(Con
     // Each row gets its own power-of-two scale (max |.| in [1/2, 1)): rounding
     // error of the shared transform then stays at each row's own scale, even
     // when one row is much smaller than the other.
+    uint32_t ma_b, mb_b;
     {
         float ma = 0.f, mb = 0.f;
 #pragma unroll
@@ -142,16 +143,11 @@ __global__ __launch_bounds__(N / 16 >= 64 ? N / 16 : 64) void fftconv_kernel(Con
             ma = fmaxf(ma, fabsf(ua[i]));
             mb = fmaxf(mb, fabsf(ub[i]));
         }
-        if (tid == 0) {
-            rmx[2 * sig] = 0u;
-            rmx[2 * sig + 1] = 0u;
-        }
-        __syncthreads();
-        atomicMax(&rmx[2 * sig], __float_as_uint(ma));
-        atomicMax(&rmx[2 * sig + 1], __float_as_uint(mb));
-        __syncthreads();
+        ma_b = __float_as_uint(ma);
+        mb_b = __float_as_uint(mb);
+        signal_max<T>(red, tid, ma_b, mb_b);
     }
-    const int ea = pow2_exp(__uint_as_float(rmx[2 * sig])), eb = pow2_exp(__uint_as_float(rmx[2 * sig + 1]));
+    const int ea = pow2_exp(__uint_as_float(ma_b)), eb = pow2_exp(__uint_as_float(mb_b));
     {
         const float sa = ldexpf(1.0f, -ea), sb = ldexpf(1.0f, -eb);
 #pragma unroll
@@ -203,9 +199,13 @@ __global__ __launch_bounds__(N / 16 >= 64 ? N / 16 : 64) void fftconv_kernel(Con
 // causal convolution plus D u on t < L) and keeps F(.)/N in registers, in the
 // layout the pointwise product reads; then it runs its row pairs.  One launch
 // instead of two, and no spectrum round trip through HBM.
+// Waves per SIMD: four (LDS allows 4.5 at N = 2048, four at 4096 and 8192),
+// three where 128 registers would spill.
+constexpr int kgen_waves(int N) { return N == 4096 || N == 512 || N == 32 ? 3 : 4; }
+
 template <int N, int DT>
-__global__ __launch_bounds__(N / 16 >= 64 ? N / 16 : 64) void fftconv_kgen_kernel(ConvArgs a, const float *k,
-                                                                                 int groups, int ppg) {
+__global__ __launch_bounds__(N / 16 >= 64 ? N / 16 : 64, kgen_waves(N)) void fftconv_kgen_kernel(
+    ConvArgs a, const float *k, int groups, int ppg) {
     using P = FFTPlan<N>;
     using io = IO<DT>;
     typedef typename io::T T_;
@@ -213,25 +213,26 @@ __global__ __launch_bounds__(N / 16 >= 64 ? N / 16 : 64) void fftconv_kgen_kerne
     constexpr int S = (T >= 64) ? 1 : 64 / T;
     constexpr int L = N / 2;
     extern __shared__ float2 lds[];
-    __shared__ uint32_t rmx[2 * S];   // per signal slot: max |row a|, max |row b| (float bits)
-    const int sig = threadIdx.x / T, tid = threadIdx.x % T;
+    __shared__ uint32_t red[T > 64 ? T / 32 : 1];
+    // one signal per block (T >= 64): the item, its rows and their addresses
+    // are the block's, held in scalar registers
+    const int sig = S == 1 ? 0 : threadIdx.x / T, tid = S == 1 ? threadIdx.x : threadIdx.x % T;
     float2 *X = lds + sig * P::LDS;
     const int item = xcd_logical_block(blockIdx.x, gridDim.x) * S + sig;
-    const bool act = item < a.H * groups;
+    const bool act = S == 1 || item < a.H * groups;   // S = 1: one block per item
     const int h = act ? item / groups : 0, grp = act ? item % groups : 0;
     const int npairs = (a.B + 1) / 2;
-    const T_ *u = (const T_ *)a.u;
-    T_ *y = (T_ *)a.y;
 
     // spectrum of k_h + D delta, scaled by 1/N (conjugated for the correlation)
     float2 kf[16];
+    const float *kh = k + (long)h * L;
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
         const int j = tid + q * T;
 #pragma unroll
         for (int r = 0; r < R1; ++r) {
             float kr = 0.f;
-            if (r < HALF && act) kr = k[(long)h * L + j + r * (N / R1)];
+            if (r < HALF && act) kr = kh[j + r * (N / R1)];
             kf[q * R1 + r] = make_float2(kr, 0.f);
         }
     }
@@ -244,63 +245,65 @@ __global__ __launch_bounds__(N / 16 >= 64 ? N / 16 : 64) void fftconv_kgen_kerne
     }
 
     for (int i = 0; i < ppg; ++i) {
-        // an opaque copy of the thread index per pair: the passes' twiddles
-        // are evaluated where they are used instead of being hoisted out of
-        // the loop (where they would all stay live)
+        // an opaque copy of the thread index per pair: the passes' addresses
+        // and twiddle factors are formed where they are used instead of being
+        // hoisted out of the loop (where they would all stay live)
         int tv = tid;
         asm volatile("" : "+v"(tv));
         const int pr = grp * ppg + i;
         const bool va = act && pr < npairs, vb = va && 2 * pr + 1 < a.B;
+        if (S == 1 && !va) break;   // uniform over the block
         const long oa = ((long)(2 * pr) * a.H + h) * L, ob = oa + (long)a.H * L;
-        float2 v[16];
-        float ma = 0.f, mb = 0.f;
+        float xa[8], xb[8];
 #pragma unroll
-        for (int q = 0; q < Q; ++q) {
-            const int j = tid + q * T;
+        for (int e = 0; e < 8; ++e) xa[e] = xb[e] = 0.f;
+        if (va) {
+            const T_ *ra = (const T_ *)a.u + oa;
 #pragma unroll
-            for (int r = 0; r < R1; ++r) {
-                float xa = 0.f, xb = 0.f;
-                if (r < HALF) {
-                    const int n = j + r * (N / R1);
-                    if (va) xa = io::ld(u, oa + n);
-                    if (vb) xb = io::ld(u, ob + n);
-                }
-                ma = fmaxf(ma, fabsf(xa));
-                mb = fmaxf(mb, fabsf(xb));
-                v[q * R1 + r] = make_float2(xa, xb);
-            }
+            for (int e = 0; e < 8; ++e) xa[e] = io::ld(ra, tid + (e / HALF) * T + (e % HALF) * (N / R1));
+        }
+        if (vb) {
+            const T_ *rb = (const T_ *)a.u + ob;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) xb[e] = io::ld(rb, tid + (e / HALF) * T + (e % HALF) * (N / R1));
         }
         // each row of the pair gets its own power-of-two scale
-        __syncthreads();   // LDS: the previous transform's reads and the previous rmx reads are done
-        if (tid == 0) {
-            rmx[2 * sig] = 0u;
-            rmx[2 * sig + 1] = 0u;
+        float ma = 0.f, mb = 0.f;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            ma = fmaxf(ma, fabsf(xa[e]));
+            mb = fmaxf(mb, fabsf(xb[e]));
         }
-        __syncthreads();
-        atomicMax(&rmx[2 * sig], __float_as_uint(ma));
-        atomicMax(&rmx[2 * sig + 1], __float_as_uint(mb));
-        __syncthreads();
-        const int ea = pow2_exp(__uint_as_float(rmx[2 * sig])), eb = pow2_exp(__uint_as_float(rmx[2 * sig + 1]));
+        uint32_t mab = __float_as_uint(ma), mbb = __float_as_uint(mb);
+        signal_max<T>(red, tid, mab, mbb);   // its barrier: the previous pair's LDS reads are done
+        const int ea = pow2_exp(__uint_as_float(mab)), eb = pow2_exp(__uint_as_float(mbb));
+        float2 v[16];
         {
             const float sa = ldexpf(1.0f, -ea), sb = ldexpf(1.0f, -eb);
 #pragma unroll
-            for (int r = 0; r < 16; ++r) v[r] = make_float2(v[r].x * sa, v[r].y * sb);
+            for (int q = 0; q < Q; ++q)
+#pragma unroll
+                for (int r = 0; r < R1; ++r)
+                    v[q * R1 + r] = r < HALF ? make_float2(xa[q * HALF + r] * sa, xb[q * HALF + r] * sb)
+                                             : make_float2(0.f, 0.f);
         }
         fft_forward_from_regs<N>(X, tv, v);
 #pragma unroll
         for (int r = 0; r < 16; ++r) v[r] = cconj(cmul(v[r], kf[r]));
         fft_second_from_regs<N>(X, tv, v);
-        const float ya_s = ldexpf(1.0f, ea), yb_s = -ldexpf(1.0f, eb);
+        if (va) {
+            const float s = ldexpf(1.0f, ea);
+            T_ *ya = (T_ *)a.y + oa;
 #pragma unroll
-        for (int q = 0; q < Q; ++q) {
-            const int j = tid + q * T;
+            for (int e = 0; e < 8; ++e)
+                io::st(ya, tid + (e / HALF) * T + (e % HALF) * (N / R1), v[e / HALF * R1 + e % HALF].x * s);
+        }
+        if (vb) {
+            const float s = -ldexpf(1.0f, eb);
+            T_ *yb = (T_ *)a.y + ob;
 #pragma unroll
-            for (int r = 0; r < HALF; ++r) {
-                const int n = j + r * (N / R1);
-                const float2 w = v[q * R1 + r];
-                if (va) io::st(y, oa + n, w.x * ya_s);
-                if (vb) io::st(y, ob + n, w.y * yb_s);
-            }
+            for (int e = 0; e < 8; ++e)
+                io::st(yb, tid + (e / HALF) * T + (e % HALF) * (N / R1), v[e / HALF * R1 + e % HALF].y * s);
         }
     }
 }
