@@ -300,7 +300,7 @@ int h3_fftconv(const void *u, const float *k, const float *D, void *y, int B, in
     a.u = u; a.y = y; a.D = D;
     a.B = B; a.H = H; a.L = L; a.nchunk = 1; a.pair_mode = 0; a.dtype = dtype;
     if (fftconv_mfma_supported(L, dtype)) return launched(launch_fftconv_mfma(a, k, s));
-    if (conv_direct_supported(B, H, L, dtype)) return launched(launch_conv_direct(a, k, s));
+    if (conv_direct_supported(L, dtype)) return launched(launch_conv_direct(a, k, s));
     if (fftconv_kgen_supported(L)) return launched(launch_fftconv_kgen(a, k, s));
     float2 *Kspec = (float2 *)workspace;
     hipError_t e = launch_spectrum(k, H, L, Kspec, s);
@@ -344,7 +344,7 @@ int h3_fftconv_bwd(const void *u, const float *k, const float *D, const void *dy
         a.conj_k = 1;
         if (fftconv_mfma_supported(L, dtype)) {   // the wave kernels (2048, 8192) or the 32768-point one
             e = launch_fftconv_mfma(a, k, s);
-        } else if (conv_direct_supported(B, H, L, dtype)) {
+        } else if (conv_direct_supported(L, dtype)) {
             e = launch_conv_direct(a, k, s);
         } else if (fftconv_kgen_supported(L)) {
             e = launch_fftconv_kgen(a, k, s);
@@ -517,7 +517,7 @@ int h3_layer_fwd_heads(const void *x, const void *Wq, const void *Wk, const void
     ca.B = B; ca.H = d * d_head; ca.L = L; ca.nchunk = 1; ca.pair_mode = 0; ca.dtype = dtype;
     if (fftconv_mfma_supported(L, dtype)) {
         e = launch_fftconv_mfma(ca, diag_k, s);
-    } else if (conv_direct_supported(B, d * d_head, L, dtype)) {
+    } else if (conv_direct_supported(L, dtype)) {
         e = launch_conv_direct(ca, diag_k, s);
     } else {
         if ((e = launch_spectrum(diag_k, d * d_head, L, Kspec, s)) != hipSuccess) return H3_EDEVICE;

@@ -1,6 +1,6 @@
 // Fused convolution of 16-bit rows by direct summation on the matrix cores
-// (L = 256, 512, 1024 and 4096; L = 2048 and 8192 up have their own
-// transforms, shorter rows and float32 the VALU transform):
+// (L = 256, 512 and 1024; L = 2048 and 8192 up have their own transforms, other
+// lengths and float32 the VALU transform):
 //     y[t] = sum_{s <= t} k[t-s] u[s] + D u[t],
 // or, for the input gradient, the correlation sum_{s >= t} k[s-t] u[s] + D u[t].
 //
@@ -22,16 +22,15 @@
 // Split of the work: one wave per R rows of a channel, all waves of a
 // workgroup on one channel, whose kernel pieces they share in LDS (read as
 // five dwords and shifted by half a dword where a lane's taps start at an odd
-// element).  R = 2 up to L = 1024 reads each kernel tile once for two rows
-// (B = 8, H = 768, L = 1024: R = 1 / 2 / 4: 29 / 27 / 30 us with the kernel
-// generation); at 4096 one row's 16 accumulator tiles and four kernel tiles
-// at a time (hi and lo) let three waves share a SIMD (134 us at B = 5, H =
-// 767; eight tiles and two waves: 144).  Bound by the matrix cores, L^2 (1 +
-// 256 / L) multiply-adds per row, and by the LDS reads up to 1024.
+// element).  R = 2 reads each kernel tile once for two rows (B = 8, H = 768, L =
+// 1024: R = 1 / 2 / 4: 29 / 27 / 30 us with the kernel generation).  Bound by
+// the matrix cores, L^2 (1 + 256 / L) multiply-adds per row, and by the LDS
+// reads.  The work grows with L^2: at L = 4096 one row per wave took 134 us at B
+// = 5, H = 767, where the transform takes 87.
 //
-// Measured, with the kernel generation (us; the float32 transform before): B =
-// 16, H = 1024, L = 512, bf16: 66 -> 23; B = 8, H = 768, L = 1024, fp16: 42 ->
-// 24; B = 5, H = 767, L = 4096, bf16: 158 -> 134.
+// Measured, with the kernel generation, against the float32 transform (us): B =
+// 8, H = 768, L = 1024, fp16: 31 -> 24; B = 2, H = 1500, L = 1024, bf16: 26 -> 25;
+// forward and backward at B = 8, H = 768, L = 1024, bf16: 63 -> 48.
 #include "direct_conv.h"
 #include "internal.h"
 
@@ -52,7 +51,7 @@ struct CdPlan {
 // Workgroup: one channel, `blockDim.x / 64` waves of R rows each.  CONJ: the
 // correlation y[t] = sum_{s>=t} k[s-t] u[s] (+ D u[t]) instead.
 template <int DT, int NB, int R, bool CONJ>
-__global__ __launch_bounds__(64 * CD_MAXW, NB == 16 ? 3 : 4) void conv_direct_kernel(const uint16_t *u, const float *k, const float *D,
+__global__ __launch_bounds__(64 * CD_MAXW, 4) void conv_direct_kernel(const uint16_t *u, const float *k, const float *D,
                                                                      uint16_t *y, int B, int H, int wg_per_ch) {
     using P = CdPlan<NB>;
     constexpr int L = P::L;
@@ -116,36 +115,32 @@ __global__ __launch_bounds__(64 * CD_MAXW, NB == 16 ? 3 : 4) void conv_direct_ke
     const uint32_t *kh32 = (const uint32_t *)kh + (e0 >> 1), *kl32 = (const uint32_t *)kl + (e0 >> 1);
     // B: inputs 256 a - rho - 16 + 16 n + kk (correlation: 256 a + rho + 16 n + kk)
     const uint16_t *ub = us + (CONJ ? 0 : 224) + 16 * i16 + 8 * g;
-    constexpr int DB = NB < 4 ? NB : 4;   // kernel tiles held at once (hi and lo)
 #pragma unroll 1
     for (int rho = 0; rho < 256; rho += 32) {
+        uint4 Ah[NB], Al[NB];
 #pragma unroll
-        for (int d0 = 0; d0 < NB; d0 += DB) {
-            uint4 Ah[DB], Al[DB];
-#pragma unroll
-            for (int d = 0; d < DB; ++d) {
-                const int o = (CONJ ? rho : -rho) / 2 + (CONJ ? 128 : -128) * (d0 + d);
-                Ah[d] = cd_frag(kh32 + o, sh);
-                Al[d] = cd_frag(kl32 + o, sh);
-            }
-#pragma unroll
-            for (int a = CONJ ? d0 : 0; a < (CONJ ? NB : NB - d0); ++a)
-#pragma unroll
-                for (int r = 0; r < R; ++r) {
-                    if (r > 0 && r >= nr) continue;
-                    const uint4 Bv = *(const uint4 *)(ub + r * P::US + 256 * a + (CONJ ? rho : -rho));
-#pragma unroll
-                    for (int d = 0; d < DB; ++d) {
-                        const int b = CONJ ? a - d0 - d : a + d0 + d;
-                        if (b >= 0 && b < NB) acc[r][b] = cd_mfma<DT>(Ah[d], Bv, acc[r][b]);
-                    }
-#pragma unroll
-                    for (int d = 0; d < DB; ++d) {
-                        const int b = CONJ ? a - d0 - d : a + d0 + d;
-                        if (b >= 0 && b < NB) acc[r][b] = cd_mfma<DT>(Al[d], Bv, acc[r][b]);
-                    }
-                }
+        for (int d = 0; d < NB; ++d) {
+            const int o = (CONJ ? rho : -rho) / 2 + (CONJ ? 128 : -128) * d;
+            Ah[d] = cd_frag(kh32 + o, sh);
+            Al[d] = cd_frag(kl32 + o, sh);
         }
+#pragma unroll
+        for (int a = 0; a < NB; ++a)
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                if (r > 0 && r >= nr) continue;
+                const uint4 Bv = *(const uint4 *)(ub + r * P::US + 256 * a + (CONJ ? rho : -rho));
+#pragma unroll
+                for (int d = 0; d < NB; ++d) {
+                    const int b = CONJ ? a - d : a + d;
+                    if (b >= 0 && b < NB) acc[r][b] = cd_mfma<DT>(Ah[d], Bv, acc[r][b]);
+                }
+#pragma unroll
+                for (int d = 0; d < NB; ++d) {
+                    const int b = CONJ ? a - d : a + d;
+                    if (b >= 0 && b < NB) acc[r][b] = cd_mfma<DT>(Al[d], Bv, acc[r][b]);
+                }
+            }
     }
     const float s = ldexpf(1.f, ek);
 #pragma unroll
@@ -180,24 +175,18 @@ hipError_t launch_direct_nb(const ConvArgs &a, const float *k, hipStream_t s) {
         case 256: return a.B >= 2 ? launch_direct<DT, 1, 2, CONJ>(a, k, s) : launch_direct<DT, 1, 1, CONJ>(a, k, s);
         case 512: return a.B >= 2 ? launch_direct<DT, 2, 2, CONJ>(a, k, s) : launch_direct<DT, 2, 1, CONJ>(a, k, s);
         case 1024: return a.B >= 2 ? launch_direct<DT, 4, 2, CONJ>(a, k, s) : launch_direct<DT, 4, 1, CONJ>(a, k, s);
-        case 4096: return launch_direct<DT, 16, 1, CONJ>(a, k, s);
     }
     return hipErrorInvalidValue;
 }
 
 }  // namespace
 
-// At L = 4096 a wave takes some 40 us for its row, and a launch that leaves the
-// chip part empty is no faster: from 1280 rows on (us, direct / transform, with
-// the kernel generation: B = 16, H = 64: 65 / 44; B = 1, H = 64: 47 / 24; B = 1,
-// H = 1482: 97 / 131; B = 2, H = 768: 68 / 83; B = 8, H = 250: 69 / 74).
-bool conv_direct_supported(int B, int H, int L, int dtype) {
-    if (dtype != F16 && dtype != BF16) return false;
-    return L == 256 || L == 512 || L == 1024 || (L == 4096 && (long)B * H >= 1280);
+bool conv_direct_supported(int L, int dtype) {
+    return (dtype == F16 || dtype == BF16) && (L == 256 || L == 512 || L == 1024);
 }
 
 hipError_t launch_conv_direct(const ConvArgs &a, const float *k, hipStream_t s) {
-    if (!conv_direct_supported(a.B, a.H, a.L, a.dtype) || a.pair_mode != 0 || a.corr || a.gate) return hipErrorInvalidValue;
+    if (!conv_direct_supported(a.L, a.dtype) || a.pair_mode != 0 || a.corr || a.gate) return hipErrorInvalidValue;
     if (a.dtype == F16) return a.conj_k ? launch_direct_nb<F16, true>(a, k, s) : launch_direct_nb<F16, false>(a, k, s);
     return a.conj_k ? launch_direct_nb<BF16, true>(a, k, s) : launch_direct_nb<BF16, false>(a, k, s);
 }

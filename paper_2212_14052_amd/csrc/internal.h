@@ -55,8 +55,8 @@ hipError_t launch_fftconv(const ConvArgs &a, hipStream_t s);
 bool fftconv_kgen_supported(int L);
 hipError_t launch_fftconv_kgen(const ConvArgs &a, const float *k, hipStream_t s);
 // The same for 16-bit rows by direct summation on the matrix cores, L 256,
-// 512, 1024 or 4096 (there with rows enough to fill the chip).
-bool conv_direct_supported(int B, int H, int L, int dtype);
+// 512 or 1024.
+bool conv_direct_supported(int L, int dtype);
 hipError_t launch_conv_direct(const ConvArgs &a, const float *k, hipStream_t s);
 // The eight-wave register-resident convolution at L = 16384 (16-bit I/O).
 bool fftconv_wave32k_supported(int L, int dtype);

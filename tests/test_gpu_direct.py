@@ -1,8 +1,8 @@
-"""The direct convolution of 16-bit rows (L = 256, 512, 1024, 4096), forward
-and as the input gradient, against the float64 oracle: batches that leave a
-wave's rows or a workgroup's waves unfilled, channel counts that split a
-channel over workgroups, row counts on both sides of the rule at 4096, kernels
-and inputs far from 1."""
+"""The convolution of 16-bit rows by direct summation (L = 256, 512, 1024) and
+by the float32 transform at 4096, forward and as the input gradient, against
+the float64 oracle: batches that leave a wave's rows or a workgroup's waves
+unfilled, channel counts that split a channel over workgroups, few and many
+rows per kernel spectrum at 4096, kernels and inputs far from 1."""
 import numpy as np
 import pytest
 import torch
