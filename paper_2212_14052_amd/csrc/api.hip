@@ -508,13 +508,20 @@ int h3_layer_fwd_heads(const void *x, const void *Wq, const void *Wk, const void
     // Kbar = shift SSM of K (no gating); G = per-head outer products of Kbar and V
     if ((e = launch_shift_gate(kk, nullptr, shift_C, shift_D, m_s, B, d, L, dtype, kbar, s)) != hipSuccess)
         return H3_EDEVICE;
-    if ((e = launch_heads_expand(d_head, kbar, v, g, B, d, L, dtype, s)) != hipSuccess) return H3_EDEVICE;
+    // (formed in the convolution's own loads where its kernel has them so)
+    const bool fused = L == 2048 || conv_direct_supported(L, dtype);
+    if (!fused && (e = launch_heads_expand(d_head, kbar, v, g, B, d, L, dtype, s)) != hipSuccess) return H3_EDEVICE;
     // S = diagonal SSM of every (h, i, j) row: the fused convolution over d d_h
-    // channels, in place (a wave or workgroup holds its rows whole before it
-    // writes them; a second buffer cost 20 us of 840 at d = 2560, d_h = 8)
+    // channels, from a built G in place (a wave or workgroup holds its rows
+    // whole before it writes them)
     ConvArgs ca{};
     ca.u = g; ca.y = g; ca.D = diag_D;
     ca.B = B; ca.H = d * d_head; ca.L = L; ca.nchunk = 1; ca.pair_mode = 0; ca.dtype = dtype;
+    if (fused) {
+        ca.u = kbar;
+        ca.heads_v = v;
+        ca.heads_log2 = d_head == 2 ? 1 : d_head == 4 ? 2 : 3;
+    }
     if (fftconv_mfma_supported(L, dtype)) {
         e = launch_fftconv_mfma(ca, diag_k, s);
     } else if (conv_direct_supported(L, dtype)) {

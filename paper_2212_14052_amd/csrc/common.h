@@ -76,6 +76,18 @@ __device__ __forceinline__ int xcd_logical_block(int b, int nblocks) {
     return (b % NXCD) * (nblocks / NXCD) + b / NXCD;
 }
 
+// Products of two 16-bit pairs, rounded once.
+template <int DT> __device__ __forceinline__ uint32_t mul_16x2(uint32_t x, uint32_t z) {
+    if constexpr (DT == F16) {
+        typedef _Float16 h2 __attribute__((ext_vector_type(2)));
+        return __builtin_bit_cast(uint32_t, __builtin_bit_cast(h2, x) * __builtin_bit_cast(h2, z));
+    } else {
+        typedef float f2 __attribute__((ext_vector_type(2)));
+        typedef __bf16 b2 __attribute__((ext_vector_type(2)));
+        const f2 p = {bf16_to_f32(x & 0xffffu) * bf16_to_f32(z & 0xffffu), bf16_to_f32(x >> 16) * bf16_to_f32(z >> 16)};
+        return __builtin_bit_cast(uint32_t, __builtin_convertvector(p, b2));
+    }
+}
 // exp(tau * lambda) for complex lambda given in float64, returned in float32:
 // the phase tau*Im(lambda) is reduced modulo 2 pi in float64 before the
 // float32 sine/cosine, so large arguments keep full accuracy.

@@ -49,17 +49,24 @@ struct CdPlan {
 };
 
 // Workgroup: one channel, `blockDim.x / 64` waves of R rows each.  CONJ: the
-// correlation y[t] = sum_{s>=t} k[s-t] u[s] (+ D u[t]) instead.
-template <int DT, int NB, int R, bool CONJ>
+// correlation y[t] = sum_{s>=t} k[s-t] u[s] (+ D u[t]) instead.  HEADS: the rows
+// are the outer products u_i v_j of the layer with heads of 2^lg channels,
+// formed on the way into LDS instead of by a kernel of their own through
+// memory (the whole layer at L = 1024, us: B = 4, d = 1280, d_h = 8, bf16: 212 ->
+// 197; B = 6, d = 1280, d_h = 8, fp16: 302 -> 277; B = 1, d = 256, d_h = 2: 41 -> 39).
+template <int DT, int NB, int R, bool CONJ, bool HEADS>
 __global__ __launch_bounds__(64 * CD_MAXW, 4) void conv_direct_kernel(const uint16_t *u, const float *k, const float *D,
-                                                                     uint16_t *y, int B, int H, int wg_per_ch) {
+                                                                     uint16_t *y, int B, int H, int wg_per_ch,
+                                                                     const uint16_t *v, int lg) {
     using P = CdPlan<NB>;
     constexpr int L = P::L;
     extern __shared__ __attribute__((aligned(16))) uint16_t cd_sm[];
     __shared__ float red[CD_MAXW];
     const int tid = threadIdx.x, lane = tid & 63, nt = blockDim.x, nw = nt >> 6;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int h = blockIdx.x / wg_per_ch, part = blockIdx.x % wg_per_ch;
+    // HEADS: a head's channels on one XCD, whose L2 then serves their shared rows
+    const int blk = HEADS ? xcd_logical_block(blockIdx.x, gridDim.x) : blockIdx.x;
+    const int h = blk / wg_per_ch, part = blk % wg_per_ch;
     const int i16 = lane & 15, g = lane >> 4;
     const int b0 = (part * nw + w) * R, nr = min(R, B - b0);   // may be <= 0
     uint16_t *kh = cd_sm, *kl = cd_sm + P::KS;
@@ -67,13 +74,18 @@ __global__ __launch_bounds__(64 * CD_MAXW, 4) void conv_direct_kernel(const uint
 
     // the wave's rows into LDS, zeros in front (behind, for the correlation)
     constexpr int PIECES = L / 8, PT = (PIECES + 63) / 64;
-    cd_u4 raw[R][PT];
+    cd_u4 raw[R][PT], rav[HEADS ? R : 1][PT];
+    const int ku = HEADS ? h >> lg : h, kv = ((h >> (2 * lg)) << lg) + (h & ((1 << lg) - 1)), Hu = HEADS ? H >> lg : H;
 #pragma unroll
     for (int r = 0; r < R; ++r)
 #pragma unroll
-        for (int p = 0; p < PT; ++p)
+        for (int p = 0; p < PT; ++p) {
             // (rows and pieces past the end: the last one again, never used)
-            raw[r][p] = *(const cd_u4 *)(u + ((long)min(b0 + r, B - 1) * H + h) * L + 8 * min(64 * p + lane, PIECES - 1));
+            const long row = (long)min(b0 + r, B - 1) * Hu;
+            const int piece = 8 * min(64 * p + lane, PIECES - 1);
+            raw[r][p] = *(const cd_u4 *)(u + (row + ku) * L + piece);
+            if constexpr (HEADS) rav[r][p] = *(const cd_u4 *)(v + (row + kv) * L + piece);
+        }
 
     // the kernel as two 16-bit pieces hi + lo (fp16: times a power of two that
     // puts its largest value in [2^14, 2^15), so that lo stays normal),
@@ -97,7 +109,14 @@ __global__ __launch_bounds__(64 * CD_MAXW, 4) void conv_direct_kernel(const uint
     for (int r = 0; r < R; ++r) {
         uint16_t *ur = us + r * P::US;
 #pragma unroll
-        for (int p = 0; p < PT; ++p) *(cd_u4 *)(ur + (CONJ ? 0 : 240) + 8 * min(64 * p + lane, PIECES - 1)) = raw[r][p];
+        for (int p = 0; p < PT; ++p) {
+            cd_u4 x = raw[r][p];
+            if constexpr (HEADS) {
+                const cd_u4 z = rav[r][p];
+                x = cd_u4{mul_16x2<DT>(x[0], z[0]), mul_16x2<DT>(x[1], z[1]), mul_16x2<DT>(x[2], z[2]), mul_16x2<DT>(x[3], z[3])};
+            }
+            *(cd_u4 *)(ur + (CONJ ? 0 : 240) + 8 * min(64 * p + lane, PIECES - 1)) = x;
+        }
         if (lane < 30) *(uint4 *)(ur + (CONJ ? L : 0) + 8 * lane) = make_uint4(0, 0, 0, 0);
     }
     __syncthreads();
@@ -154,19 +173,26 @@ __global__ __launch_bounds__(64 * CD_MAXW, 4) void conv_direct_kernel(const uint
         }
 }
 
-template <int DT, int NB, int R, bool CONJ>
-hipError_t launch_direct(const ConvArgs &a, const float *k, hipStream_t s) {
+template <int DT, int NB, int R, bool CONJ, bool HEADS>
+hipError_t launch_direct_h(const ConvArgs &a, const float *k, hipStream_t s) {
     using P = CdPlan<NB>;
     const int groups = (a.B + R - 1) / R;
     int wgc = (groups + CD_MAXW - 1) / CD_MAXW;
     while ((long)a.H * wgc < 512 && wgc * 2 <= groups) wgc *= 2;
     const int nw = (groups + wgc - 1) / wgc;
     const size_t lds = P::lds(nw, R);
-    auto fn = conv_direct_kernel<DT, NB, R, CONJ>;
+    auto fn = conv_direct_kernel<DT, NB, R, CONJ, HEADS>;
     if (lds > 60000) (void)hipFuncSetAttribute((const void *)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     hipLaunchKernelGGL(fn, dim3((unsigned)(a.H * wgc)), dim3(64 * nw), lds, s, (const uint16_t *)a.u, k, a.D,
-                       (uint16_t *)a.y, a.B, a.H, wgc);
+                       (uint16_t *)a.y, a.B, a.H, wgc, (const uint16_t *)a.heads_v, a.heads_log2);
     return hipGetLastError();
+}
+
+template <int DT, int NB, int R, bool CONJ>
+hipError_t launch_direct(const ConvArgs &a, const float *k, hipStream_t s) {
+    if constexpr (!CONJ)
+        if (a.heads_v) return launch_direct_h<DT, NB, R, false, true>(a, k, s);
+    return launch_direct_h<DT, NB, R, CONJ, false>(a, k, s);
 }
 
 template <int DT, bool CONJ>
@@ -186,7 +212,7 @@ bool conv_direct_supported(int L, int dtype) {
 }
 
 hipError_t launch_conv_direct(const ConvArgs &a, const float *k, hipStream_t s) {
-    if (!conv_direct_supported(a.L, a.dtype) || a.pair_mode != 0 || a.corr || a.gate) return hipErrorInvalidValue;
+    if (!conv_direct_supported(a.L, a.dtype) || a.pair_mode != 0 || a.corr || a.gate || (a.heads_v && a.conj_k)) return hipErrorInvalidValue;
     if (a.dtype == F16) return a.conj_k ? launch_direct_nb<F16, true>(a, k, s) : launch_direct_nb<F16, false>(a, k, s);
     return a.conj_k ? launch_direct_nb<BF16, true>(a, k, s) : launch_direct_nb<BF16, false>(a, k, s);
 }

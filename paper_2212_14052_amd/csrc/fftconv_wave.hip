@@ -183,6 +183,24 @@ __device__ __forceinline__ void out_layer(uint32_t (&d)[64], const h8_t &Fc, flo
     }
 }
 
+// Lanes l < 32 hold points of the Kbar row, lanes l + 32 the same points of the
+// V row: their products in the lanes l < 32, zeros in the others.  A swap of
+// the halves puts two dwords' factors side by side in both halves, a second
+// one takes the products back, so no lane idles.
+template <int DT> __device__ __forceinline__ void heads_product(uint4 (&r)[8]) {
+    auto two = [](uint32_t &x, uint32_t &z) {
+        const auto f = __builtin_amdgcn_permlane32_swap(x, z, false, false);
+        const auto p = __builtin_amdgcn_permlane32_swap(mul_16x2<DT>(f[0], f[1]), 0u, false, false);
+        x = p[0];
+        z = p[1];
+    };
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        two(r[i].x, r[i].y);
+        two(r[i].z, r[i].w);
+    }
+}
+
 }  // namespace wv
 
 // ============================================================================
@@ -192,7 +210,12 @@ __device__ __forceinline__ void out_layer(uint32_t (&d)[64], const h8_t &Fc, flo
 // take the first channel's pairs and waves 2, 3 the second's, so no wave
 // idles while its workgroup holds the CU's LDS.
 // GATE: the output is multiplied by a.gate (same layout as y) before rounding.
-template <int DT, int CPW, bool CT = false, bool GATE = false>
+// HEADS: the rows are the outer products Kbar_i V_j of the layer with heads,
+// formed in the loads' registers (the halves of the wave that hold no points
+// take the V rows) instead of by a kernel of their own through memory.  The whole
+// layer, us: B = 4, d = 2560, d_h = 8, bf16: 824 -> 785; B = 2, d = 1536, d_h = 4,
+// bf16: 222 -> 217; B = 6, d = 512, d_h = 4, fp16: 131 -> 121.
+template <int DT, int CPW, bool CT = false, bool GATE = false, bool HEADS = false>
 __global__ __launch_bounds__(wv::NT) __attribute__((amdgpu_waves_per_eu(CPW == 1 || CT ? 3 : 2))) void
 fftconv_wave4096_kernel(ConvArgs a, const float *k, int wg_per_ch, int pairs_per_ch) {
     using namespace wv;
@@ -207,7 +230,9 @@ fftconv_wave4096_kernel(ConvArgs a, const float *k, int wg_per_ch, int pairs_per
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform
     const int g = lane >> 4, c = lane & 15;
-    const int hb = blockIdx.x / wg_per_ch, part = blockIdx.x % wg_per_ch;
+    // HEADS: a head's channels on one XCD, whose L2 then serves their shared rows
+    const int blk = HEADS ? xcd_logical_block(blockIdx.x, gridDim.x) : blockIdx.x;
+    const int hb = blk / wg_per_ch, part = blk % wg_per_ch;
     const int chw = CPW == 1 ? 0 : (w >> 1);   // this wave's channel within the workgroup
     const int h = hb * CPW + chw;              // this wave's channel
     const int wl = CPW == 1 ? w : (w & 1);     // this wave's index among its channel's waves
@@ -234,7 +259,21 @@ fftconv_wave4096_kernel(ConvArgs a, const float *k, int wg_per_ch, int pairs_per
             ra[i] = make_uint4(0, 0, 0, 0);
             rb[i] = make_uint4(0, 0, 0, 0);
         }
-        if (g < 2) {
+        if constexpr (HEADS) {
+            // lanes g < 2 the Kbar rows, lanes g >= 2 the V rows, same points
+            const int lg = a.heads_log2, di = a.H >> lg;
+            const int kr = h >> lg, vr = ((h >> (2 * lg)) << lg) + (h & ((1 << lg) - 1));
+            const uint16_t *p = g < 2 ? u + (long)kr * L : (const uint16_t *)a.heads_v + (long)vr * L;
+            const uint16_t *ua = p + (long)(2 * qq) * di * L + 1024 * (g & 1) + 16 * c;
+            const uint16_t *ub = ob >= 0 ? ua + (long)di * L : ua;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                ra[2 * j] = *(const uint4 *)(ua + 256 * j);
+                ra[2 * j + 1] = *(const uint4 *)(ua + 256 * j + 8);
+                rb[2 * j] = *(const uint4 *)(ub + 256 * j);
+                rb[2 * j + 1] = *(const uint4 *)(ub + 256 * j + 8);
+            }
+        } else if (g < 2) {
             const uint16_t *ua = u + oa, *ub = u + obl;   // wave-uniform bases
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
@@ -377,6 +416,10 @@ fftconv_wave4096_kernel(ConvArgs a, const float *k, int wg_per_ch, int pairs_per
     // One flag guards both the prefetch and the back edge, so the staged
     // registers are dead between their unpacking and the next prefetch.
     while (have) {
+        if constexpr (HEADS) {
+            heads_product<DT>(ra);
+            heads_product<DT>(rb);
+        }
         // max |u| per row, then packing into (a + i b) complex fp16: p2 =
         // 4 g + j : G, p1 = c : C, p0 = T : tile
         float mxa, mxb;
@@ -565,6 +608,13 @@ hipError_t launch_fftconv_wave(const ConvArgs &a, const float *k, hipStream_t s)
         // -> 20 us at H = 768)
         const dim3 grid2((a.H + 1) / 2);
         const bool ct = grid2.x >= 512;
+        if (a.heads_v) {   // (the compact table's at every size: one instance less)
+            if (a.dtype == F16)
+                hipLaunchKernelGGL((fftconv_wave4096_kernel<F16, 2, true, false, true>), grid2, block, 0, s, a, k, 1, pairs_per_ch);
+            else
+                hipLaunchKernelGGL((fftconv_wave4096_kernel<BF16, 2, true, false, true>), grid2, block, 0, s, a, k, 1, pairs_per_ch);
+            return hipGetLastError();
+        }
 #define H3_WAVE2_LAUNCH(DTV, CTV, GV) \
     hipLaunchKernelGGL((fftconv_wave4096_kernel<DTV, 2, CTV, GV>), grid2, block, 0, s, a, k, 1, pairs_per_ch)
 #define H3_WAVE2_CT(DTV, GV) \
@@ -581,6 +631,13 @@ hipError_t launch_fftconv_wave(const ConvArgs &a, const float *k, hipStream_t s)
         }
 #undef H3_WAVE2_CT
 #undef H3_WAVE2_LAUNCH
+        return hipGetLastError();
+    }
+    if (a.heads_v) {
+        if (a.dtype == F16)
+            hipLaunchKernelGGL((fftconv_wave4096_kernel<F16, 1, false, false, true>), grid, block, 0, s, a, k, wg_per_ch, pairs_per_ch);
+        else
+            hipLaunchKernelGGL((fftconv_wave4096_kernel<BF16, 1, false, false, true>), grid, block, 0, s, a, k, wg_per_ch, pairs_per_ch);
         return hipGetLastError();
     }
 #define H3_WAVE_LAUNCH(DTV, GV) \

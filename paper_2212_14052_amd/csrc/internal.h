@@ -47,6 +47,11 @@ struct ConvArgs {
     // convolution + D u), elementwise, gate in the I/O dtype and layout of y
     // (the output gating of the H3 layer, O = Q * S)
     const void *gate;
+    // heads_v (L = 2048 wave kernel without gate, and the direct kernel; may be null): the rows
+    // are the outer products u_i heads_v_j of the layer with heads of 2^heads_log2
+    // channels, u and heads_v (B, H >> heads_log2, L), channel (h d_h + i) d_h + j
+    const void *heads_v;
+    int heads_log2;
 };
 hipError_t launch_fftconv(const ConvArgs &a, hipStream_t s);
 // The VALU convolution of plain (B, H, L) rows (pair_mode 0, no correction

@@ -4,7 +4,8 @@
 // kernel per entry (h, i, j)), and the head's output is  O_t[j] =
 // sum_i Q_t[i] S_t[i][j].  The outer products are d_h^2 sequence rows per head,
 // channel (h d_h + i) d_h + j, convolved by the fused FFT convolution like any
-// other rows; the two kernels here build them and contract them with Q.
+// other rows; the two kernels here build them (at the lengths whose convolution
+// does not form them in its own loads) and contract them with Q.
 #include "common.h"
 #include "internal.h"
 
