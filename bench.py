@@ -44,7 +44,7 @@ MFMA_BF16_PEAK_TFLOPS = 2500.0
 # this script (each counter set in a run of its own):
 #   fetch_kib, write_kib: FETCH_SIZE and WRITE_SIZE (KiB per dispatch),
 #     calibrated against a 512 MiB device copy (--copy-probe), which reads
-#     FETCH_SIZE = 262156.7 KiB and writes WRITE_SIZE = 524288 KiB: bytes =
+#     FETCH_SIZE = 262156.8 KiB and writes WRITE_SIZE = 524288 KiB: bytes =
 #     KiB x 1024 x 2.0 (fetch) and x 1.0 (write);
 #   valu, mfma: SQ_INSTS_VALU, SQ_INSTS_MFMA (wave instructions per dispatch);
 #   mfma_busy: SQ_VALU_MFMA_BUSY_CYCLES / (1024 SIMDs x SQ_BUSY_CYCLES / 32).
@@ -54,11 +54,11 @@ MFMA_BF16_PEAK_TFLOPS = 2500.0
 FETCH_FACTOR, WRITE_FACTOR = 2.0, 1.0
 COUNTERS = {
     "headline": {"src": ("paper_2212_14052_amd/csrc/fftconv_wave.hip", "paper_2212_14052_amd/csrc/wave_common.h"),
-                 "sha": "b4c45271e860df90", "fetch_kib": 15636.2, "write_kib": 24576.0,
-                 "valu": 6062592, "mfma": 614400, "mfma_busy": 0.194},
+                 "sha": "0add9cc847a08b63", "fetch_kib": 15626.5, "write_kib": 24576.0,
+                 "valu": 6038016, "mfma": 614400, "mfma_busy": 0.200},
     "cfg0_scaled": {"src": ("paper_2212_14052_amd/csrc/fftconv.hip", "paper_2212_14052_amd/csrc/fft_valu.h"),
-                    "sha": "a55c178cb10dd628", "fetch_kib": 73914.3, "write_kib": 131072.0,
-                    "valu": 84164608, "mfma": 0},
+                    "sha": "05694e8b4ccecec9", "fetch_kib": 73925.3, "write_kib": 131072.0,
+                    "valu": 54972416, "mfma": 0},
 }
 SIMDS, CLOCK_GHZ = 1024, 2.4
 

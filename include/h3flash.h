@@ -132,8 +132,9 @@ int h3_fftconv_spectral(const void *u, const float *Kspec, const float *D, void 
  *   x_final     (B, H, m) complex written, or NULL.
  *   chunk       power of two in [H3_MIN_LEN, H3_FUSED_LIMIT] dividing L.
  *   workspace >= h3_workspace_size(H3_OP_STATEPASS, B, H, L, m, chunk, dtype)
- *   (the chunk kernel, the chunk end-states and the initial-state term's
- *   inputs; its contents on entry do not matter).
+ *   (the chunk kernel, the chunk end-states and the initial-state term, or
+ *   the end states of the segments that few rows are cut into; its contents
+ *   on entry do not matter).
  * Errors: EINVAL (null, sizes, L % chunk), EUNSUPPORTED (chunk, m, dtype),
  *         EWORKSPACE, EDEVICE.
  */
@@ -225,10 +226,10 @@ int h3_ssm_step(const void *u, const float *Abar, const float *Bbar, const float
  *   B * L a multiple of 128 (the tiles of the library's own GEMM).
  *   workspace >= h3_workspace_size(H3_OP_LAYER, B, d, L, m_s, 0, dtype).
  * The four projections run on the library's own matrix-core GEMM: when d is
- * a multiple of 320 (or 256) and B * L of 256 it reads the weights as stored,
- * Q, K and V in one launch of 320 x 256 (256 x 256) tiles; other shapes take
- * one 128 x 128-tile launch per projection on transposed copies of the
- * weights made in the workspace.
+ * a multiple of 128 and B * L of 256 it reads the weights as stored, Q, K and V
+ * in one launch of tiles 320, 256 or 128 features wide; B * L not a multiple of
+ * 256 takes one 128 x 128-tile launch per projection on transposed copies of
+ * the weights made in the workspace.
  * Errors: EINVAL, EUNSUPPORTED (L, d, B * L, m_s, dtype), EWORKSPACE, EDEVICE.
  */
 int h3_layer_fwd(const void *x, const void *Wq, const void *Wk, const void *Wv,

@@ -184,7 +184,7 @@ int statepass_run(const void *u, const float *Abar, const float *Bbar, const flo
     const StatepassWs w = statepass_ws(B, H, L, m, chunk, dtype);
     // the result does not depend on the chunk: 16-bit rows at the chunks of the
     // matrix-core convolutions go through the sequence in one pass (B = 2, H =
-    // 1024, L = 131072, chunk 8192, fp16: 305 us, against 705 us for chunk
+    // 1024, L = 131072, chunk 8192, fp16: 277 us, against 708 us for chunk
     // end-states and a convolution of chunks)
     if (w.scan) return launched(launch_ssm_scan(u, Abar, Bbar, C, D, x0, B, H, L, m, dtype, y, x_final, ws, w.total, s));
     float *kbuf = (float *)(ws + w.k);

@@ -30,8 +30,8 @@
 //
 // Bound by the serial chain of each wave at two waves per SIMD (433 VALU and
 // 38 matrix instructions per 2048 inputs): B = 2, H = 1024, L = 131072, fp16:
-// 305 us = 3.5 TB/s (the same loop without the arithmetic: 257 us); chunk
-// states and convolution before: 705 us.
+// 277 us = 3.9 TB/s (305 us on a slower card, where the same loop without the
+// arithmetic took 257); chunk states and convolution before: 708 us.
 #include "common.h"
 #include "internal.h"
 
