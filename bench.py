@@ -120,7 +120,7 @@ def bench_headline(h3, steps, warmup, dev, nstreams=2):
     launching stream before the first, and after every stream has been joined
     back).  The arguments go through the Python binding's checks once; the
     timed loops then call the C entry points with prebuilt arguments, because
-    the binding's marshalling (about 12 us of host time per call) would
+    the binding's marshalling (about 9 us of host time per call) would
     otherwise pace a step whose GPU time is about 25 us."""
     import ctypes
     import torch
