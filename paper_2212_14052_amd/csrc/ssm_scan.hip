@@ -214,6 +214,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void s
     }
     const float2 th = TH[lane];
     const float gf = GF[lane];
+    const int egf = __builtin_amdgcn_readfirstlane(pow2_exp(sc_wave_max(gf)));   // of the largest
     float *xb = (float *)(sm + 16384 * NP + SC_XB * w);   // the wave's exchange buffer
     // M_xy: row R is output i = 32 rho + 16 (R / 16) + 8 (R / 4 % 2) + 4 (R / 8
     // % 2) + R % 4 (so that a lane ends up with runs of eight consecutive
@@ -389,7 +390,19 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void s
             // the states as fp16 (re, im) words, scaled by a common power of
             // two, through LDS: lane = mode to lane = block
             const int e = __builtin_amdgcn_readfirstlane(pow2_exp(sc_wave_max(mxv * gf))) - 10;
-            const float f = ldexpf(gf, -e);
+            float f = ldexpf(gf, -e);
+            if (egf - e > 127) {
+                // a state so small that f leaves float32 (an input of zeros lets
+                // it decay to nothing): scaled value by value
+#pragma unroll
+                for (int t = 0; t < 2; ++t)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) {
+                        sx[t][0][r] = ldexpf(sx[t][0][r] * gf, -e);
+                        sx[t][1][r] = ldexpf(sx[t][1][r] * gf, -e);
+                    }
+                f = 1.f;
+            }
 #pragma unroll
             for (int n = 0; n < 32; ++n) {
                 const int r = 4 * (n >> 3) + (n & 3), t = (n >> 2) & 1;

@@ -110,3 +110,22 @@ def test_scan_unusual_parameters(h3, dtype, case):
     for h in range(H):
         check(np.ascontiguousarray(y[:, h]), np.ascontiguousarray(y2[:, h]), 2 * TOL[dtype], f"y{h} chunk 512")
     check(xf, x2, 2 * TOL_X[dtype], "x_final chunk 512", rows=False)
+
+
+@pytest.mark.parametrize("dtype", [workloads.F16, workloads.BF16])
+@pytest.mark.parametrize("B,H,L", [(2, 6, 24 * 2048), (1, 1024, 16 * 2048)])   # one step per segment; one segment
+def test_scan_zero_tail(h3, dtype, B, H, L):
+    """A zero-padded sequence: the state decays through the smallest floats to
+    zero, over steps that hold nothing else."""
+    w = workloads.statepass_workload("t", B, H, L, 2048, dtype, seed=23, m=4, dt_lo=3e-3, dt_hi=1e-1)
+    w.u[..., 2048:] = 0
+    w.u64[..., 2048:] = 0
+    Ab, Bb, C = _params(w)
+    y, xf = _run(h3, w, Ab, Bb, C, w.D, None, 2048)
+    assert np.isfinite(y).all() and np.isfinite(xf).all()
+    sel = np.unique(np.r_[0, H // 3, H - 1])
+    ry, rx = oracle.recurrence(np.ascontiguousarray(w.u64[:, sel]), *(cplx64(a[sel]) for a in (Ab, Bb, C)),
+                               w.D[sel].astype(np.float64))
+    check(np.ascontiguousarray(y[:, sel]), ry, TOL[dtype], "y")
+    # (most final states lie below float32's range)
+    assert np.abs(xf[:, sel] - rx).max() <= TOL_X[dtype] * np.abs(rx).max() + 1e-37
