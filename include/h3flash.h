@@ -129,7 +129,7 @@ int h3_fftconv_spectral(const void *u, const float *Kspec, const float *D, void 
  *   u, y        (B, H, L) of `dtype`; must not overlap.
  *   Abar, Bbar, C (H, m) complex.  D (H) float32 (NULL: no skip term).
  *   x0          (B, H, m) complex, or NULL for the zero state.
- *   x_final     (B, H, m) complex written, or NULL.
+ *   x_final     (B, H, m) complex written, or NULL; may be the buffer of x0.
  *   chunk       power of two in [H3_MIN_LEN, H3_FUSED_LIMIT] dividing L.
  *   workspace >= h3_workspace_size(H3_OP_STATEPASS, B, H, L, m, chunk, dtype)
  *   (the chunk kernel, the chunk end-states and the initial-state term, or

@@ -125,7 +125,7 @@ struct ScanArgs {
     uint16_t *y;
     const float *Abar, *Bbar, *C, *D, *x0;
     float *x_final;
-    float2 *seg;          // (B, H, nseg, 64) end states of the segments, scaled
+    float2 *seg;          // (B, H, nseg, 64) scaled: end states of the segments but the last, then x0
     int B, H, L, m;
     int nseg, seg_steps;  // segments per row, steps per segment
     int items;            // segments per row that this launch runs
@@ -141,7 +141,7 @@ constexpr size_t scan_lds(int waves) {
 }
 
 // NP: 16-bit pieces of the state and Toeplitz tables (1, or 2 for hi + lo).
-// STATES: only the segments' end states from a zero state, to a.seg.
+// STATES: only the segments' end states from a zero state, and x0, to a.seg.
 template <int DT, int NP, bool STATES>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void ssm_scan_kernel(ScanArgs a) {
     extern __shared__ __attribute__((aligned(16))) char sm[];
@@ -291,12 +291,23 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void s
     const double2 z64 = sc_zpow(z, SC_Q);
     const float2 a1 = make_float2((float)z64.x, (float)z64.y);
     float2 x = make_float2(0.f, 0.f);
-    if constexpr (!STATES) {
+    // the given state.  Of several segments, the launch of the end states alone
+    // reads it, and leaves it in the last segment's slot: x_final may be the
+    // same buffer, and the last segment's wave writes it while others start
+    float2 *const given = a.seg + (row * a.nseg + a.nseg - 1) * 64 + lane;
+    if (STATES ? sg == 0 : a.nseg == 1) {
         if (on && a.x0) {
             const long xi = row * a.m + lane;
             const float d = 1.f / fmaf(th.x, th.x, th.y * th.y);
             x = cscale(cmul(make_float2(a.x0[2 * xi], a.x0[2 * xi + 1]), cconj(th)), d);
         }
+        if constexpr (STATES) {
+            *given = x;
+            x = make_float2(0.f, 0.f);
+        }
+    }
+    if constexpr (!STATES) {
+        if (a.nseg > 1) x = *given;
         if (sg > 0) {   // the state at the segment's start
             const double2 ps = sc_zpow(z64, a.seg_steps * (SC_STEP / SC_Q));
             const float2 as = make_float2((float)ps.x, (float)ps.y);

@@ -129,3 +129,19 @@ def test_scan_zero_tail(h3, dtype, B, H, L):
     check(np.ascontiguousarray(y[:, sel]), ry, TOL[dtype], "y")
     # (most final states lie below float32's range)
     assert np.abs(xf[:, sel] - rx).max() <= TOL_X[dtype] * np.abs(rx).max() + 1e-37
+
+
+@pytest.mark.parametrize("dtype,chunk", [(workloads.F16, 2048), (workloads.BF16, 2048), (workloads.F16, 512)])
+@pytest.mark.parametrize("B,H,L", [(1, 2, 2 * 2048), (3, 5, 8 * 2048), (2, 100, 13 * 2048), (1, 1040, 2048)])
+def test_scan_state_in_place(h3, dtype, chunk, B, H, L):
+    """x_final on x0's own buffer, as a program that carries one state along
+    calls it: the rows cut into segments, and whole ones."""
+    w = workloads.statepass_workload("t", B, H, L, chunk, dtype, seed=41 + H, m=24, dt_lo=1e-4, dt_hi=1e-2, x0_scale=4.0)
+    Ab, Bb, C = (f32dev(v) for v in _params(w))
+    u, D, x0 = to_dev(w.u, dtype), f32dev(w.D), f32dev(w.x0)
+    y, xf = h3.statepass_conv(u, Ab, Bb, C, D, chunk, x0=x0)
+    state = x0.clone()
+    y2, xf2 = h3.statepass_conv_noalloc(u, Ab, Bb, C, D, chunk, x0=state, x_final=state)
+    torch.cuda.synchronize()
+    assert xf2.data_ptr() == state.data_ptr()
+    assert torch.equal(y, y2) and torch.equal(xf, state)
