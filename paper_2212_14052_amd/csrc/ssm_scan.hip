@@ -25,7 +25,8 @@
 //
 // Precision: M_ux and T in 16 bits for fp16 rows, as 16-bit hi + lo pairs for
 // bf16 rows (two products); M_xy and the scaled states in fp16; the state and
-// its decay over blocks in float32 from float64 powers.  theta scales each
+// its decay over blocks in float32 from float64 powers, what a step's 32 factors
+// miss of theirs added back.  theta scales each
 // mode so that its tables have moduli just below 1, where fp16 rounds finest.
 //
 // Bound by the serial chain of each wave at two waves per SIMD (433 VALU and
@@ -97,6 +98,11 @@ __device__ __forceinline__ double2 sc_zpow(double2 z, int e) {
         e >>= 1;
     }
     return r;
+}
+template <int N> __device__ __forceinline__ double2 sc_zsqr(double2 z) {   // z^(2^N)
+#pragma unroll
+    for (int i = 0; i < N; ++i) z = sc_zmul(z, z);
+    return z;
 }
 // a x + s
 __device__ __forceinline__ float2 sc_cfma(float2 a, float2 x, float2 s) {
@@ -288,8 +294,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void s
     const bool on = lane < a.m;
     double2 z = make_double2(0.0, 0.0);
     if (on) z = make_double2(a.Abar[2 * ((long)h * a.m + lane)], a.Abar[2 * ((long)h * a.m + lane) + 1]);
-    const double2 z64 = sc_zpow(z, SC_Q);
+    const double2 z64 = sc_zsqr<6>(z), zstep = sc_zsqr<5>(z64);   // a block's and a step's decay
+    static_assert(SC_Q == 64 && SC_STEP == 32 * 64, "powers by squaring");
     const float2 a1 = make_float2((float)z64.x, (float)z64.y);
+    // what 32 factors a1 leave over of a step's z^2048, added once per step: the
+    // rounding of a1 would add up (modes that hardly decay, L = 2^18: the state
+    // off by 5e-5, with it 2e-6)
+    const double2 z32 = sc_zsqr<5>(make_double2((double)a1.x, (double)a1.y));
+    const float2 da = make_float2((float)(zstep.x - z32.x), (float)(zstep.y - z32.y));
     float2 x = make_float2(0.f, 0.f);
     // the given state.  Of several segments, the launch of the end states alone
     // reads it, and leaves it in the last segment's slot: x_final may be the
@@ -309,11 +321,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void s
     if constexpr (!STATES) {
         if (a.nseg > 1) x = *given;
         if (sg > 0) {   // the state at the segment's start
-            const double2 ps = sc_zpow(z64, a.seg_steps * (SC_STEP / SC_Q));
+            const double2 ps = sc_zpow(zstep, a.seg_steps);
             const float2 as = make_float2((float)ps.x, (float)ps.y);
+            const float2 al = make_float2((float)(ps.x - as.x), (float)(ps.y - as.y));
             const float2 *e = a.seg + row * a.nseg * 64 + lane;
 #pragma unroll 8
-            for (int s = 0; s < sg; ++s) x = sc_cfma(as, x, e[64 * s]);
+            for (int s = 0; s < sg; ++s) x = sc_cfma(as, x, sc_cfma(al, x, e[64 * s]));
         }
     }
 
@@ -377,6 +390,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void s
             }
         // the states before each block, in place
         float mxv = 0.f;
+        const float2 xs = x;
 #pragma unroll
         for (int n = 0; n < 32; ++n) {
             const int r = 4 * (n >> 3) + (n & 3), t = (n >> 2) & 1;
@@ -388,6 +402,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void s
             }
             x = sc_cfma(a1, x, s);
         }
+        x = sc_cfma(da, xs, x);
         if constexpr (!STATES) {
             // T u
             sc_f16 yt[2] = {zero, zero};

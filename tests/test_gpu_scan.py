@@ -9,7 +9,7 @@ import torch
 
 import oracle
 import workloads
-from tests._util import check, cplx64, cplx_to_f32pairs, f32dev, to_dev, to_np64
+from tests._util import check, cplx64, cplx_to_f32pairs, f32dev, record, to_dev, to_np64
 
 pytestmark = pytest.mark.gpu
 
@@ -145,3 +145,30 @@ def test_scan_state_in_place(h3, dtype, chunk, B, H, L):
     torch.cuda.synchronize()
     assert xf2.data_ptr() == state.data_ptr()
     assert torch.equal(y, y2) and torch.equal(xf, state)
+
+
+@pytest.mark.parametrize("B,H,L", [(1, 1024, 1 << 18), (1, 1, 1 << 21)])   # 4096 blocks in one segment; 1024 segments
+def test_scan_undamped_modes(h3, B, H, L):
+    """Modes of modulus 1 over a long sequence, bf16 rows: the state's decay
+    factor acts once per block or segment, and what its rounding leaves over
+    must not add up.  The bf16 pairs hold the tables to 2^-17 and the state is
+    rounded twice per block, as a random walk 2^-24 sqrt(2 L / 64): 1.2e-5
+    together, relative to the norm (a float32 factor alone: 2^-25 L / 64 on
+    average, 1e-4 here)."""
+    m = 4
+    rng = np.random.default_rng(31)
+    a = cplx_to_f32pairs(np.exp(1j * rng.uniform(0, np.pi, (H, m))))
+    b = cplx_to_f32pairs(rng.standard_normal((H, m)) + 1j * rng.standard_normal((H, m)))
+    c = cplx_to_f32pairs((rng.standard_normal((H, m)) + 1j * rng.standard_normal((H, m))) / 8)
+    a = a * (1 - 2.0 ** -24 * np.float32(rng.uniform(0, 1)))
+    g = torch.Generator(device="cuda")
+    g.manual_seed(5)
+    u = torch.randn((B, H, L), generator=g, device="cuda", dtype=torch.bfloat16) * 2.0 ** -4
+    _, xf = h3.statepass_conv(u, f32dev(a), f32dev(b), f32dev(c), None, 2048)
+    torch.cuda.synchronize()
+    xf = cplx64(to_np64(xf))
+    sel = np.unique(np.r_[0, H // 3, H - 1])
+    _, rx = oracle.recurrence(to_np64(u[:, sel.tolist()]), *(cplx64(v[sel].astype(np.float32)) for v in (a, b, c)), None)
+    err = np.linalg.norm(xf[:, sel] - rx) / np.linalg.norm(rx)
+    record(f"undamped L={L}", rel_err=float(err))
+    assert err < 1.2e-5, err
