@@ -328,27 +328,35 @@ __global__ __launch_bounds__(GW_T) __attribute__((amdgpu_waves_per_eu(NS == 3 ? 
     const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
     const int ww = wv >> 2, wx = wv & 3;
     // this wave's slices q = wv + 8 s, s < NSL (a wave past the last slice
-    // copies slice wv again into the never-read slot): the lane's source as an
-    // element offset from the operand's base (W_jq for q < WS, X after) at
-    // K step 0; a step adds 32 rows of W (32 ldw) or 32 columns of X
+    // copies slice wv again into the never-read slot), of W_jq for q < WS, of X
+    // after: a 64-bit base in scalar registers (X may exceed 4 GiB), the tile's
+    // at K step 0, that moves on by 32 rows of W (32 ldw) or 32 columns of X per
+    // step, and the lane's byte offset from it
     const int wvu = __builtin_amdgcn_readfirstlane(wv);   // the wave index, in a scalar register
-    uint32_t soff[S::NSL];
+    const char *src[S::NSL];
+    uint32_t step[S::NSL], soff[S::NSL];
 #pragma unroll
     for (int sl = 0; sl < S::NSL; ++sl) {
         const int q = wvu + 8 * sl < S::SLICES ? wvu + 8 * sl : wvu;
         if (q < S::WS) {
             const int b = 1024 * q + 16 * lane;
             const int r = b / S::WP, c = b % S::WP;
-            soff[sl] = (uint32_t)(r * ldw + wc + (c < 2 * TW ? c / 2 : 0));
+            src[sl] = (const char *)(Wj + wc);
+            step[sl] = 2 * GW_K * (uint32_t)ldw;
+            soff[sl] = 2 * (uint32_t)(r * ldw + (c < 2 * TW ? c / 2 : 0));
         } else if constexpr (XKM) {
             // rows k of the tile's 256 activation rows, which lie in batch x0 / L
             const int b = 1024 * (q - S::WS) + 16 * lane;
             const int r = b / S::XP, c = b % S::XP;
-            soff[sl] = (uint32_t)((x0 / L) * K * L + (x0 % L) + r * L + (c < 2 * GW_X ? c / 2 : 0));
+            src[sl] = (const char *)(X + (long)(x0 / L) * K * L + x0 % L);
+            step[sl] = 2 * GW_K * (uint32_t)L;
+            soff[sl] = 2 * (uint32_t)(r * L + (c < 2 * GW_X ? c / 2 : 0));
         } else {
             const int r = 16 * (q - S::WS) + (lane >> 2);
             const int c = (lane & 3) ^ ((r >> 2) & 3);
-            soff[sl] = (uint32_t)((x0 + r) * K + 8 * c);
+            src[sl] = (const char *)(X + (long)x0 * K);
+            step[sl] = 2 * GW_K;
+            soff[sl] = 2 * (uint32_t)(r * K + 8 * c);
         }
     }
     const int nk = K / GW_K;
@@ -357,23 +365,21 @@ __global__ __launch_bounds__(GW_T) __attribute__((amdgpu_waves_per_eu(NS == 3 ? 
     // and the lane's byte offset): the compiler then places no wait of its
     // own for them before LDS reads; the explicit vmcnt waits order them.
     const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_void *)gw_lds;
-    // copies of K step kt (clamped to the last step: past it they only keep
-    // the count per step fixed) into stage kt % NS
+    // copies of K step kt into stage kt % NS, called for kt = 0, 1, ...; past
+    // the last step they read it again and only keep the count per step fixed
     auto issue = [&](int kt) {
         const uint32_t st = lds0 + (uint32_t)((kt % NS) * S::STAGE_B);
-        const uint32_t k0 = (uint32_t)min(kt, nk - 1) * GW_K;
+        const bool more = kt + 1 < nk;
 #pragma unroll
         for (int sl = 0; sl < S::NSL; ++sl) {
             const int q = wvu + 8 * sl;
             const bool real = q < S::SLICES;
-            const bool wside = (real ? q : wvu) < S::WS;
-            const uint16_t *base = wside ? Wj : X;
-            const uint32_t vo = 2 * (soff[sl] + k0 * (wside ? (uint32_t)ldw : (XKM ? (uint32_t)L : 1u)));
             const uint32_t la = real ? st + (uint32_t)q * 1024 : lds0 + (uint32_t)(NS * S::STAGE_B);
             asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, %2"
                          :
-                         : "v"(vo), "s"(la), "s"(base)
+                         : "v"(soff[sl]), "s"(la), "s"(src[sl])
                          : "memory", "m0");
+            if (more) src[sl] += step[sl];
         }
     };
     f32x16_t acc[S::TI][2];
@@ -953,7 +959,7 @@ static hipError_t launch_gemm_w_t(const void *const *W, const void *X, void *C, 
     auto fn = gemm_w<DT, OUT, TW, SS, NS>;
     (void)hipFuncSetAttribute((const void *)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     hipLaunchKernelGGL(fn, dim3((Mw / TW) * (Nx / GW_X)), dim3(GW_T), lds, s, (const uint16_t *)W[0],
-                       (const uint16_t *)W[OUT ? 1 : 0], (const uint16_t *)W[OUT ? 2 : 0], (const uint16_t *)X,
+                       (const uint16_t *)W[OUT == 1 ? 1 : 0], (const uint16_t *)W[OUT == 1 ? 2 : 0], (const uint16_t *)X,
                        (uint16_t *)C, Mw, Nx, K, ldw, d, L);
     return hipGetLastError();
 }
