@@ -133,17 +133,16 @@ __global__ __launch_bounds__(64 * LD_MAXW, 2) void layer_direct_kernel(const uin
             }
     }
     int eg[R];
-    const float ft = ldexpf(1.f, et);
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         float mx = 0.f;
 #pragma unroll
         for (int b = 0; b < NB; ++b) {
             const float2 v0 = cd_unpack<DT>(vv[r][b].x), v1 = cd_unpack<DT>(vv[r][b].y);
-            acc[r][b][0] = acc[r][b][0] * ft * v0.x;
-            acc[r][b][1] = acc[r][b][1] * ft * v0.y;
-            acc[r][b][2] = acc[r][b][2] * ft * v1.x;
-            acc[r][b][3] = acc[r][b][3] * ft * v1.y;
+            acc[r][b][0] = ldexpf(acc[r][b][0], et) * v0.x;
+            acc[r][b][1] = ldexpf(acc[r][b][1], et) * v0.y;
+            acc[r][b][2] = ldexpf(acc[r][b][2], et) * v1.x;
+            acc[r][b][3] = ldexpf(acc[r][b][3], et) * v1.y;
 #pragma unroll
             for (int e = 0; e < 4; ++e) mx = fmaxf(mx, fabsf(acc[r][b][e]));
         }
@@ -157,12 +156,13 @@ __global__ __launch_bounds__(64 * LD_MAXW, 2) void layer_direct_kernel(const uin
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         uint16_t *gh = slot + r * 2 * P::GS, *gl = gh + P::GS;
-        const float f = ldexpf(1.f, -eg[r]);
 #pragma unroll
         for (int b = 0; b < NB; ++b) {
             float x[4], y[4];
+            // (the exponent applied to each value, here and below: the power of
+            // two alone leaves float32 for rows below 2^-113)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) x[e] = acc[r][b][e] * f;
+            for (int e = 0; e < 4; ++e) x[e] = ldexpf(acc[r][b][e], -eg[r]);
             const uint2 hi = make_uint2(cd_pack<F16>(x[0], x[1]), cd_pack<F16>(x[2], x[3]));
             const float2 h0 = cd_unpack<F16>(hi.x), h1 = cd_unpack<F16>(hi.y);
             y[0] = x[0] - h0.x; y[1] = x[1] - h0.y; y[2] = x[2] - h1.x; y[3] = x[3] - h1.y;
@@ -215,13 +215,13 @@ __global__ __launch_bounds__(64 * LD_MAXW, 2) void layer_direct_kernel(const uin
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         if (r >= nr) continue;
-        const float f = ldexpf(1.f, ek + eg[r]);
+        const int eo = ek + eg[r];
 #pragma unroll
         for (int b = 0; b < NB; ++b) {
             const float2 q0 = cd_unpack<DT>(vv[r][b].x), q1 = cd_unpack<DT>(vv[r][b].y);
             *(uint2 *)(o + ro[r] + 256 * b + lo4) =
-                make_uint2(cd_pack<DT>(acc[r][b][0] * f * q0.x, acc[r][b][1] * f * q0.y),
-                           cd_pack<DT>(acc[r][b][2] * f * q1.x, acc[r][b][3] * f * q1.y));
+                make_uint2(cd_pack<DT>(ldexpf(acc[r][b][0], eo) * q0.x, ldexpf(acc[r][b][1], eo) * q0.y),
+                           cd_pack<DT>(ldexpf(acc[r][b][2], eo) * q1.x, ldexpf(acc[r][b][3], eo) * q1.y));
         }
     }
 }

@@ -44,3 +44,21 @@ def test_layer_direct(h3, dtype, B, L, d, m_s, skips, vscale):
                           k.astype(np.float64), None if dD is None else dD.astype(np.float64),
                           shift_D=None if sD is None else sD.astype(np.float64))
     check(out, ref, TOL[dtype], "out", rows=False)
+
+
+@pytest.mark.parametrize("B,L", [(1, 256), (3, 1024)])
+def test_layer_direct_tiny_gate(h3, B, L):
+    """G = Kbar V near 2^-118, whose reciprocal is no float32; Q brings the
+    output back into range."""
+    d, dtype = 128, workloads.BF16
+    w = workloads.layer_workload("t", B, L, d, dtype, seed=L, m=8, m_shift=64)
+    A, Bm, C, dt = w.diag.complex64()
+    k = oracle.ssm_kernel(A, Bm, C, dt, L).astype(np.float32)
+    W = {n: workloads.round_to(w.W[n][1] * s, dtype)
+         for n, s in (("q", 2.0 ** 30), ("k", 2.0 ** -10), ("v", 2.0 ** -110), ("o", 1.0))}
+    out = h3.layer_fwd(to_dev(w.x, dtype), *(to_dev(W[n][0], dtype) for n in "qkvo"), f32dev(w.shift_C), None,
+                       f32dev(k), f32dev(w.diag_D))
+    torch.cuda.synchronize()
+    ref = oracle.h3_layer(w.x64, *(W[n][1] for n in "qkvo"), w.shift_C.astype(np.float64), k.astype(np.float64),
+                          w.diag_D.astype(np.float64))
+    check(out, ref, TOL[dtype], "out", rows=False)
