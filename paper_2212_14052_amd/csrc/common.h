@@ -76,6 +76,28 @@ __device__ __forceinline__ int xcd_logical_block(int b, int nblocks) {
     return (b % NXCD) * (nblocks / NXCD) + b / NXCD;
 }
 
+// max of x over each group of W consecutive lanes, in every lane of the group
+// (W a power of two <= 64): lane exchanges on the VALU, no LDS.
+template <int CTRL> __device__ __forceinline__ uint32_t max_dpp(uint32_t x) {
+    const uint32_t y = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, 0xf, 0xf, false);
+    return x > y ? x : y;
+}
+template <int W> __device__ __forceinline__ uint32_t group_max(uint32_t x) {
+    if constexpr (W >= 2) x = max_dpp<0xB1>(x);     // quad_perm [1,0,3,2]
+    if constexpr (W >= 4) x = max_dpp<0x4E>(x);     // quad_perm [2,3,0,1]
+    if constexpr (W >= 8) x = max_dpp<0x141>(x);    // row_half_mirror
+    if constexpr (W >= 16) x = max_dpp<0x140>(x);   // row_mirror
+    if constexpr (W >= 32) {
+        const auto r = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+        x = r[0] > r[1] ? r[0] : r[1];
+    }
+    if constexpr (W >= 64) {
+        const auto r = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+        x = r[0] > r[1] ? r[0] : r[1];
+    }
+    return x;
+}
+
 // Products of two 16-bit pairs, rounded once.
 template <int DT> __device__ __forceinline__ uint32_t mul_16x2(uint32_t x, uint32_t z) {
     if constexpr (DT == F16) {
@@ -88,6 +110,7 @@ template <int DT> __device__ __forceinline__ uint32_t mul_16x2(uint32_t x, uint3
         return __builtin_bit_cast(uint32_t, __builtin_convertvector(p, b2));
     }
 }
+
 // exp(tau * lambda) for complex lambda given in float64, returned in float32:
 // the phase tau*Im(lambda) is reduced modulo 2 pi in float64 before the
 // float32 sine/cosine, so large arguments keep full accuracy.

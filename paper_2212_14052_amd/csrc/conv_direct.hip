@@ -4,11 +4,13 @@
 //     y[t] = sum_{s <= t} k[t-s] u[s] + D u[t],
 // or, for the input gradient, the correlation sum_{s >= t} k[s-t] u[s] + D u[t].
 //
-// u is 16-bit as it comes; the float32 kernel (skip term in its first tap) is
-// split into two 16-bit pieces, k = hi + lo, so that every product is exact in
-// the matrix core's float32 and the result is the float32 sum of a kernel
-// rounded to 22 bits (fp16) or 16 (bf16): its error is the output's own
-// rounding, as with the float32 transform that this replaces.
+// u enters as fp16, bf16 rows scaled by a power of two; the float32 kernel
+// (skip term in its first tap), scaled likewise, is split into two fp16
+// pieces, k = hi + lo, so that every product is exact in the matrix core's
+// float32 and the result is the float32 sum of a kernel off by 2^-23 at most,
+// where a float32 transform rounds at every pass.  (A kernel of cancelling taps,
+// rms 1.15, at L = 1024 came out 3.7e-6 off, by the float32 transform 1.0e-5; with
+// the kernel in bf16 pieces, 2^-17, it was 1.7e-4.)
 //
 // One tile product, rows i < 16, columns n < 16, reduction kk < 32:
 //     D[i][n] += sum_kk A[i][kk] B[kk][n],   A[i][kk] = k[tau + 16 + i - kk],
@@ -28,9 +30,11 @@
 // reads.  The work grows with L^2: at L = 4096 one row per wave took 134 us at B
 // = 5, H = 767, where the transform takes 87.
 //
-// Measured, with the kernel generation, against the float32 transform (us): B =
-// 8, H = 768, L = 1024, fp16: 31 -> 24; B = 2, H = 1500, L = 1024, bf16: 26 -> 25;
-// forward and backward at B = 8, H = 768, L = 1024, bf16: 63 -> 48.
+// Measured, with the kernel generation, float32 transform -> this (us): B = 8,
+// H = 768, L = 1024: fp16 29.4 -> 23.3, bf16 31.0 -> 23.2; B = 16, H = 2048: 97 -> 83,
+// 102 -> 84; B = 1, H = 4096: 51 -> 43, 53 -> 43; L = 512, B = 8, H = 768, bf16: 19.1
+// -> 18.2.  Level where the two calls' host time covers it, from L = 256 to B = 1, H =
+// 768 at 1024; B = 2, H = 1500 at 1024, one wave per workgroup: 24.9 -> 26.0, 25.6 -> 26.3.
 #include "direct_conv.h"
 #include "internal.h"
 
@@ -38,7 +42,6 @@ namespace h3 {
 namespace {
 
 constexpr int CD_MAXW = 8;
-
 
 // LDS elements (16-bit) of the two kernel pieces and of a row slot
 template <int NB>
@@ -72,6 +75,9 @@ __global__ __launch_bounds__(64 * CD_MAXW, 4) void conv_direct_kernel(const uint
     uint16_t *kh = cd_sm, *kl = cd_sm + P::KS;
     uint16_t *us = cd_sm + 2 * P::KS + w * R * P::US;
 
+    // the channel's kernel, then the wave's rows: every load in flight at once
+    CdKernel<L> kr;
+    kr.load(k + (long)h * L, D ? D[h] : 0.f, tid, nt);
     // the wave's rows into LDS, zeros in front (behind, for the correlation)
     constexpr int PIECES = L / 8, PT = (PIECES + 63) / 64;
     cd_u4 raw[R][PT], rav[HEADS ? R : 1][PT];
@@ -87,17 +93,14 @@ __global__ __launch_bounds__(64 * CD_MAXW, 4) void conv_direct_kernel(const uint
             if constexpr (HEADS) rav[r][p] = *(const cd_u4 *)(v + (row + kv) * L + piece);
         }
 
-    // the kernel as two 16-bit pieces hi + lo (fp16: times a power of two that
-    // puts its largest value in [2^14, 2^15), so that lo stays normal),
-    // reversed: element L - t holds k_t (the correlation: element 16 + t)
-    const float skip = D ? D[h] : 0.f;
-    const float *kr = k + (long)h * L;
-    int ek = 0;
-    if constexpr (DT == F16) ek = cd_kernel_exp(kr, L, skip, red, tid, nt);
-    for (int t = tid; t < L; t += nt) {
-        const float v = ldexpf(t == 0 ? kr[0] + skip : kr[t], -ek);
-        const int x = CONJ ? 16 + t : L - t;
-        cd_split<DT>(v, kh[x], kl[x]);
+    // the kernel as two fp16 pieces hi + lo, times a power of two that puts its
+    // largest value in [2^14, 2^15), so that lo stays normal, reversed: element
+    // L - t holds k_t (the correlation: element 16 + t)
+    const int ek = cd_group_exp(kr.max_abs(), red, tid, nt);
+#pragma unroll
+    for (int i = 0; i < CdKernel<L>::N; ++i) {
+        const int t = tid + i * nt, x = CONJ ? 16 + t : L - t;
+        if (i * nt < L && t < L) cd_split(ldexpf(kr.v[i], -ek), kh[x], kl[x]);
     }
     // zeros: lags below 0 and (reversed: element 0) from L on
     for (int x = tid; x < 24; x += nt) {
@@ -105,18 +108,21 @@ __global__ __launch_bounds__(64 * CD_MAXW, 4) void conv_direct_kernel(const uint
         kh[z] = 0;
         kl[z] = 0;
     }
+    int er[R];   // the rows' exponents
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         uint16_t *ur = us + r * P::US;
+        if constexpr (HEADS) {
 #pragma unroll
-        for (int p = 0; p < PT; ++p) {
-            cd_u4 x = raw[r][p];
-            if constexpr (HEADS) {
-                const cd_u4 z = rav[r][p];
-                x = cd_u4{mul_16x2<DT>(x[0], z[0]), mul_16x2<DT>(x[1], z[1]), mul_16x2<DT>(x[2], z[2]), mul_16x2<DT>(x[3], z[3])};
+            for (int p = 0; p < PT; ++p) {
+                const cd_u4 x = raw[r][p], z = rav[r][p];
+                raw[r][p] = cd_u4{mul_16x2<DT>(x[0], z[0]), mul_16x2<DT>(x[1], z[1]), mul_16x2<DT>(x[2], z[2]), mul_16x2<DT>(x[3], z[3])};
             }
-            *(cd_u4 *)(ur + (CONJ ? 0 : 240) + 8 * min(64 * p + lane, PIECES - 1)) = x;
         }
+        er[r] = ek;
+        if constexpr (DT == BF16) er[r] += cd_bf16_to_f16(raw[r]);
+#pragma unroll
+        for (int p = 0; p < PT; ++p) *(cd_u4 *)(ur + (CONJ ? 0 : 240) + 8 * min(64 * p + lane, PIECES - 1)) = raw[r][p];
         if (lane < 30) *(uint4 *)(ur + (CONJ ? L : 0) + 8 * lane) = make_uint4(0, 0, 0, 0);
     }
     __syncthreads();
@@ -152,24 +158,24 @@ __global__ __launch_bounds__(64 * CD_MAXW, 4) void conv_direct_kernel(const uint
 #pragma unroll
                 for (int d = 0; d < NB; ++d) {
                     const int b = CONJ ? a - d : a + d;
-                    if (b >= 0 && b < NB) acc[r][b] = cd_mfma<DT>(Ah[d], Bv, acc[r][b]);
+                    if (b >= 0 && b < NB) acc[r][b] = cd_mfma(Ah[d], Bv, acc[r][b]);
                 }
 #pragma unroll
                 for (int d = 0; d < NB; ++d) {
                     const int b = CONJ ? a - d : a + d;
-                    if (b >= 0 && b < NB) acc[r][b] = cd_mfma<DT>(Al[d], Bv, acc[r][b]);
+                    if (b >= 0 && b < NB) acc[r][b] = cd_mfma(Al[d], Bv, acc[r][b]);
                 }
             }
     }
-    const float s = ldexpf(1.f, ek);
+    // (the exponent applied to each value: 2^er alone may leave float32)
 #pragma unroll
     for (int r = 0; r < R; ++r)
         if (r < nr) {
             uint16_t *yr = y + ((long)(b0 + r) * H + h) * L + 16 * i16 + 4 * g;
 #pragma unroll
             for (int b = 0; b < NB; ++b)
-                *(uint2 *)(yr + 256 * b) = make_uint2(cd_pack<DT>(acc[r][b][0] * s, acc[r][b][1] * s),
-                                                      cd_pack<DT>(acc[r][b][2] * s, acc[r][b][3] * s));
+                *(uint2 *)(yr + 256 * b) = make_uint2(cd_pack<DT>(ldexpf(acc[r][b][0], er[r]), ldexpf(acc[r][b][1], er[r])),
+                                                      cd_pack<DT>(ldexpf(acc[r][b][2], er[r]), ldexpf(acc[r][b][3], er[r])));
         }
 }
 

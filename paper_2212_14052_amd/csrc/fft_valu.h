@@ -214,28 +214,6 @@ __device__ __forceinline__ void pass_twiddles(float2 *v, const float2 *e) {
     for (int r = 1; r < R; ++r) v[r] = cmul(v[r], w[r]);
 }
 
-// max of x over each group of W consecutive lanes, in every lane of the group
-// (W a power of two <= 64): lane exchanges on the VALU, no LDS.
-template <int CTRL> __device__ __forceinline__ uint32_t max_dpp(uint32_t x) {
-    const uint32_t y = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, 0xf, 0xf, false);
-    return x > y ? x : y;
-}
-template <int W> __device__ __forceinline__ uint32_t group_max(uint32_t x) {
-    if constexpr (W >= 2) x = max_dpp<0xB1>(x);     // quad_perm [1,0,3,2]
-    if constexpr (W >= 4) x = max_dpp<0x4E>(x);     // quad_perm [2,3,0,1]
-    if constexpr (W >= 8) x = max_dpp<0x141>(x);    // row_half_mirror
-    if constexpr (W >= 16) x = max_dpp<0x140>(x);   // row_mirror
-    if constexpr (W >= 32) {
-        const auto r = __builtin_amdgcn_permlane16_swap(x, x, false, false);
-        x = r[0] > r[1] ? r[0] : r[1];
-    }
-    if constexpr (W >= 64) {
-        const auto r = __builtin_amdgcn_permlane32_swap(x, x, false, false);
-        x = r[0] > r[1] ? r[0] : r[1];
-    }
-    return x;
-}
-
 // The largest |row a| and |row b| of a signal of T threads (float bits), from
 // each thread's own.  Signals of one wave or less need no LDS; wider ones pass
 // one value per wave through red (2 T / 64 words) and one barrier, which also

@@ -9,7 +9,7 @@ import torch
 
 import oracle
 import workloads
-from tests._util import check, f32dev, to_dev
+from tests._util import check, f32dev, record, to_dev, to_np64
 
 pytestmark = pytest.mark.gpu
 
@@ -58,3 +58,53 @@ def test_conv_direct_ranges(h3, dtype, ks, us):
     y = h3.fftconv(to_dev(u_s, dtype), f32dev(k))
     torch.cuda.synchronize()
     check(y, oracle.causal_conv(u64, k.astype(np.float64), None), TOL[dtype], "y")
+
+
+@pytest.mark.parametrize("dtype", [workloads.F16, workloads.BF16])
+@pytest.mark.parametrize("L", [256, 512, 1024])
+def test_conv_direct_cancelling_taps(h3, dtype, L):
+    """Taps that sum to nothing in threes against a constant row: what is left
+    of them at every third output is the error of the taps and of the sums.
+    An fp16 pair holds a tap to 2^-23 of itself and the sums round to 2^-24 per
+    32 terms, together below 2^-22 sqrt(L) of the taps' rms, and the result is
+    rounded once (bf16 pieces of a tap: 2^-17 of it)."""
+    B, H = 3, 4
+    rng = np.random.default_rng(L)
+    a = rng.standard_normal((H, L // 3 + 1, 3))
+    a[..., 2] = -a[..., 0] - a[..., 1]
+    k = a.reshape(H, -1)[:, :L].astype(np.float32)
+    D = np.full(H, 3.0, np.float32)
+    k[:, 0] -= D                      # the skip weight is part of tap 0
+    u = np.zeros((B, H, L)) + 1.0
+    u_s, u64 = workloads.round_to(u, dtype)
+    ud = to_dev(u_s, dtype)
+    y = h3.fftconv(ud, f32dev(k), f32dev(D))
+    du, _, _ = h3.fftconv_bwd(None, f32dev(k), f32dev(D), ud, want_dk=False, want_dD=False)
+    torch.cuda.synchronize()
+    kd = k.astype(np.float64)
+    kd[:, 0] = (k[:, 0] + D).astype(np.float32)
+    ref = np.cumsum(kd, axis=1)[:, 2::3]
+    tol = 2.0 ** -22 * np.sqrt(L * np.mean(kd ** 2)) + np.abs(ref).max() * (2.0 ** -8 if dtype == workloads.BF16 else 2.0 ** -11)
+    for what, v in (("y", y), ("du", torch.flip(du, (-1,)))):
+        err = np.abs(to_np64(v)[..., 2::3] - ref).max()
+        record(f"cancelling {what} {dtype} L={L}", err=float(err), tol=float(tol))
+        assert err < tol, (what, err, tol)
+
+
+@pytest.mark.parametrize("us", [2.0 ** -100, 2.0 ** 100])
+def test_conv_direct_bf16_scales(h3, us):
+    """bf16 rows far outside fp16's range, row by row, and one with an infinity,
+    which leaves the other rows alone."""
+    B, H, L = 5, 3, 512
+    rng = np.random.default_rng(7)
+    scale = us ** rng.uniform(0, 1, (B, H, 1))
+    u_s, u64 = workloads.round_to(rng.standard_normal((B, H, L)) * scale, workloads.BF16)
+    k = rng.standard_normal((H, L)).astype(np.float32)
+    u = to_dev(u_s, workloads.BF16)
+    u[1, 2, 100] = float("inf")
+    y = to_np64(h3.fftconv(u, f32dev(k)))
+    ref = oracle.causal_conv(u64, k.astype(np.float64), None)
+    assert not np.isfinite(y[1, 2, 100:]).any()
+    y[1, 2], ref[1, 2] = 1.0, 1.0
+    n = np.abs(ref).max(axis=-1, keepdims=True)
+    check(y / n, ref / n, TOL[workloads.BF16], "y")
