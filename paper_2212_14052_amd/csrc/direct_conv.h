@@ -7,17 +7,13 @@
 namespace h3 {
 
 typedef _Float16 cd_h8 __attribute__((ext_vector_type(8)));
-typedef __bf16 cd_b8 __attribute__((ext_vector_type(8)));
 typedef _Float16 cd_h2 __attribute__((ext_vector_type(2)));
 typedef __bf16 cd_b2 __attribute__((ext_vector_type(2)));
 typedef unsigned cd_u4 __attribute__((ext_vector_type(4)));
 typedef float cd_f2 __attribute__((ext_vector_type(2)));
 typedef float cd_f4 __attribute__((ext_vector_type(4)));
 
-template <int DT = F16>
 __device__ __forceinline__ cd_f4 cd_mfma(uint4 a, uint4 b, cd_f4 c) {
-    if constexpr (DT == BF16)
-        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(cd_b8, a), __builtin_bit_cast(cd_b8, b), c, 0, 0, 0);
     return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(cd_h8, a), __builtin_bit_cast(cd_h8, b), c, 0, 0, 0);
 }
 template <int DT>
@@ -26,8 +22,6 @@ __device__ __forceinline__ uint32_t cd_pack(float lo, float hi) {
     if constexpr (DT == BF16) return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, cd_b2));
     else return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, cd_h2));
 }
-template <int DT>
-__device__ __forceinline__ uint16_t cd_round(float v) { return DT == BF16 ? f32_to_bf16(v) : f32_to_f16(v); }
 template <int DT>
 __device__ __forceinline__ float cd_value(uint16_t v) { return DT == BF16 ? bf16_to_f32(v) : f16_to_f32(v); }
 template <int DT>
@@ -44,8 +38,9 @@ __device__ __forceinline__ uint4 cd_frag(const uint32_t *s, uint32_t sh) {
 }
 
 // Exponent that puts the largest of the workgroup's values, mx of each thread
-// (not below 0), into [2^14, 2^15); red: one float per wave.  A barrier
-// separates the call from the last use of red.
+// (not below 0), into [2^14, 2^15); red: one float per wave (nt = 64: the
+// wave's own, without barrier).  A barrier separates the call from the last use
+// of red.
 __device__ __forceinline__ int cd_group_exp(float mx, float *red, int tid, int nt) {
     mx = __uint_as_float(group_max<64>(__float_as_uint(mx)));   // (bits order floats >= 0)
     if (nt > 64) {
@@ -54,13 +49,6 @@ __device__ __forceinline__ int cd_group_exp(float mx, float *red, int tid, int n
         for (int v = 0; v < nt >> 6; ++v) mx = fmaxf(mx, red[v]);
     }
     return pow2_exp(mx) - 15;
-}
-
-// The same over a kernel row's n values in memory, skip added to tap 0.
-__device__ __forceinline__ int cd_kernel_exp(const float *k, int n, float skip, float *red, int tid, int nt) {
-    float mx = 0.f;
-    for (int t = tid; t < n; t += nt) mx = fmaxf(mx, fabsf(t == 0 ? k[0] + skip : k[t]));
-    return cd_group_exp(mx, red, tid, nt);
 }
 
 // A kernel row's L values over nt threads, the skip weight added to tap 0:
@@ -87,10 +75,9 @@ struct CdKernel {
 
 // v = hi + lo in fp16: |v - hi - lo| <= 2^-23 |v| (half a unit of lo, which is
 // below half a unit of hi), where lo is a normal number
-template <int DT = F16>
 __device__ __forceinline__ void cd_split(float v, uint16_t &hi, uint16_t &lo) {
-    hi = cd_round<DT>(v);
-    lo = cd_round<DT>(v - cd_value<DT>(hi));
+    hi = f32_to_f16(v);
+    lo = f32_to_f16(v - f16_to_f32(hi));
 }
 
 // A row of bf16 values, 16 bytes per lane and piece, as fp16 times a power of

@@ -5,11 +5,14 @@
 // on (B, d, L) rows, O channel-major.
 //
 // Both convolutions are direct sums (see the direct convolution kernel for the
-// tile product): the FIR's 64 float32 taps as a pair of 16-bit pieces against K
-// as it comes, three tiles per 256 outputs; the diagonal SSM's kernel as a pair
-// against G as a pair, k_hi G_hi + k_lo G_hi + k_hi G_lo, both scaled to fp16
-// by a power of two (G per row).  G stays a float32 value between the two,
-// rounded to 22 bits; nothing of it reaches memory.
+// tile product) of fp16 operands, each row, kernel and tap set scaled by a power
+// of two: the FIR's 64 float32 taps as a pair against K (bf16 fits), three tiles
+// per 256 outputs; the diagonal SSM's kernel as a pair against G as a pair, k_hi
+// G_hi + k_lo G_hi + k_hi G_lo.  A pair is off by 2^-23 at most and the product
+// left out is below 2^-22 of its term.  With cancelling parameters (L = 1024) the
+// second sum comes out 3.1e-6 off, where the float32 transform before was 3.6e-6
+// off, and the first 1.3e-6 (float32 multiply-adds 0.6e-6; bf16 pieces of the taps
+// 6e-5).  G is a float32 value between the two; nothing of it reaches memory.
 //
 // One wave carries R rows of a channel through all steps; K, then G_hi and
 // G_lo lie in the wave's own LDS slots, so that after the channel's kernel and
@@ -56,6 +59,11 @@ __global__ __launch_bounds__(64 * LD_MAXW, 2) void layer_direct_kernel(const uin
     uint16_t *kh = ld_sm, *kl = kh + P::KS, *th = kl + P::KS, *tl = th + LD_TAPS;
     uint16_t *slot = tl + LD_TAPS + w * R * 2 * P::GS;
 
+    // the channel's kernel, and its taps, one per lane of every wave
+    CdKernel<L> kr;
+    kr.load(diag_k + (long)c * L, diag_D ? diag_D[c] : 0.f, tid, nt);
+    float tap = lane < m_s ? shift_C[(long)c * m_s + lane] : 0.f;
+    if (lane == 0 && shift_D) tap += shift_D[c];
     // K of the wave's rows (rows past the end: the last one again, never used)
     constexpr int PIECES = L / 8, PT = (PIECES + 63) / 64;
     cd_u4 raw[R][PT];
@@ -75,29 +83,32 @@ __global__ __launch_bounds__(64 * LD_MAXW, 2) void layer_direct_kernel(const uin
         for (int b = 0; b < NB; ++b) vv[r][b] = *(const uint2 *)(v + ro[r] + 256 * b + lo4);
 
     // diag_k as an fp16 pair, reversed: element L - t holds tap t
-    const float *kr = diag_k + (long)c * L;
-    const float skip = diag_D ? diag_D[c] : 0.f;
-    const int ek = cd_kernel_exp(kr, L, skip, red, tid, nt);
-    for (int t = tid; t < L; t += nt) cd_split<F16>(ldexpf(t == 0 ? kr[0] + skip : kr[t], -ek), kh[L - t], kl[L - t]);
+    const int ek = cd_group_exp(kr.max_abs(), red, tid, nt);
+#pragma unroll
+    for (int i = 0; i < CdKernel<L>::N; ++i) {
+        const int t = tid + i * nt;
+        if (i * nt < L && t < L) cd_split(ldexpf(kr.v[i], -ek), kh[L - t], kl[L - t]);
+    }
     for (int x = tid; x < 24; x += nt) {
         const int z = x == 0 ? 0 : L + x;
         kh[z] = 0;
         kl[z] = 0;
     }
-    // the shift taps as a pair in K's type, reversed: element 96 - j holds tap j
-    __syncthreads();   // red is reused
-    const float *cs = shift_C + (long)c * m_s;
-    const float sd = shift_D ? shift_D[c] : 0.f;
-    const int et = DT == F16 ? cd_kernel_exp(cs, m_s, sd, red, tid, nt) : 0;
-    for (int x = tid; x < LD_TAPS; x += nt) {
-        const int j = 96 - x;
-        const float t = j >= 0 && j < m_s ? cs[j] + (j == 0 ? sd : 0.f) : 0.f;
-        cd_split<DT>(ldexpf(t, -et), th[x], tl[x]);
+    // the shift taps as an fp16 pair, reversed: element 96 - j holds tap j
+    const int et = cd_group_exp(fabsf(tap), red, lane, 64);   // (64: the wave's own maximum)
+    if (w == 0) {
+        cd_split(ldexpf(tap, -et), th[96 - lane], tl[96 - lane]);
+        const int z = lane < 33 ? lane : 64 + lane;   // 0 .. 32, 97 .. 127
+        th[z] = 0;
+        tl[z] = 0;
     }
     // K behind 80 zeros, in the row's first piece
+    int eb[R];   // the exponents of the rows' Kbar
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         uint16_t *s = slot + r * 2 * P::GS;
+        eb[r] = et;
+        if constexpr (DT == BF16) eb[r] += cd_bf16_to_f16(raw[r]);
 #pragma unroll
         for (int p = 0; p < PT; ++p) *(cd_u4 *)(s + 80 + 8 * min(64 * p + lane, PIECES - 1)) = raw[r][p];
         if (lane < 10) *(uint4 *)(s + 8 * lane) = make_uint4(0, 0, 0, 0);
@@ -126,8 +137,8 @@ __global__ __launch_bounds__(64 * LD_MAXW, 2) void layer_direct_kernel(const uin
 #pragma unroll
                 for (int p = 0; p < 3; ++p) {
                     const uint4 Bv = *(const uint4 *)(kb + r * 2 * P::GS + 256 * b - 32 * p);
-                    s = cd_mfma<DT>(Th[p], Bv, s);
-                    s = cd_mfma<DT>(Tl[p], Bv, s);
+                    s = cd_mfma(Th[p], Bv, s);
+                    s = cd_mfma(Tl[p], Bv, s);
                 }
                 acc[r][b] = s;
             }
@@ -139,10 +150,10 @@ __global__ __launch_bounds__(64 * LD_MAXW, 2) void layer_direct_kernel(const uin
 #pragma unroll
         for (int b = 0; b < NB; ++b) {
             const float2 v0 = cd_unpack<DT>(vv[r][b].x), v1 = cd_unpack<DT>(vv[r][b].y);
-            acc[r][b][0] = ldexpf(acc[r][b][0], et) * v0.x;
-            acc[r][b][1] = ldexpf(acc[r][b][1], et) * v0.y;
-            acc[r][b][2] = ldexpf(acc[r][b][2], et) * v1.x;
-            acc[r][b][3] = ldexpf(acc[r][b][3], et) * v1.y;
+            acc[r][b][0] = ldexpf(acc[r][b][0], eb[r]) * v0.x;
+            acc[r][b][1] = ldexpf(acc[r][b][1], eb[r]) * v0.y;
+            acc[r][b][2] = ldexpf(acc[r][b][2], eb[r]) * v1.x;
+            acc[r][b][3] = ldexpf(acc[r][b][3], eb[r]) * v1.y;
 #pragma unroll
             for (int e = 0; e < 4; ++e) mx = fmaxf(mx, fabsf(acc[r][b][e]));
         }
@@ -205,11 +216,11 @@ __global__ __launch_bounds__(64 * LD_MAXW, 2) void layer_direct_kernel(const uin
                 const uint4 Bh = *(const uint4 *)(gb + r * 2 * P::GS + 256 * a - rho);
                 const uint4 Bl = *(const uint4 *)(gb + r * 2 * P::GS + P::GS + 256 * a - rho);
 #pragma unroll
-                for (int e = 0; a + e < NB; ++e) acc[r][a + e] = cd_mfma<F16>(Ah[e], Bh, acc[r][a + e]);
+                for (int e = 0; a + e < NB; ++e) acc[r][a + e] = cd_mfma(Ah[e], Bh, acc[r][a + e]);
 #pragma unroll
-                for (int e = 0; a + e < NB; ++e) acc[r][a + e] = cd_mfma<F16>(Al[e], Bh, acc[r][a + e]);
+                for (int e = 0; a + e < NB; ++e) acc[r][a + e] = cd_mfma(Al[e], Bh, acc[r][a + e]);
 #pragma unroll
-                for (int e = 0; a + e < NB; ++e) acc[r][a + e] = cd_mfma<F16>(Ah[e], Bl, acc[r][a + e]);
+                for (int e = 0; a + e < NB; ++e) acc[r][a + e] = cd_mfma(Ah[e], Bl, acc[r][a + e]);
             }
     }
 #pragma unroll

@@ -8,7 +8,7 @@ import torch
 
 import oracle
 import workloads
-from tests._util import check, f32dev, to_dev
+from tests._util import check, f32dev, record, to_dev, to_np64
 
 pytestmark = pytest.mark.gpu
 
@@ -62,3 +62,48 @@ def test_layer_direct_tiny_gate(h3, B, L):
     ref = oracle.h3_layer(w.x64, *(W[n][1] for n in "qkvo"), w.shift_C.astype(np.float64), k.astype(np.float64),
                           w.diag_D.astype(np.float64))
     check(out, ref, TOL[dtype], "out", rows=False)
+
+
+@pytest.mark.parametrize("dtype", [workloads.F16, workloads.BF16])
+@pytest.mark.parametrize("L", [256, 512, 1024])
+@pytest.mark.parametrize("which", ["taps", "kernel"])
+def test_layer_direct_cancelling(h3, dtype, L, which):
+    """Q, K, V of ones and an output projection that changes nothing, so that
+    the output is the running sum of the shift taps (the diagonal kernel a
+    unit) or of the diagonal kernel (one tap of 1/3, so that G is no 16-bit
+    value): in threes they sum to nothing, and every third output is the error
+    of what the float32 parameters are held in and of the sums.  fp16 pairs are
+    off by 2^-23, 2^-22 where the low halves' product is left out, at random:
+    2^-24 sqrt(n) of the rms.  The partial sums, of 32 terms that split the
+    threes, wander to sqrt(n / 32) rms and are rounded to 2^-24 of themselves
+    3 n / 32 times: 2^-25 sqrt(3) n / 32, at n = 1024 as much.  Four deviations
+    of the two are below 2^-21 sqrt(n) (the float32 transform: 3.6e-6 at L =
+    1024 with its kernel of rms 0.38; bf16 pieces of a tap: 2^-18 sqrt(n)).  The
+    output is rounded once."""
+    B, d = 3, 128
+    rng = np.random.default_rng(L)
+    n = 63 if which == "taps" else L
+    a = rng.standard_normal((d, n // 3 + 1, 3))
+    a[..., 2] = -a[..., 0] - a[..., 1]
+    p = a.reshape(d, -1)[:, :n].astype(np.float32)
+    if which == "taps":
+        taps, k = p, np.zeros((d, L), np.float32)
+        k[:, 0] = 1.0
+        unit = 1.0
+    else:
+        taps, k = np.full((d, 1), 1 / 3, np.float32), p
+        unit = float(taps[0, 0])
+    x = torch.zeros((B, L, d), device="cuda")
+    x[..., 0] = 1.0
+    one = torch.zeros((d, d), device="cuda")
+    one[0] = 1.0
+    t = torch.float16 if dtype == workloads.F16 else torch.bfloat16
+    out = h3.layer_fwd(x.to(t), *(w.to(t) for w in (one, one, one, torch.eye(d, device="cuda"))), f32dev(taps), None,
+                       f32dev(k), None)
+    torch.cuda.synchronize()
+    ref = np.cumsum(p.astype(np.float64), axis=1)[:, 2::3].T * unit
+    err = np.abs(to_np64(out)[:, 2:n:3] - ref).max()
+    tol = 2.0 ** -21 * np.sqrt(n * np.mean(p.astype(np.float64) ** 2)) * unit
+    tol += np.abs(ref).max() * (2.0 ** -8 if dtype == workloads.BF16 else 2.0 ** -11)
+    record(f"cancelling layer {which} {dtype} L={L}", err=float(err), tol=float(tol))
+    assert err < tol, (err, tol)
