@@ -104,6 +104,12 @@ template <int N> __device__ __forceinline__ double2 sc_zsqr(double2 z) {   // z^
     for (int i = 0; i < N; ++i) z = sc_zmul(z, z);
     return z;
 }
+// rounded to float32, saturating: a growing mode's power must not turn a state
+// that is zero into NaN
+__device__ __forceinline__ float sc_float(double v) {
+    return (float)fmin(fmax(v, -3.4e38), 3.4e38);   // (NaN: inf - inf, saturates too)
+}
+__device__ __forceinline__ float2 sc_float2(double2 z) { return make_float2(sc_float(z.x), sc_float(z.y)); }
 // a x + s
 __device__ __forceinline__ float2 sc_cfma(float2 a, float2 x, float2 s) {
     return make_float2(fmaf(a.x, x.x, fmaf(-a.y, x.y, s.x)), fmaf(a.x, x.y, fmaf(a.y, x.x, s.y)));
@@ -296,12 +302,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void s
     if (on) z = make_double2(a.Abar[2 * ((long)h * a.m + lane)], a.Abar[2 * ((long)h * a.m + lane) + 1]);
     const double2 z64 = sc_zsqr<6>(z), zstep = sc_zsqr<5>(z64);   // a block's and a step's decay
     static_assert(SC_Q == 64 && SC_STEP == 32 * 64, "powers by squaring");
-    const float2 a1 = make_float2((float)z64.x, (float)z64.y);
+    const float2 a1 = sc_float2(z64);
     // what 32 factors a1 leave over of a step's z^2048, added once per step: the
     // rounding of a1 would add up (modes that hardly decay, L = 2^18: the state
     // off by 5e-5, with it 2e-6)
     const double2 z32 = sc_zsqr<5>(make_double2((double)a1.x, (double)a1.y));
-    const float2 da = make_float2((float)(zstep.x - z32.x), (float)(zstep.y - z32.y));
+    const float2 da = sc_float2(make_double2(zstep.x - z32.x, zstep.y - z32.y));
     float2 x = make_float2(0.f, 0.f);
     // the given state.  Of several segments, the launch of the end states alone
     // reads it, and leaves it in the last segment's slot: x_final may be the
@@ -322,8 +328,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void s
         if (a.nseg > 1) x = *given;
         if (sg > 0) {   // the state at the segment's start
             const double2 ps = sc_zpow(zstep, a.seg_steps);
-            const float2 as = make_float2((float)ps.x, (float)ps.y);
-            const float2 al = make_float2((float)(ps.x - as.x), (float)(ps.y - as.y));
+            const float2 as = sc_float2(ps), al = sc_float2(make_double2(ps.x - as.x, ps.y - as.y));
             const float2 *e = a.seg + row * a.nseg * 64 + lane;
 #pragma unroll 8
             for (int s = 0; s < sg; ++s) x = sc_cfma(as, x, sc_cfma(al, x, e[64 * s]));

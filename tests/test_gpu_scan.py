@@ -172,3 +172,17 @@ def test_scan_undamped_modes(h3, B, H, L):
     err = np.linalg.norm(xf[:, sel] - rx) / np.linalg.norm(rx)
     record(f"undamped L={L}", rel_err=float(err))
     assert err < 1.2e-5, err
+
+
+@pytest.mark.parametrize("dtype", [workloads.F16, workloads.BF16])
+@pytest.mark.parametrize("B,H,mag", [(1, 3, 1.06), (1, 3, 2.0), (2, 520, 1.06)])   # four segments; one
+def test_scan_growing_mode_without_input(h3, dtype, B, H, mag):
+    """A mode outside the unit circle whose state is and stays zero (Bbar = 0,
+    no initial state) is as good as absent."""
+    w = workloads.statepass_workload("t", B, H, 4 * 2048, 2048, dtype, seed=3, m=4, dt_lo=1e-3, dt_hi=1e-1)
+    Ab, Bb, C = _params(w)
+    y, xf = _run(h3, w, Ab, Bb, C, w.D, None, 2048)
+    one = np.zeros((H, 1, 2), np.float32)
+    Ab2 = np.concatenate([Ab, one + np.float32([mag, 0.1])], axis=1)
+    y2, xf2 = _run(h3, w, Ab2, np.concatenate([Bb, one], axis=1), np.concatenate([C, one + 1], axis=1), w.D, None, 2048)
+    assert np.array_equal(y, y2) and np.array_equal(xf, xf2[:, :, :4]) and not xf2[:, :, 4].any()
