@@ -12,8 +12,9 @@ from tests._util import check, f32dev, record, to_dev, to_np64
 
 pytestmark = pytest.mark.gpu
 
-# the 16-bit Q, K, V and O between the matrix products, as for the layer tests
-TOL = {workloads.F16: 1e-2, workloads.BF16: 2e-2}
+# Q, K, V, O and the output are rounded to 16 bits: five times half a unit in
+# the last place of the largest value
+TOL = {workloads.F16: 5 * 2.0 ** -12, workloads.BF16: 5 * 2.0 ** -9}
 
 
 @pytest.fixture(scope="module")

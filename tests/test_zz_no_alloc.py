@@ -1,8 +1,10 @@
 """h3_statepass_conv_noalloc (state passing on the library's static scratch,
 for callers that cannot allocate) against h3_statepass_conv on the same
-inputs: two calls in a row, the second smaller and on the other state-passing
-path (the first uses the fused initial-state term, the second the separate
-correction term), so the second runs on scratch the first left behind."""
+inputs: calls in a row, the second and third smaller and on the other
+state-passing path (the first goes through the sequence in one pass, with
+segment states in the scratch; the others form the chunk kernel, its spectrum,
+the chunk states and the correction term there), so that they run on scratch
+the first left behind."""
 import numpy as np
 import pytest
 import torch
@@ -24,13 +26,14 @@ def test_noalloc_matches_workspace_entry_point():
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
     import paper_2212_14052_amd as h3
-    cases = [  # (B, H, L, chunk, dtype, seed): the second is smaller
+    cases = [  # (B, H, L, chunk, dtype, seed): each smaller than the one before
         (2, 256, 65536, 8192, workloads.F16, 1),
-        (1, 64, 16384, 2048, workloads.BF16, 2),
+        (1, 64, 16384, 512, workloads.BF16, 2),
+        (1, 40, 8192, 4096, workloads.F32, 3),
     ]
-    need = [h3.workspace_size(h3.OP_STATEPASS, B, H, L, 64, ch, {workloads.F16: h3.F16, workloads.BF16: h3.BF16}[dt])
-            for B, H, L, ch, dt, _ in cases]
-    assert need[1] < need[0] <= (128 << 20)
+    code = {workloads.F16: h3.F16, workloads.BF16: h3.BF16, workloads.F32: h3.F32}
+    need = [h3.workspace_size(h3.OP_STATEPASS, B, H, L, 64, ch, code[dt]) for B, H, L, ch, dt, _ in cases]
+    assert need[2] < need[1] < need[0] <= (128 << 20)
     for B, H, L, chunk, dtype, seed in cases:
         print(f"noalloc case B={B} H={H} L={L} chunk={chunk} {dtype}", flush=True)
         w = workloads.statepass_workload("t", B, H, L, chunk, dtype, seed=seed, dt_lo=1e-4, dt_hi=1e-2,
