@@ -104,11 +104,12 @@ LayerWs layer_ws(int B, int d, int L) {
     return w;
 }
 
-// Layer heads with d_h > 1: Q, K, V, Kbar, the outer products G and their
-// convolutions S (d_h rows per channel), O token-major, the spectra for the
-// VALU convolution, the transposed weights.
+// Layer heads with d_h > 1: Q, K, V, Kbar, the outer products G that become
+// their convolutions S in place (d_h rows per channel), O token-major, the
+// spectra for the VALU convolution, the transposed weights.  The size is the
+// one that this entry has always answered: once more S, which nothing uses.
 struct HeadsWs {
-    size_t qkv, kbar, g, sv, o_tm, kspec, wt, total;
+    size_t qkv, kbar, g, o_tm, kspec, wt, total;
 };
 HeadsWs heads_ws(int B, int d, int L, int dh) {
     HeadsWs w;
@@ -116,8 +117,7 @@ HeadsWs heads_ws(int B, int d, int L, int dh) {
     w.qkv = 0;
     w.kbar = w.qkv + align_up(3 * act);
     w.g = w.kbar + align_up(act);
-    w.sv = w.g + align_up((size_t)dh * act);
-    w.o_tm = w.sv + align_up((size_t)dh * act);
+    w.o_tm = w.g + 2 * align_up((size_t)dh * act);
     w.kspec = w.o_tm + align_up(act);
     w.wt = w.kspec + align_up((size_t)d * dh * (L + 1) * sizeof(float2));
     w.total = w.wt + (wide_tiles(d, B * L) ? 0 : align_up((size_t)4 * d * d * 2));

@@ -186,10 +186,9 @@ hipError_t launch_direct_h(const ConvArgs &a, const float *k, hipStream_t s) {
     int wgc = (groups + CD_MAXW - 1) / CD_MAXW;
     while ((long)a.H * wgc < 512 && wgc * 2 <= groups) wgc *= 2;
     const int nw = (groups + wgc - 1) / wgc;
+    static_assert(P::lds(CD_MAXW, R) <= 65536 - 1024, "no larger dynamic LDS asked for");
     const size_t lds = P::lds(nw, R);
-    auto fn = conv_direct_kernel<DT, NB, R, CONJ, HEADS>;
-    if (lds > 60000) (void)hipFuncSetAttribute((const void *)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    hipLaunchKernelGGL(fn, dim3((unsigned)(a.H * wgc)), dim3(64 * nw), lds, s, (const uint16_t *)a.u, k, a.D,
+    hipLaunchKernelGGL((conv_direct_kernel<DT, NB, R, CONJ, HEADS>), dim3((unsigned)(a.H * wgc)), dim3(64 * nw), lds, s, (const uint16_t *)a.u, k, a.D,
                        (uint16_t *)a.y, a.B, a.H, wgc, (const uint16_t *)a.heads_v, a.heads_log2);
     return hipGetLastError();
 }

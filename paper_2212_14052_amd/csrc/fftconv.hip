@@ -440,10 +440,10 @@ static hipError_t launch_kgen_n(const ConvArgs &a, const float *k, hipStream_t s
 
 template <int N>
 static hipError_t launch_kgen_dt(const ConvArgs &a, const float *k, hipStream_t s) {
-    switch (a.dtype) {
-        case F32: return launch_kgen_n<N, F32>(a, k, s);
-        case F16: return launch_kgen_n<N, F16>(a, k, s);
-        case BF16: return launch_kgen_n<N, BF16>(a, k, s);
+    if (a.dtype == F32) return launch_kgen_n<N, F32>(a, k, s);
+    if constexpr (N < 512 || N > 4096) {   // L = 256 .. 2048: 16-bit rows have other kernels
+        if (a.dtype == F16) return launch_kgen_n<N, F16>(a, k, s);
+        if (a.dtype == BF16) return launch_kgen_n<N, BF16>(a, k, s);
     }
     return hipErrorInvalidValue;
 }

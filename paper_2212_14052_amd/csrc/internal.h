@@ -56,7 +56,7 @@ struct ConvArgs {
 hipError_t launch_fftconv(const ConvArgs &a, hipStream_t s);
 // The VALU convolution of plain (B, H, L) rows (pair_mode 0, no correction
 // term) with each channel's spectrum computed in the kernel from k (skip term
-// folded into k[0]); L a power of two in [16, 4096].
+// folded into k[0]); L a power of two in [16, 4096], for 16-bit rows [16, 128] or 4096.
 bool fftconv_kgen_supported(int L);
 hipError_t launch_fftconv_kgen(const ConvArgs &a, const float *k, hipStream_t s);
 // The same for 16-bit rows by direct summation on the matrix cores, L 256,

@@ -142,91 +142,6 @@ __global__ __launch_bounds__(256) void gemm_nt_kernel(const uint16_t *A, const u
                                 n0 + wn * 64 + j * 32 + (lane & 31), N, d, L);
 }
 
-// ------------------------------------------------------ GEMM, large tiles ---
-// Same contract as gemm_nt_kernel for M, N % 256 == 0 and K % 64 == 0.
-// Block tile 256 x 256 x 64, 8 waves as 2 (M) x 4 (N), each wave 128 x 64 =
-// 4 x 2 tiles of 32x32x16 MFMA (fp32 accumulators, 128 per lane).  LDS holds
-// two stages of A and B (rows padded to 72 elements: 16-byte fragment reads
-// of 8 consecutive rows hit 8 different bank groups); the next stage is
-// fetched into registers while the current one is multiplied, so one barrier
-// per K step suffices.  Tiles run in the grouped order of gemm_tile.
-constexpr int G2_M = 256, G2_N = 256, G2_K = 64, G2_LD = G2_K + 8, G2_T = 512;
-
-template <int DT, int OUT>
-__global__ __launch_bounds__(G2_T) void gemm_nt_256(const uint16_t *A, const uint16_t *Bt, uint16_t *C,
-                                                    int M, int N, int K, int d, int L) {
-    extern __shared__ __attribute__((aligned(16))) uint16_t g2_lds[];
-    uint16_t *As = g2_lds;                          // [2][256][72]
-    uint16_t *Bs = g2_lds + 2 * G2_M * G2_LD;       // [2][256][72]
-    int tm, tn;
-    gemm_tile(M / G2_M, N / G2_N, tm, tn);
-    const int m0 = tm * G2_M, n0 = tn * G2_N;
-    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
-    const int wm = w >> 2, wn = w & 3;
-    // loader mapping: thread -> rows t / 8 + 64 i, 16-byte column chunk (t % 8) * 8
-    const int lr = t >> 3, lk = (t & 7) * 8;
-    const uint16_t *ga = A + (long)(m0 + lr) * K + lk, *gb = Bt + (long)(n0 + lr) * K + lk;
-    const long g64 = 64L * K;
-    uint16_t *la = As + lr * G2_LD + lk, *lb = Bs + lr * G2_LD + lk;
-    f32x16_t acc[4][2];
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
-
-    uint4 a0 = *(const uint4 *)(ga), a1 = *(const uint4 *)(ga + g64), a2 = *(const uint4 *)(ga + 2 * g64),
-          a3 = *(const uint4 *)(ga + 3 * g64);
-    uint4 b0 = *(const uint4 *)(gb), b1 = *(const uint4 *)(gb + g64), b2 = *(const uint4 *)(gb + 2 * g64),
-          b3 = *(const uint4 *)(gb + 3 * g64);
-    constexpr int S64 = 64 * G2_LD, STAGE = G2_M * G2_LD;
-    *(uint4 *)(la) = a0; *(uint4 *)(la + S64) = a1; *(uint4 *)(la + 2 * S64) = a2; *(uint4 *)(la + 3 * S64) = a3;
-    *(uint4 *)(lb) = b0; *(uint4 *)(lb + S64) = b1; *(uint4 *)(lb + 2 * S64) = b2; *(uint4 *)(lb + 3 * S64) = b3;
-    __syncthreads();
-    const int nk = K / G2_K;
-    for (int kt = 0; kt < nk; ++kt) {
-        const int buf = kt & 1;
-        const bool more = kt + 1 < nk;
-        if (more) {
-            const int k1 = (kt + 1) * G2_K;
-            a0 = *(const uint4 *)(ga + k1); a1 = *(const uint4 *)(ga + g64 + k1);
-            a2 = *(const uint4 *)(ga + 2 * g64 + k1); a3 = *(const uint4 *)(ga + 3 * g64 + k1);
-            b0 = *(const uint4 *)(gb + k1); b1 = *(const uint4 *)(gb + g64 + k1);
-            b2 = *(const uint4 *)(gb + 2 * g64 + k1); b3 = *(const uint4 *)(gb + 3 * g64 + k1);
-        }
-        const uint16_t *as = As + buf * STAGE, *bs = Bs + buf * STAGE;
-#pragma unroll
-        for (int ks = 0; ks < G2_K / 16; ++ks) {
-            const int kk = ks * 16 + 8 * (lane >> 5);
-            uint4 af[4], bf[2];
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-                af[i] = *(const uint4 *)(as + (wm * 128 + i * 32 + (lane & 31)) * G2_LD + kk);
-#pragma unroll
-            for (int j = 0; j < 2; ++j)
-                bf[j] = *(const uint4 *)(bs + (wn * 64 + j * 32 + (lane & 31)) * G2_LD + kk);
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 2; ++j) acc[i][j] = Mfma<DT>::run(af[i], bf[j], acc[i][j]);
-        }
-        if (more) {
-            uint16_t *sa = la + (buf ^ 1) * STAGE, *sb = lb + (buf ^ 1) * STAGE;
-            *(uint4 *)(sa) = a0; *(uint4 *)(sa + S64) = a1; *(uint4 *)(sa + 2 * S64) = a2; *(uint4 *)(sa + 3 * S64) = a3;
-            *(uint4 *)(sb) = b0; *(uint4 *)(sb + S64) = b1; *(uint4 *)(sb + 2 * S64) = b2; *(uint4 *)(sb + 3 * S64) = b3;
-        }
-        __syncthreads();
-    }
-    // epilogue: lane holds column (lane & 31) and rows 8(e/4) + 4(lane/32) + e%4
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-            store_tile<DT, OUT>(C, acc[i][j], m0 + wm * 128 + i * 32 + 4 * (lane >> 5),
-                                n0 + wn * 64 + j * 32 + (lane & 31), N, d, L);
-}
-
 // ------------------------------------------- GEMM, TW x 256 weight tiles ---
 // C = W^T . X^T with the weights W (K, ldw) as stored (input features along
 // the rows, output features contiguous: the projections of Algorithm 1 as
@@ -925,15 +840,8 @@ hipError_t launch_shift_gate(const void *k, const void *v, const float *shift_C,
 template <int DT, int OUT>
 static hipError_t launch_gemm_t(const void *A, const void *Bt, void *C, int M, int N, int K, int d,
                                 int L, hipStream_t s) {
-    if (M % G2_M == 0 && N % G2_N == 0 && K % G2_K == 0) {
-        const size_t lds = (size_t)2 * (G2_M + G2_N) * G2_LD * sizeof(uint16_t);
-        (void)hipFuncSetAttribute((const void *)gemm_nt_256<DT, OUT>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        hipLaunchKernelGGL((gemm_nt_256<DT, OUT>), dim3((M / G2_M) * (N / G2_N)), dim3(G2_T), lds, s,
-                           (const uint16_t *)A, (const uint16_t *)Bt, (uint16_t *)C, M, N, K, d, L);
-    } else {
-        hipLaunchKernelGGL((gemm_nt_kernel<DT, OUT>), dim3((M / GB_M) * (N / GB_N)), dim3(256), 0, s,
-                           (const uint16_t *)A, (const uint16_t *)Bt, (uint16_t *)C, M, N, K, d, L);
-    }
+    hipLaunchKernelGGL((gemm_nt_kernel<DT, OUT>), dim3((M / GB_M) * (N / GB_N)), dim3(256), 0, s, (const uint16_t *)A,
+                       (const uint16_t *)Bt, (uint16_t *)C, M, N, K, d, L);
     return hipGetLastError();
 }
 
@@ -1037,17 +945,12 @@ hipError_t launch_layer_mid(const void *q, const void *k, const void *v, const f
     case LL:                                                                                    \
         return launch_mid_dt<2 * LL>(dtype, q, k, v, shift_C, shift_D, m_s, Kspec, diag_D, B, d, \
                                      o, s);
-    switch (L) {
+    switch (L) {   // the lengths that have no kernel of their own
         H3_MID_CASE(16)
         H3_MID_CASE(32)
         H3_MID_CASE(64)
         H3_MID_CASE(128)
-        H3_MID_CASE(256)
-        H3_MID_CASE(512)
-        H3_MID_CASE(1024)
-        H3_MID_CASE(2048)
         H3_MID_CASE(4096)
-        H3_MID_CASE(8192)
     }
 #undef H3_MID_CASE
     return hipErrorInvalidValue;
