@@ -98,16 +98,26 @@ template <int W> __device__ __forceinline__ uint32_t group_max(uint32_t x) {
     return x;
 }
 
+// Two floats rounded to 16 bits (nearest even) in one word, lo in its low half.
+template <int DT> __device__ __forceinline__ uint32_t pack_16x2(float lo, float hi) {
+    typedef float f2 __attribute__((ext_vector_type(2)));
+    const f2 v = {lo, hi};
+    if constexpr (DT == BF16) {
+        typedef __bf16 b2 __attribute__((ext_vector_type(2)));
+        return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, b2));
+    } else {
+        typedef _Float16 h2 __attribute__((ext_vector_type(2)));
+        return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, h2));
+    }
+}
+
 // Products of two 16-bit pairs, rounded once.
 template <int DT> __device__ __forceinline__ uint32_t mul_16x2(uint32_t x, uint32_t z) {
     if constexpr (DT == F16) {
         typedef _Float16 h2 __attribute__((ext_vector_type(2)));
         return __builtin_bit_cast(uint32_t, __builtin_bit_cast(h2, x) * __builtin_bit_cast(h2, z));
     } else {
-        typedef float f2 __attribute__((ext_vector_type(2)));
-        typedef __bf16 b2 __attribute__((ext_vector_type(2)));
-        const f2 p = {bf16_to_f32(x & 0xffffu) * bf16_to_f32(z & 0xffffu), bf16_to_f32(x >> 16) * bf16_to_f32(z >> 16)};
-        return __builtin_bit_cast(uint32_t, __builtin_convertvector(p, b2));
+        return pack_16x2<BF16>(bf16_to_f32(x & 0xffffu) * bf16_to_f32(z & 0xffffu), bf16_to_f32(x >> 16) * bf16_to_f32(z >> 16));
     }
 }
 

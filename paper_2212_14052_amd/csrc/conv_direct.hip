@@ -174,8 +174,8 @@ __global__ __launch_bounds__(64 * CD_MAXW, 4) void conv_direct_kernel(const uint
             uint16_t *yr = y + ((long)(b0 + r) * H + h) * L + 16 * i16 + 4 * g;
 #pragma unroll
             for (int b = 0; b < NB; ++b)
-                *(uint2 *)(yr + 256 * b) = make_uint2(cd_pack<DT>(ldexpf(acc[r][b][0], er[r]), ldexpf(acc[r][b][1], er[r])),
-                                                      cd_pack<DT>(ldexpf(acc[r][b][2], er[r]), ldexpf(acc[r][b][3], er[r])));
+                *(uint2 *)(yr + 256 * b) = make_uint2(pack_16x2<DT>(ldexpf(acc[r][b][0], er[r]), ldexpf(acc[r][b][1], er[r])),
+                                                      pack_16x2<DT>(ldexpf(acc[r][b][2], er[r]), ldexpf(acc[r][b][3], er[r])));
         }
 }
 

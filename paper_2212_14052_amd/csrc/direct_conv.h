@@ -1,4 +1,4 @@
-// Shared by the kernels that convolve 16-bit rows by direct summation on the
+// Shared by the kernels that convolve or correlate 16-bit rows by direct summation on the
 // matrix cores: 16x16x32 products, 16-bit pairs, bf16 rows as scaled fp16, and
 // operands whose elements start at any 16-bit offset of an LDS array.
 #pragma once
@@ -7,20 +7,11 @@
 namespace h3 {
 
 typedef _Float16 cd_h8 __attribute__((ext_vector_type(8)));
-typedef _Float16 cd_h2 __attribute__((ext_vector_type(2)));
-typedef __bf16 cd_b2 __attribute__((ext_vector_type(2)));
 typedef unsigned cd_u4 __attribute__((ext_vector_type(4)));
-typedef float cd_f2 __attribute__((ext_vector_type(2)));
 typedef float cd_f4 __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ cd_f4 cd_mfma(uint4 a, uint4 b, cd_f4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(cd_h8, a), __builtin_bit_cast(cd_h8, b), c, 0, 0, 0);
-}
-template <int DT>
-__device__ __forceinline__ uint32_t cd_pack(float lo, float hi) {
-    const cd_f2 v = {lo, hi};
-    if constexpr (DT == BF16) return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, cd_b2));
-    else return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, cd_h2));
 }
 template <int DT>
 __device__ __forceinline__ float cd_value(uint16_t v) { return DT == BF16 ? bf16_to_f32(v) : f16_to_f32(v); }
@@ -101,7 +92,7 @@ __device__ __forceinline__ int cd_bf16_to_f16(cd_u4 (&x)[P]) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const float2 v = cd_unpack<BF16>(x[p][i]);
-            x[p][i] = finite ? cd_pack<F16>(ldexpf(v.x, -e), ldexpf(v.y, -e)) : 0x7e007e00u;
+            x[p][i] = finite ? pack_16x2<F16>(ldexpf(v.x, -e), ldexpf(v.y, -e)) : 0x7e007e00u;
         }
     return e;
 }

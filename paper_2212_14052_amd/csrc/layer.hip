@@ -185,18 +185,6 @@ typedef __attribute__((address_space(3))) void lds_void;
 typedef short gw_v4s __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) gw_v4s lds_v4s;
 
-template <int DT>
-__device__ __forceinline__ uint32_t gw_pack(float lo, float hi) {
-    typedef float f2 __attribute__((ext_vector_type(2)));
-    const f2 v = {lo, hi};
-    if constexpr (DT == BF16) {
-        typedef __bf16 b2 __attribute__((ext_vector_type(2)));
-        return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, b2));
-    } else {
-        typedef _Float16 h2 __attribute__((ext_vector_type(2)));
-        return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, h2));
-    }
-}
 __device__ __forceinline__ int gw_xoff(int row, int chunk) { return row * 64 + ((chunk ^ ((row >> 2) & 3)) << 4); }
 
 template <int TW, int SS, bool XKM, int NS> struct GwShape {
@@ -389,8 +377,8 @@ __global__ __launch_bounds__(GW_T) __attribute__((amdgpu_waves_per_eu(NS == 3 ? 
                                        : eb + (x + (lane & 31)) * EP + 2 * (f + 4 * (lane >> 5));
 #pragma unroll
                     for (int e = 0; e < 4; ++e)
-                        *(uint2 *)(p + 16 * e) = make_uint2(gw_pack<DT>(acc[i][j][4 * e], acc[i][j][4 * e + 1]),
-                                                            gw_pack<DT>(acc[i][j][4 * e + 2], acc[i][j][4 * e + 3]));
+                        *(uint2 *)(p + 16 * e) = make_uint2(pack_16x2<DT>(acc[i][j][4 * e], acc[i][j][4 * e + 1]),
+                                                            pack_16x2<DT>(acc[i][j][4 * e + 2], acc[i][j][4 * e + 3]));
                 }
         }
         __syncthreads();

@@ -174,11 +174,11 @@ __global__ __launch_bounds__(64 * LD_MAXW, 2) void layer_direct_kernel(const uin
             // two alone leaves float32 for rows below 2^-113)
 #pragma unroll
             for (int e = 0; e < 4; ++e) x[e] = ldexpf(acc[r][b][e], -eg[r]);
-            const uint2 hi = make_uint2(cd_pack<F16>(x[0], x[1]), cd_pack<F16>(x[2], x[3]));
+            const uint2 hi = make_uint2(pack_16x2<F16>(x[0], x[1]), pack_16x2<F16>(x[2], x[3]));
             const float2 h0 = cd_unpack<F16>(hi.x), h1 = cd_unpack<F16>(hi.y);
             y[0] = x[0] - h0.x; y[1] = x[1] - h0.y; y[2] = x[2] - h1.x; y[3] = x[3] - h1.y;
             *(uint2 *)(gh + 240 + 256 * b + lo4) = hi;
-            *(uint2 *)(gl + 240 + 256 * b + lo4) = make_uint2(cd_pack<F16>(y[0], y[1]), cd_pack<F16>(y[2], y[3]));
+            *(uint2 *)(gl + 240 + 256 * b + lo4) = make_uint2(pack_16x2<F16>(y[0], y[1]), pack_16x2<F16>(y[2], y[3]));
         }
         if (lane < 30) {
             *(uint4 *)(gh + 8 * lane) = make_uint4(0, 0, 0, 0);
@@ -231,8 +231,8 @@ __global__ __launch_bounds__(64 * LD_MAXW, 2) void layer_direct_kernel(const uin
         for (int b = 0; b < NB; ++b) {
             const float2 q0 = cd_unpack<DT>(vv[r][b].x), q1 = cd_unpack<DT>(vv[r][b].y);
             *(uint2 *)(o + ro[r] + 256 * b + lo4) =
-                make_uint2(cd_pack<DT>(ldexpf(acc[r][b][0], eo) * q0.x, ldexpf(acc[r][b][1], eo) * q0.y),
-                           cd_pack<DT>(ldexpf(acc[r][b][2], eo) * q1.x, ldexpf(acc[r][b][3], eo) * q1.y));
+                make_uint2(pack_16x2<DT>(ldexpf(acc[r][b][0], eo) * q0.x, ldexpf(acc[r][b][1], eo) * q0.y),
+                           pack_16x2<DT>(ldexpf(acc[r][b][2], eo) * q1.x, ldexpf(acc[r][b][3], eo) * q1.y));
         }
     }
 }

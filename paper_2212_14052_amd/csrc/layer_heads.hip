@@ -18,18 +18,6 @@ __device__ __forceinline__ uint16_t st16(float v) {
     if constexpr (DT == BF16) return __builtin_bit_cast(uint16_t, (__bf16)v);
     else return f32_to_f16(v);
 }
-template <int DT>
-__device__ __forceinline__ uint32_t st16x2(float lo, float hi) {
-    typedef float f2 __attribute__((ext_vector_type(2)));
-    const f2 v = {lo, hi};
-    if constexpr (DT == BF16) {
-        typedef __bf16 b2 __attribute__((ext_vector_type(2)));
-        return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, b2));
-    } else {
-        typedef _Float16 h2 __attribute__((ext_vector_type(2)));
-        return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, h2));
-    }
-}
 
 // G[b, (h d_h + i) d_h + j, t] = Kbar[b, h d_h + i, t] V[b, h d_h + j, t], one
 // rounding; Kbar, V (B, d, L) channel-major, G (B, d d_h, L).  One thread per
@@ -62,7 +50,7 @@ __global__ __launch_bounds__(256) void heads_expand_kernel(const uint16_t *kbar,
             uint32_t o4[4];
 #pragma unroll
             for (int e = 0; e < 4; ++e)
-                o4[e] = st16x2<DT>(kf[i][2 * e] * vf[j][2 * e], kf[i][2 * e + 1] * vf[j][2 * e + 1]);
+                o4[e] = pack_16x2<DT>(kf[i][2 * e] * vf[j][2 * e], kf[i][2 * e + 1] * vf[j][2 * e + 1]);
             const long row = (((long)b * nh + h) * DH * DH + i * DH + j) * L + t;
             *(uint4 *)(g + row) = make_uint4(o4[0], o4[1], o4[2], o4[3]);
         }

@@ -42,8 +42,6 @@ namespace {
 typedef _Float16 sc_h8 __attribute__((ext_vector_type(8)));
 typedef _Float16 sc_h2 __attribute__((ext_vector_type(2)));
 typedef __bf16 sc_b8 __attribute__((ext_vector_type(8)));
-typedef __bf16 sc_b2 __attribute__((ext_vector_type(2)));
-typedef float sc_f2 __attribute__((ext_vector_type(2)));
 typedef float sc_f16 __attribute__((ext_vector_type(16)));
 
 constexpr int SC_Q = 64;             // inputs per block
@@ -63,12 +61,6 @@ __device__ __forceinline__ sc_f16 sc_mfma(uint4 a, uint4 b, sc_f16 c) {
         return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(sc_h8, a), __builtin_bit_cast(sc_h8, b), c, 0, 0, 0);
 }
 template <int DT>
-__device__ __forceinline__ uint32_t sc_pack(float lo, float hi) {
-    const sc_f2 v = {lo, hi};
-    if constexpr (DT == BF16) return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, sc_b2));
-    else return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, sc_h2));
-}
-template <int DT>
 __device__ __forceinline__ float2 sc_unpack(uint32_t w) {
     if constexpr (DT == BF16) return make_float2(__uint_as_float(w << 16), __uint_as_float(w & 0xffff0000u));
     const sc_h2 h = __builtin_bit_cast(sc_h2, w);
@@ -80,9 +72,9 @@ __device__ __forceinline__ uint4 sc_pack8(const float (&v)[8], uint4 *lo) {
     uint32_t hi[4], lw[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        hi[i] = sc_pack<DT>(v[2 * i], v[2 * i + 1]);
+        hi[i] = pack_16x2<DT>(v[2 * i], v[2 * i + 1]);
         const float2 r = sc_unpack<DT>(hi[i]);
-        lw[i] = sc_pack<DT>(v[2 * i] - r.x, v[2 * i + 1] - r.y);
+        lw[i] = pack_16x2<DT>(v[2 * i] - r.x, v[2 * i + 1] - r.y);
     }
     if (lo) *lo = make_uint4(lw[0], lw[1], lw[2], lw[3]);
     return make_uint4(hi[0], hi[1], hi[2], hi[3]);
@@ -437,7 +429,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void s
 #pragma unroll
             for (int n = 0; n < 32; ++n) {
                 const int r = 4 * (n >> 3) + (n & 3), t = (n >> 2) & 1;
-                xw[SC_PITCH * n + lane] = sc_pack<F16>(sx[t][0][r] * f, sx[t][1][r] * f);
+                xw[SC_PITCH * n + lane] = pack_16x2<F16>(sx[t][0][r] * f, sx[t][1][r] * f);
             }
             settle();
             sc_f16 yx[2] = {zero, zero};
@@ -454,8 +446,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void s
                 float o[8];
 #pragma unroll
                 for (int r = 0; r < 8; ++r) o[r] = fmaf(yx[q >> 1][8 * (q & 1) + r], fx, yt[q >> 1][8 * (q & 1) + r] * ft);
-                *(uint4 *)(frags + 32 * q) = make_uint4(sc_pack<DT>(o[0], o[1]), sc_pack<DT>(o[2], o[3]),
-                                                        sc_pack<DT>(o[4], o[5]), sc_pack<DT>(o[6], o[7]));
+                *(uint4 *)(frags + 32 * q) = make_uint4(pack_16x2<DT>(o[0], o[1]), pack_16x2<DT>(o[2], o[3]),
+                                                        pack_16x2<DT>(o[4], o[5]), pack_16x2<DT>(o[6], o[7]));
             }
             settle();
 #pragma unroll

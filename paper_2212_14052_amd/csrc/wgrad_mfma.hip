@@ -37,7 +37,7 @@
 // the fp16 transform kernel with an error of 1e-3): B = 8, H = 768, L = 1024:
 // 60 -> 15; L = 2048: 44 -> 31; B = 4, H = 400, L = 4096: 88 -> 35; B = 3, H =
 // 400, L = 8192: 321 -> 100.
-#include "common.h"
+#include "direct_conv.h"
 #include "internal.h"
 
 namespace h3 {
@@ -184,12 +184,7 @@ __global__ __launch_bounds__(WG_NT, (WgPlan<NB, CS>::WPE)) void wgrad_direct_ker
             for (int a0 = 0; a0 < NB; a0 += P::AB) {
                 uint4 A[P::AB];
 #pragma unroll
-                for (int a = 0; a < P::AB; ++a) {
-                    const uint32_t *s = up + 128 * (a0 + a);
-                    const uint32_t q0 = s[0], q1 = s[1], q2 = s[2], q3 = s[3], q4 = s[4];
-                    A[a] = make_uint4(__builtin_amdgcn_alignbit(q1, q0, sh), __builtin_amdgcn_alignbit(q2, q1, sh),
-                                      __builtin_amdgcn_alignbit(q3, q2, sh), __builtin_amdgcn_alignbit(q4, q3, sh));
-                }
+                for (int a = 0; a < P::AB; ++a) A[a] = cd_frag(up + 128 * (a0 + a), sh);
 #pragma unroll
                 for (int b = a0; b < NB; ++b) {
                     const uint4 Bv = *(const uint4 *)(dp + 256 * b);
