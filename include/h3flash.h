@@ -122,8 +122,10 @@ int h3_fftconv_spectral(const void *u, const float *Kspec, const float *D, void 
  * SSM given in discrete form, over sequences longer than the fused limit:
  * the sequence is cut into L/chunk chunks; each chunk is a fused FFT
  * convolution with the length-`chunk` kernel plus the contribution of the
- * state carried in, and the state is advanced chunk to chunk.  The result is
- * that of the recurrence (Proposition 2):
+ * state carried in, and the state is advanced chunk to chunk.  16-bit rows at
+ * chunk 2048, 8192 and 16384 go through in one pass of blocks of the kernel's
+ * own length (64).  The result does not depend on the chunk; it is that of the
+ * recurrence (Proposition 2):
  *   x_t = Abar x_{t-1} + Bbar u_t (per mode),  y_t = 2 Re(C . x_t) + D u_t,
  *   x_{-1} = x0,  x_final = x_{L-1}.
  *   u, y        (B, H, L) of `dtype`; must not overlap.

@@ -608,7 +608,9 @@ hipError_t launch_fftconv_wave(const ConvArgs &a, const float *k, hipStream_t s)
         // -> 20 us at H = 768)
         const dim3 grid2((a.H + 1) / 2);
         const bool ct = grid2.x >= 512;
-        if (a.heads_v) {   // (the compact table's at every size: one instance less)
+        // (outer-product rows take the compact table at every size: the whole
+        // layer the same within 0.3 % with either, d d_h = 256 .. 1536, B = 1 .. 4)
+        if (a.heads_v) {
             if (a.dtype == F16)
                 hipLaunchKernelGGL((fftconv_wave4096_kernel<F16, 2, true, false, true>), grid2, block, 0, s, a, k, 1, pairs_per_ch);
             else

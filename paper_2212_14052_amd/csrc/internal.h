@@ -103,7 +103,7 @@ hipError_t launch_state_scan(const float *Abar, const float *C, const float *x0,
 hipError_t launch_state_correction(const float *Abar, const float2 *corr_W, int B, int H, int m,
                                    int chunk, int nchunk, float *corr, hipStream_t s);
 // State passing in one pass on the matrix cores (16-bit I/O, chunk 2048, 8192
-// or 16384; L a multiple of 1024, m <= 64).  ws: scratch for segment states;
+// or 16384; L a multiple of 2048, m <= 64).  ws: scratch for segment states;
 // what it holds bounds the segments per row.
 bool ssm_scan_supported(int chunk, int dtype);
 hipError_t launch_ssm_scan(const void *u, const float *Abar, const float *Bbar, const float *C, const float *D,

@@ -148,18 +148,20 @@ __global__ __launch_bounds__(256) void gemm_nt_kernel(const uint16_t *A, const u
 // written, Q = x W_Q) and the activations X (Nx, K) K-contiguous, 16-bit, fp32
 // accumulation.  Mw output features: for OUT 1 the three projections Q, K, V
 // (Mw = 3 d, weight tile rows w0 .. from W_{w0 / d}), for OUT 0 one (Mw = d).
-// Block tile TW (output features: 320 or 256) x 256 (activation rows) x 32.
+// Block tile TW (output features: 320, 256 or 128) x 256 (activation rows) x 32.
 // At d = 2560 (a multiple of 320) the fused Q/K/V projection and the output
 // projection over Nx = B L = 8192 tokens are 768 and 256 tiles of 320 x 256:
 // whole rounds of the 256 CUs, where 256 x 256 tiles leave the last round a
 // quarter full.  Eight waves, 2 (weight) x 4 (activation), each (TW / 2) x 64
 // = (TW / 64) x 2 tiles of 32x32x16 MFMA (up to 160 fp32 accumulators per
-// lane, two waves per SIMD).
+// lane, two waves per SIMD; the 128-wide tile needs 64, four waves per SIMD).
 // Operands reach LDS without passing through registers: each wave copies
 // 1 KB slices of a stage (64 lanes x 16 bytes, lane i to byte 16 i of the
-// slice) with global_load_lds_dwordx4, four stages deep (copies run three K
-// steps ahead; a stage is waited for with vmcnt and one barrier per K step,
-// which also orders the refill of the buffer read in the step before).
+// slice) with global_load_lds_dwordx4, NS stages deep: four, so that copies run
+// three K steps ahead, or three for the 128-wide tile with row-major
+// activations, so that two workgroups fit a CU.  A stage is waited for with
+// vmcnt and one barrier per K step, which also orders the refill of the buffer
+// read in the step before.
 // A stage holds
 //  - the weight tile as stored: 32 rows (k) of TW output features, row pitch
 //    WP = 2 TW + 64 bytes (the last 64 bytes of a row are filled with
@@ -188,14 +190,14 @@ typedef __attribute__((address_space(3))) gw_v4s lds_v4s;
 __device__ __forceinline__ int gw_xoff(int row, int chunk) { return row * 64 + ((chunk ^ ((row >> 2) & 3)) << 4); }
 
 template <int TW, int SS, bool XKM, int NS> struct GwShape {
-    static constexpr int WP = 2 * TW + 64;            // weight row pitch, bytes (704 or 576)
+    static constexpr int WP = 2 * TW + 64;            // weight row pitch, bytes (704, 576 or 320)
     static constexpr int WB = GW_K * WP;              // weight part of a stage, bytes
-    static constexpr int WS = WB / 1024;              // its slices (22 or 18)
+    static constexpr int WS = WB / 1024;              // its slices (22, 18 or 10)
     static constexpr int XP = 2 * GW_X + 64;          // K-major activation row pitch, bytes (576)
     static constexpr int XB = XKM ? GW_K * XP : GW_X * 64;   // activation part of a stage, bytes
     static constexpr int XS = XB / 1024;              // its slices (18 or 16)
     static constexpr int SLICES = WS + XS;
-    static constexpr int NSL = (SLICES + 7) / 8;      // copies per wave per step (5)
+    static constexpr int NSL = (SLICES + 7) / 8;      // copies per wave per step (4 or 5)
     static constexpr int STAGE_B = WB + XB;           // bytes per stage
     static constexpr int TI = TW / 64;                // weight-side MFMA tiles per wave
     static_assert(WB % 1024 == 0 && (WP % 256 == 64 || WP % 256 == 192), "weight stage layout");
