@@ -200,6 +200,9 @@ template <int TW, int SS, bool XKM, int NS> struct GwShape {
     static constexpr int NSL = (SLICES + 7) / 8;      // copies per wave per step (4 or 5)
     static constexpr int STAGE_B = WB + XB;           // bytes per stage
     static constexpr int TI = TW / 64;                // weight-side MFMA tiles per wave
+    // K steps between two moves of the operands' bases (Q/K/V, us: 271.7 with
+    // 256 and 275 with 1 at 320 x 256 tiles, d = 2560; 44.5 and 43.7 at 128 x 256, d = 768)
+    static constexpr int REB = TW == 128 ? 1 : 256;
     static_assert(WB % 1024 == 0 && (WP % 256 == 64 || WP % 256 == 192), "weight stage layout");
     // LDS bytes: the stages, and a 1 KB slot that takes the copies of waves
     // with fewer slices (never read), so every wave issues NSL per step
@@ -234,9 +237,10 @@ __global__ __launch_bounds__(GW_T) __attribute__((amdgpu_waves_per_eu(NS == 3 ? 
     const int ww = wv >> 2, wx = wv & 3;
     // this wave's slices q = wv + 8 s, s < NSL (a wave past the last slice
     // copies slice wv again into the never-read slot), of W_jq for q < WS, of X
-    // after: a 64-bit base in scalar registers (X may exceed 4 GiB), the tile's
-    // at K step 0, that moves on by 32 rows of W (32 ldw) or 32 columns of X per
-    // step, and the lane's byte offset from it
+    // after: a 64-bit base in scalar registers, the tile's at K step 0 (X may
+    // exceed 4 GiB), the lane's byte offset from it, and the bytes of a K step, 32
+    // rows of W (32 ldw) or 32 columns of X.  Every REB steps the base moves on,
+    // so that 32 bits do for the rest of any operand
     const int wvu = __builtin_amdgcn_readfirstlane(wv);   // the wave index, in a scalar register
     const char *src[S::NSL];
     uint32_t step[S::NSL], soff[S::NSL];
@@ -274,7 +278,11 @@ __global__ __launch_bounds__(GW_T) __attribute__((amdgpu_waves_per_eu(NS == 3 ? 
     // the last step they read it again and only keep the count per step fixed
     auto issue = [&](int kt) {
         const uint32_t st = lds0 + (uint32_t)((kt % NS) * S::STAGE_B);
-        const bool more = kt + 1 < nk;
+        const uint32_t ks = (uint32_t)min(kt, nk - 1) % S::REB;
+        if (kt > 0 && kt < nk && ks == 0) {
+#pragma unroll
+            for (int sl = 0; sl < S::NSL; ++sl) src[sl] += (uint64_t)S::REB * step[sl];
+        }
 #pragma unroll
         for (int sl = 0; sl < S::NSL; ++sl) {
             const int q = wvu + 8 * sl;
@@ -282,9 +290,8 @@ __global__ __launch_bounds__(GW_T) __attribute__((amdgpu_waves_per_eu(NS == 3 ? 
             const uint32_t la = real ? st + (uint32_t)q * 1024 : lds0 + (uint32_t)(NS * S::STAGE_B);
             asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, %2"
                          :
-                         : "v"(soff[sl]), "s"(la), "s"(src[sl])
+                         : "v"(soff[sl] + ks * step[sl]), "s"(la), "s"(src[sl])
                          : "memory", "m0");
-            if (more) src[sl] += step[sl];
         }
     };
     f32x16_t acc[S::TI][2];

@@ -1,6 +1,5 @@
-"""A layer whose activations pass 4 GiB (B L d > 2^31 values of 16 bits), each
-way the projections read them: the last two sequences against the same two in
-a call of their own, all others zero."""
+"""The projections' addresses: activations past 4 GiB (B L d > 2^31 values of 16
+bits), each way they are read, and sums of more than 256 steps, each tile width."""
 import pytest
 import torch
 
@@ -13,6 +12,8 @@ pytestmark = pytest.mark.gpu
     (342, 16384, 384),    # O token-major
 ])
 def test_layer_past_4gib(B, L, d):
+    """The last two sequences against the same two in a call of their own, all
+    others zero."""
     import paper_2212_14052_amd as h3
     need = h3.workspace_size(h3.OP_LAYER, B, d, L, 4, 0, h3.F16) + 4 * B * L * d
     if torch.cuda.mem_get_info()[0] < need + (4 << 30):
@@ -37,3 +38,24 @@ def test_layer_past_4gib(B, L, d):
     del x, out
     torch.cuda.empty_cache()
     assert e < 2e-3, e
+
+
+@pytest.mark.parametrize("B,d", [(1, 8320), (5, 8448), (19, 8320)])   # weight tiles 128, 256 and 320 wide
+def test_layer_many_steps(B, d):
+    """More than 256 steps along the projections' sums: the operands' bases
+    move on.  Against float64, the sequence mixing a unit (one tap, a unit
+    kernel): out = (Q K V) Wo."""
+    import paper_2212_14052_amd as h3
+    L = 256
+    g = torch.Generator(device="cuda")
+    g.manual_seed(d)
+    W = [torch.randn((d, d), generator=g, device="cuda", dtype=torch.float16) * d ** -0.5 for _ in range(4)]
+    x = torch.randn((B, L, d), generator=g, device="cuda", dtype=torch.float16)
+    k = torch.zeros((d, L), device="cuda")
+    k[:, 0] = 1.0
+    out = h3.layer_fwd(x, *W, torch.ones((d, 1), device="cuda"), None, k, None)
+    q, kk, v = (x.double() @ w.double() for w in W[:3])
+    ref = (q * kk * v) @ W[3].double()
+    # Q, K, V, O and the output rounded to 2^-12 of themselves on average
+    e = float((out.double() - ref).norm() / ref.norm())
+    assert e < 5 * 2.0 ** -12, e
