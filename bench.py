@@ -57,7 +57,7 @@ COUNTERS = {
                  "sha": "eb3b4c66d980682a", "fetch_kib": 15626.5, "write_kib": 24576.0,
                  "valu": 6038016, "mfma": 614400, "mfma_busy": 0.200},
     "cfg0_scaled": {"src": ("paper_2212_14052_amd/csrc/fftconv.hip", "paper_2212_14052_amd/csrc/fft_valu.h"),
-                    "sha": "571bb5a4ab0e6d7e", "fetch_kib": 73925.3, "write_kib": 131072.0,
+                    "sha": "e5b19edc34f3e309", "fetch_kib": 73925.3, "write_kib": 131072.0,
                     "valu": 54972416, "mfma": 0},
 }
 SIMDS, CLOCK_GHZ = 1024, 2.4

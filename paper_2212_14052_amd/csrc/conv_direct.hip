@@ -55,8 +55,8 @@ struct CdPlan {
 // correlation y[t] = sum_{s>=t} k[s-t] u[s] (+ D u[t]) instead.  HEADS: the rows
 // are the outer products u_i v_j of the layer with heads of 2^lg channels,
 // formed on the way into LDS instead of by a kernel of their own through
-// memory (the whole layer at L = 1024, us: B = 4, d = 1280, d_h = 8, bf16: 212 ->
-// 197; B = 6, d = 1280, d_h = 8, fp16: 302 -> 277; B = 1, d = 256, d_h = 2: 41 -> 39).
+// memory (the whole layer at L = 1024, us: B = 4, d = 1280, d_h = 8, bf16: 220 ->
+// 205; B = 6, d = 1280, d_h = 8, fp16: 300 -> 280; B = 1, d = 256, d_h = 2: 39 -> 36).
 template <int DT, int NB, int R, bool CONJ, bool HEADS>
 __global__ __launch_bounds__(64 * CD_MAXW, 4) void conv_direct_kernel(const uint16_t *u, const float *k, const float *D,
                                                                      uint16_t *y, int B, int H, int wg_per_ch,

@@ -201,10 +201,11 @@ __global__ __launch_bounds__(N / 16 >= 64 ? N / 16 : 64) void fftconv_kernel(Con
 // instead of two, and no spectrum round trip through HBM.
 //
 // Bound by VALU issue: about 1500 instructions per pair and wave at N = 2048 (90
-// of 110 us at B = 8, H = 4096, float32).  Pass twiddles from tables, the rows'
-// addresses in scalar registers and the row maxima by lane exchanges took the
-// call, with the kernel generation, from 163 to 122 us there, from 63 to 47 at
-// B = 8, H = 768, L = 2048 and from 158 to 87 at B = 5, H = 767, L = 4096, bf16.
+// of 100 us at B = 8, H = 4096, float32).  Pass twiddles from tables, the rows'
+// addresses in scalar registers, the row maxima by lane exchanges and kernel
+// generation without idle tiles took both calls from 162 to 127 us there, from 63
+// to 47 at B = 8, H = 768, L = 2048 and from 159 to 87 at B = 5, H = 767, L = 4096,
+// bf16.
 
 // Waves per SIMD: four (LDS allows 4.5 at N = 2048, four at 4096 and 8192),
 // three where 128 registers would spill.

@@ -29,9 +29,9 @@
 // miss of theirs added back.  theta scales each
 // mode so that its tables have moduli just below 1, where fp16 rounds finest.
 //
-// Bound by the serial chain of each wave at two waves per SIMD (433 VALU and
-// 38 matrix instructions per 2048 inputs): B = 2, H = 1024, L = 131072, fp16:
-// 277 us = 3.9 TB/s (305 us on a slower card, where the same loop without the
+// Bound by the serial chain of each wave at two waves per SIMD (about 440 VALU
+// and 38 matrix instructions per 2048 inputs): B = 2, H = 1024, L = 131072, fp16:
+// 270-280 us = 3.9 TB/s (305 us on a slower card, where the same loop without the
 // arithmetic took 257); chunk states and convolution before: 708 us.
 #include "common.h"
 #include "internal.h"
